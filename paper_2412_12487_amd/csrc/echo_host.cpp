@@ -3,9 +3,10 @@
 // echo_load_graph is the simulator's initialisation step (Table 8 "Init."):
 // it validates the per-rank graphs, matches collectives (Sec. 4.2 matching
 // rules), merges every collective into one barrier node, levels the merged
-// graph with Kahn's algorithm (a cycle is a deadlocked job), and lays out one
-// level-ordered walk list per walker (a group of consecutive ranks walked by one
-// wavefront) for the device.  echo_compose_batch is the
+// graph with Kahn's algorithm (a cycle is a deadlocked job), cuts every stream into
+// segments (runs of compute and memcpy ops that only follow one another), and lays out
+// one level-ordered walk list of segments and comm ops per walker (a group of
+// consecutive ranks walked by one wavefront) for the device.  echo_compose_batch is the
 // execution step: it only enqueues kernels.
 #include <hip/hip_runtime.h>
 
@@ -100,7 +101,7 @@ struct echo_graph_s {
     int device = 0;
     int64_t n_ops = 0, n_colls = 0, n_levels = 0;
     int64_t n_items = 0;               // entries of the walk lists
-    int64_t n_compute = 0;             // compute ops (overlap detection's compute records)
+    int64_t n_steps = 0;               // ops and barrier waits of the walk lists (ops + comm ops)
     int32_t n_ranks = 0, n_walkers = 0;
     int64_t capacity[kWalkVariants] = {};   // co-resident walk workgroups per kernel variant
     int64_t spin_limit = kDefaultSpinNs / 10;   // 100 MHz ticks
@@ -208,6 +209,63 @@ struct Timed {
     }
     hipError_t end() { return g->timing ? hipEventRecord(g->events[2 * slot + 1], s) : hipSuccess; }
 };
+
+// Segments that comm ops may overlap, and per comm stream of their rank the range of comm
+// ops in question (OverlapSeg, CommRange).  cl_off / cl / cl_pos: comm ops of each (rank,
+// stream) in program order.  Only the dependencies given for the ops themselves are
+// followed along the two streams, so a range may be wider than it has to be, never narrower.
+void overlap_ranges(const echo_graph_desc *d, const std::vector<int32_t> &poff, const std::vector<int32_t> &preds,
+                    const std::vector<int32_t> &seg_of, const std::vector<int32_t> &seg_off,
+                    const std::vector<SegRec> &recs, const std::vector<int64_t> &cl_off, const std::vector<int32_t> &cl,
+                    const std::vector<int32_t> &cl_pos, std::vector<OverlapSeg> *osegs, std::vector<CommRange> *ranges,
+                    int32_t *max_ranges) {
+    const int64_t n_segs = (int64_t)seg_off.size() - 1;
+    // per (compute stream, comm stream) of the current rank: positions before done finish before
+    // the compute stream's next segment starts; positions from next on are not yet known to
+    // launch after it
+    int64_t done[kStreams][kStreams], next[kStreams][kStreams];
+    int32_t rank = -1;
+    for (int64_t k = 0; k < n_segs; ++k) {
+        const int32_t first = recs[seg_off[k]].op, last = recs[seg_off[k + 1] - 1].op;
+        const int32_t r = d->op_rank[first], st = d->op_stream[first];
+        if (r != rank) {
+            rank = r;
+            for (int x = 0; x < kStreams; ++x)
+                for (int q = 0; q < kStreams; ++q) done[x][q] = next[x][q] = cl_off[(int64_t)r * kStreams + q];
+        }
+        for (int32_t j = poff[first]; j < poff[first + 1]; ++j) {
+            const int32_t u = preds[j];
+            if (cl_pos[u] >= 0) {
+                int64_t &x = done[st][d->op_stream[u]];
+                x = std::max<int64_t>(x, cl_pos[u] + 1);
+            }
+        }
+        bool compute = false;
+        for (int32_t j = seg_off[k]; j < seg_off[k + 1]; ++j) compute = compute || (recs[j].meta & kRecCompute);
+        if (!compute) continue;
+        OverlapSeg os{seg_off[k], seg_off[k + 1] - seg_off[k], first, last, (int32_t)ranges->size(), 0, {0, 0}};
+        for (int q = 0; q < kStreams; ++q) {
+            // up to the first comm op that waits for this segment's last op or a later op of its stream
+            const int64_t end = cl_off[(int64_t)r * kStreams + q + 1];
+            int64_t &hi = next[st][q];
+            while (hi < end) {
+                bool after = false;
+                for (int32_t j = poff[cl[hi]]; j < poff[cl[hi] + 1]; ++j)
+                    after = after || (seg_of[preds[j]] >= 0 && d->op_stream[preds[j]] == st && preds[j] >= last);
+                if (after) break;
+                ++hi;
+            }
+            const int64_t lo = done[st][q];
+            if (lo < hi) {
+                ranges->push_back(CommRange{(int32_t)lo, (int32_t)hi, cl[hi - 1], 0});
+                ++os.ncand;
+            }
+        }
+        if (os.ncand == 0) continue;
+        *max_ranges = std::max(*max_ranges, os.ncand);
+        osegs->push_back(os);
+    }
+}
 
 // ------------------------------------------------------------------ loader
 int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out) {
@@ -424,6 +482,47 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
     std::vector<int64_t>().swap(succ);
     std::vector<int64_t>().swap(soff);
 
+    // segments: op v joins the segment of op u when u is its only predecessor (then u is the
+    // op before it on its stream, or v is the first of its stream), both run on one stream,
+    // neither is a comm op and nothing else waits for u.  Numbered by first op, so rank-major.
+    std::vector<int32_t> seg_of(n, -1);          // segment of a compute / memcpy op
+    std::vector<int32_t> seg_off(1, 0);          // its records: [seg_off[g], seg_off[g + 1])
+    std::vector<SegRec> recs;
+    {
+        std::vector<uint8_t> succs(n, 0);        // ops waiting for each op (2: two or more)
+        for (int32_t u : preds) succs[u] = (uint8_t)std::min(succs[u] + 1, 2);
+        std::vector<int32_t> len;
+        for (int64_t v = 0; v < n; ++v) {
+            if (d->op_kind[v] == ECHO_COMM) continue;
+            if (poff[v + 1] - poff[v] == 1) {
+                const int32_t u = preds[poff[v]];
+                if (seg_of[u] >= 0 && d->op_stream[u] == d->op_stream[v] && succs[u] == 1 && len[seg_of[u]] < kSegOps) {
+                    seg_of[v] = seg_of[u];
+                    ++len[seg_of[v]];
+                    continue;
+                }
+            }
+            seg_of[v] = (int32_t)len.size();
+            len.push_back(1);
+        }
+        seg_off.resize(len.size() + 1);
+        for (size_t k = 0; k < len.size(); ++k) seg_off[k + 1] = seg_off[k] + len[k];
+        recs.resize(seg_off.back());
+        std::vector<int32_t> fill(seg_off.begin(), seg_off.end() - 1);
+        for (int64_t v = 0; v < n; ++v) {
+            const int32_t k = seg_of[v];
+            if (k < 0) continue;
+            const int32_t i = fill[k]++;
+            recs[i] = SegRec{(int32_t)v,
+                             (uint32_t)d->op_class[v] | (d->op_kind[v] == ECHO_COMPUTE ? kRecCompute : 0u) |
+                                 (i == seg_off[k] ? kRecFirst : 0u) | (i + 1 == seg_off[k + 1] ? kRecLast : 0u),
+                             d->op_dur_ns[v]};
+        }
+    }
+    const int64_t n_segs = (int64_t)seg_off.size() - 1;
+    auto is_head = [&](int64_t v) { return seg_of[v] < 0 || recs[seg_off[seg_of[v]]].op == v; };
+    auto tail_of = [&](int64_t v) { return seg_of[v] < 0 ? (int32_t)v : recs[seg_off[seg_of[v] + 1] - 1].op; };
+
     // walkers: every walk workgroup of a scenario tile must be co-resident, so a
     // graph with more ranks than the device holds wavefronts walks several
     // consecutive ranks per wavefront
@@ -531,29 +630,66 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
         }
     auto item_coll = [&](int64_t c) { return counted[c] >= 0 ? counted[c] : (int32_t)c; };
 
+    // Linked collectives: met in device memory, and on every member's stream the op before is
+    // the member of one and the same collective.  That one's finish is common to all members,
+    // so a member publishes its launch time without it -- its launch item does not wait for
+    // the collective before -- and each resolve item applies it:  the barrier is the latest
+    // of the published times and of that finish.  A data-parallel rank thus publishes all
+    // its gradient buckets as its backward pass goes by, and waits for them where the
+    // optimizer does.  link_prev[v]: the stream's previous op of a linked comm op, else -1.
+    std::vector<int32_t> link_prev(n, -1);
+    {
+        std::vector<int32_t> prev_of(n, -1);
+        std::fill(last.begin(), last.end(), -1);
+        for (int64_t v = 0; v < n; ++v) {
+            int32_t &l = last[(int64_t)d->op_rank[v] * kStreams + d->op_stream[v]];
+            prev_of[v] = l;
+            l = (int32_t)v;
+        }
+        for (int64_t c = 0; c < nc; ++c) {
+            if (coll_aux[c] & kAuxLocal) continue;
+            int64_t before = -1;
+            bool linked = true;
+            for (int64_t j = moff[c]; linked && j < moff[c + 1]; ++j) {
+                const int32_t u = prev_of[mem[j]];
+                linked = u >= 0 && d->op_kind[u] == ECHO_COMM && (j == moff[c] || d->op_coll[u] == before);
+                if (linked) before = d->op_coll[u];
+            }
+            if (!linked || cN[before] != cN[c]) continue;
+            for (int64_t j = moff[c]; j < moff[c + 1]; ++j) link_prev[mem[j]] = prev_of[mem[j]];
+        }
+    }
+
     // walk lists: each walker's ops by (key, rank, program order), key = level
-    // for compute/memcpy, the launch level for a comm op
+    // for compute/memcpy, the launch level for a comm op (of a linked one, without the op it
+    // is linked to, but not before that one's launch)
     std::vector<int32_t> key(n);
     for (int64_t v = 0; v < n; ++v) {
         if (d->op_kind[v] == ECHO_COMM) {
-            int32_t k = 0;
-            for (int32_t j = poff[v]; j < poff[v + 1]; ++j) k = std::max(k, level[node(preds[j])] + 1);
+            int32_t k = link_prev[v] >= 0 ? key[link_prev[v]] : 0;
+            for (int32_t j = poff[v]; j < poff[v + 1]; ++j)
+                if (preds[j] != link_prev[v]) k = std::max(k, level[node(preds[j])] + 1);
             key[v] = k;
         } else {
             key[v] = level[v];
         }
     }
-    std::vector<int64_t> op_off(W + 1, 0);            // ops of walker w: [op_off[w], op_off[w + 1])
-    for (int64_t v = 0; v < n; ++v) ++op_off[d->op_rank[v] / rpw + 1];
+    // the walk's nodes: every comm op and the first op of every segment
+    std::vector<int64_t> op_off(W + 1, 0);            // nodes of walker w: [op_off[w], op_off[w + 1])
+    std::vector<int32_t> order;
+    for (int64_t v = 0; v < n; ++v)                   // rank-major already
+        if (is_head(v)) {
+            order.push_back((int32_t)v);
+            ++op_off[d->op_rank[v] / rpw + 1];
+        }
     for (int64_t w = 0; w < W; ++w) op_off[w + 1] += op_off[w];
-    std::vector<int32_t> order(n);
-    for (int64_t v = 0; v < n; ++v) order[v] = (int32_t)v;   // rank-major already
     for (int64_t w = 0; w < W; ++w)
         std::stable_sort(order.begin() + op_off[w], order.begin() + op_off[w + 1],
                          [&](int32_t x, int32_t y) { return key[x] < key[y]; });
-    std::vector<WalkItem> items;
-    items.reserve(n);
-    std::vector<int64_t> walk_off(W + 1, 0);
+    std::vector<WalkItem> items;                      // rounds of kBlock items, padded with empty ones
+    items.reserve(2 * (order.size() + mem.size()));
+    std::vector<int64_t> round_off(W + 1, 0);
+    std::vector<RowPair> rows;                        // kDurs per round: its segments' first and last ops
     std::vector<int32_t> far;
     {
         const int npair = (int)(rpw * kStreams);       // (rank, stream) pairs of a walker
@@ -562,6 +698,27 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
         std::vector<int> slot(npair);
         std::vector<int32_t> first_succ(n, -1);         // walk position of a comm op's first successor
         std::vector<std::pair<int32_t, int32_t>> sched; // (position, comm op) of the resolve items
+        int32_t in_round = kBlock, segs_in_round = kDurs;   // of the walker's current round
+        WalkItem empty{};
+        empty.meta = kEmpty;
+        empty.coll = -1;
+        auto close_round = [&]() {
+            for (; in_round < kBlock; ++in_round) items.push_back(empty);
+            for (; segs_in_round < kDurs; ++segs_in_round) rows.push_back(RowPair{0, 0});
+        };
+        // the next item of the walk list; a round holds kBlock items, kDurs of them segments
+        auto emit = [&](const WalkItem &it, bool seg) {
+            if (in_round == kBlock || (seg && segs_in_round == kDurs)) {
+                close_round();
+                in_round = segs_in_round = 0;
+            }
+            items.push_back(it);
+            ++in_round;
+            if (seg) {
+                rows.push_back(RowPair{it.op, it.coll});
+                ++segs_in_round;
+            }
+        };
         auto pair_of = [&](int64_t v, int64_t r0) { return (int)((d->op_rank[v] - r0) * kStreams + d->op_stream[v]); };
         // resolve item of comm op v: its barrier wait and finish; sv = its register slot
         // (-1: none), fold: also raise slot 0 to that finish for the compute op that follows
@@ -569,15 +726,15 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
             WalkItem it{};
             it.op = v;
             it.meta = (uint32_t)kResolve | ((uint32_t)(sv >= 0 ? sv : 0) << 2) | (sv < 0 ? kNoReg : 0u) |
-                      (fold ? kFold : 0u);
+                      (fold ? kFold : 0u) | (link_prev[v] >= 0 ? kLinked : 0u);
             const int64_t c = d->op_coll[v];
             // the collective's first member slot (slot mode), else unused
             it.far_off = slot_base[c] >= 0 ? (int32_t)slot_base[c] : (int32_t)far.size();
             it.coll = item_coll(c);
             it.dur = ccls[c];    // the cost class its finish reads
-            it.nfar = 0;
+            it.nfar = link_prev[v];
             it.aux = coll_aux[d->op_coll[v]] | ((uint32_t)op_slot[v] << 5);
-            items.push_back(it);
+            emit(it, false);
         };
         for (int64_t w = 0; w < W; ++w) {
             const int64_t r0 = w * rpw, lo = op_off[w], hi = op_off[w + 1];
@@ -586,8 +743,10 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
             std::fill(busy.begin(), busy.end(), 0);
             std::fill(total.begin(), total.end(), 0);
             for (int64_t i = lo; i < hi; ++i) {
-                ++total[pair_of(i, r0)];
-                if (d->op_kind[i] != ECHO_COMM) ++busy[pair_of(i, r0)];
+                const int32_t v = order[i], k = seg_of[v];
+                const int64_t ops = k < 0 ? 1 : seg_off[k + 1] - seg_off[k];
+                total[pair_of(v, r0)] += ops;
+                if (k >= 0) busy[pair_of(v, r0)] += ops;
             }
             const int top = int(std::max_element(busy.begin(), busy.end()) - busy.begin());
             if (rpw == 1) {
@@ -603,26 +762,29 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
             }
             // Every comm op is finished by a resolve item placed right before its first
             // successor in the walk (or at the walk's end): its barrier is waited for as
-            // late as the walk allows, and every reader of its slot comes after.
+            // late as the walk allows, and every reader of its slot comes after.  A linked
+            // comm op is no successor of the op it is linked to, but that one is resolved
+            // before it (its slot then holds the finish to apply).
             sched.clear();
             for (int64_t i = lo; i < hi; ++i) {
                 const int32_t v = order[i];
                 for (int32_t j = poff[v]; j < poff[v + 1]; ++j) {
                     const int32_t u = preds[j];
-                    if (d->op_kind[u] == ECHO_COMM && first_succ[u] < 0) {
+                    if (d->op_kind[u] == ECHO_COMM && first_succ[u] < 0 && u != link_prev[v])
                         first_succ[u] = (int32_t)(i - lo);
-                        sched.emplace_back((int32_t)(i - lo), u);
-                    }
                 }
             }
-            for (int64_t i = lo; i < hi; ++i) {
+            for (int64_t i = hi - 1; i >= lo; --i) {
+                // launches of a stream are in program order, so a linked op comes after the one
+                // it is linked to: visited backwards, its own place is known
                 const int32_t v = order[i];
-                if (d->op_kind[v] == ECHO_COMM && first_succ[v] < 0) sched.emplace_back((int32_t)(hi - lo), v);
+                if (d->op_kind[v] != ECHO_COMM) continue;
+                if (first_succ[v] < 0) first_succ[v] = (int32_t)(hi - lo);
+                const int32_t u = link_prev[v];
+                if (u >= 0 && (first_succ[u] < 0 || first_succ[u] > first_succ[v])) first_succ[u] = first_succ[v];
+                sched.emplace_back(first_succ[v], v);
             }
-            std::stable_sort(sched.begin(), sched.end(),
-                             [](const std::pair<int32_t, int32_t> &x, const std::pair<int32_t, int32_t> &y) {
-                                 return x.first < y.first;
-                             });
+            std::sort(sched.begin(), sched.end());
             size_t next_due = 0;
             std::fill(latest.begin(), latest.end(), -1);
             for (int64_t i = lo; i < hi; ++i) {
@@ -630,9 +792,9 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
                 const int sv = slot[pair_of(v, r0)];
                 size_t due_end = next_due;
                 while (due_end < sched.size() && sched[due_end].first == i - lo) ++due_end;
-                // a compute/memcpy op of slot 0 whose other predecessors are exactly the comm ops
-                // resolved right before it: the resolve items raise slot 0 to their finishes and
-                // the op becomes a fast one (start = slot 0)
+                // a segment of slot 0 whose other predecessors are exactly the comm ops resolved
+                // right before it: the resolve items raise slot 0 to their finishes, and the
+                // segment starts at slot 0
                 bool fold = due_end > next_due && d->op_kind[v] != ECHO_COMM && sv == 0;
                 for (int32_t j = poff[v]; fold && j < poff[v + 1]; ++j) {
                     const int32_t u = preds[j];
@@ -642,42 +804,43 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
                     const int32_t u = sched[next_due].second;
                     emit_resolve(u, slot[pair_of(u, r0)], fold);
                 }
-                unsigned mask = 0;
+                unsigned mask = fold ? 1u : 0u;
                 const int64_t f0 = (int64_t)far.size();
                 for (int32_t j = poff[v]; j < poff[v + 1]; ++j) {
                     const int32_t u = preds[j];
+                    if (u == link_prev[v]) continue;               // applied by the resolve item
                     if (fold && u != latest[0]) continue;          // folded into slot 0
                     const int su = slot[pair_of(u, r0)];
                     if (su >= 0 && latest[su] == u) mask |= 1u << su;
                     else far.push_back(u);
                 }
-                if (sv >= 0) latest[sv] = v;
-                const bool fast = d->op_kind[v] != ECHO_COMM && sv == 0 && (mask & ~1u) == 0 &&
-                                  (int64_t)far.size() == f0;
+                if (sv >= 0) latest[sv] = tail_of(v);
                 WalkItem it{};
                 it.op = v;
-                it.meta = (uint32_t)d->op_kind[v] | ((uint32_t)(sv >= 0 ? sv : 0) << 2) |
-                          ((uint32_t)d->op_class[v] << 5) | (mask << 8) | (fast ? kFast : 0u) |
-                          (sv < 0 ? kNoReg : 0u);
                 it.nfar = (int32_t)((int64_t)far.size() - f0);
                 it.far_off = (int32_t)f0;
-                it.coll = d->op_kind[v] == ECHO_COMM ? item_coll(d->op_coll[v]) : -1;
-                it.aux = d->op_kind[v] == ECHO_COMM
-                             ? coll_aux[d->op_coll[v]] | ((uint32_t)op_slot[v] << 5)
-                             : 0u;
+                it.meta = (uint32_t)d->op_kind[v] | ((uint32_t)(sv >= 0 ? sv : 0) << 2) | (mask << 8) |
+                          (it.nfar > 0 ? kHasFar : 0u) | (sv < 0 ? kNoReg : 0u) | (link_prev[v] >= 0 ? kLinked : 0u);
                 if (d->op_kind[v] == ECHO_COMM) {
                     const int64_t c = d->op_coll[v];
+                    it.coll = item_coll(c);
+                    it.aux = coll_aux[c] | ((uint32_t)op_slot[v] << 5);
                     it.dur = slot_base[c] >= 0 ? slot_base[c] + op_member[v] : 0;   // this member's slot
                 } else {
-                    it.dur = d->op_dur_ns[v];
+                    const int32_t k = seg_of[v];
+                    it.coll = tail_of(v);
+                    it.aux = seg_off[k + 1] - seg_off[k];
+                    it.dur = 0;
+                    for (int32_t j = seg_off[k]; j < seg_off[k + 1]; ++j) it.dur += recs[j].dur;
                 }
-                items.push_back(it);
+                emit(it, d->op_kind[v] != ECHO_COMM);
             }
             while (next_due < sched.size()) {
                 const int32_t u = sched[next_due++].second;
                 emit_resolve(u, slot[pair_of(u, r0)], false);
             }
-            walk_off[w + 1] = (int64_t)items.size();
+            close_round();
+            round_off[w + 1] = (int64_t)items.size() / kBlock;
         }
     }
     if ((int64_t)far.size() > kI32Max || (int64_t)items.size() > kI32Max)
@@ -688,7 +851,8 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
         std::vector<uint8_t> written(n_slots, 0);
         for (const WalkItem &it : items) {
             const uint32_t x = (uint32_t)it.aux;
-            if ((x & kAuxLocal) || !(x & kAuxSlots)) continue;
+            const int kind = item_kind(it.meta);
+            if ((it.meta & kEmpty) || (kind != ECHO_COMM && kind != kResolve) || (x & kAuxLocal) || !(x & kAuxSlots)) continue;
             const int64_t c = it.coll, base = slot_base[c], N = aux_expected(x);
             if (base < 0 || N != cN[c])
                 return fail(ECHO_ERR_ARG, "internal: collective %lld has an inconsistent slot layout", (long long)c);
@@ -703,83 +867,55 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
             if (!written[k]) return fail(ECHO_ERR_ARG, "internal: member slot %lld is never written", (long long)k);
     }
     {
-        // what a pass without caller-visible timelines must still store
-        std::vector<uint32_t> need(n, 0);
-        for (int32_t u : far) need[u] |= kNeedF;
-        // the last op of every overlap-detection block of a (rank, stream) compute list
-        std::vector<int32_t> n_compute(R * kStreams, 0), i_compute(R * kStreams, 0);
-        for (int64_t v = 0; v < n; ++v)
-            if (d->op_kind[v] == ECHO_COMPUTE) ++n_compute[(int64_t)d->op_rank[v] * kStreams + d->op_stream[v]];
-        for (int64_t v = 0; v < n; ++v)
-            if (d->op_kind[v] == ECHO_COMPUTE) {
-                const int64_t k = (int64_t)d->op_rank[v] * kStreams + d->op_stream[v];
-                const int32_t i = i_compute[k]++;
-                if (i % kOverlapBlock == kOverlapBlock - 1 || i == n_compute[k] - 1) need[v] |= kNeedF;
-            }
-        std::vector<int32_t> prev_on_stream(R * kStreams, -1);
-        for (int64_t v = 0; v < n; ++v) {
-            const int64_t k = (int64_t)d->op_rank[v] * kStreams + d->op_stream[v];
-            const int32_t prev = prev_on_stream[k];
-            prev_on_stream[k] = (int32_t)v;
-            if (d->op_kind[v] == ECHO_COMM) {
-                need[v] |= kNeedS | kNeedF;
-            } else if (d->op_kind[v] == ECHO_COMPUTE) {
-                const bool chained = prev >= 0 && d->op_kind[prev] == ECHO_COMPUTE && poff[v + 1] - poff[v] == 1 &&
-                                     preds[poff[v]] == prev;
-                if (!chained) need[v] |= kNeedS;
-            }
+        // what a pass that stores nothing else must still store
+        std::vector<uint8_t> need(n, 0);
+        for (int32_t u : far) need[u] = 1;
+        for (int32_t u : link_prev)
+            if (u >= 0) need[u] = 1;         // read back where the stream has no slot
+        for (WalkItem &it : items) {
+            if (it.meta & kEmpty) continue;
+            const bool comm = item_kind(it.meta) == ECHO_COMM || item_kind(it.meta) == kResolve;
+            if (need[comm ? it.op : it.coll]) it.meta |= kNeedF;
         }
-        for (WalkItem &it : items)
-            if (item_kind(it.meta) != kResolve) it.meta |= need[it.op];
     }
 
-    // per (rank, stream) comm and compute op lists in program order
-    std::vector<int64_t> cl_off(R * kStreams + 1, 0), cp_off(R * kStreams + 1, 0);
-    for (int64_t v = 0; v < n; ++v) {
-        const int64_t k = (int64_t)d->op_rank[v] * kStreams + d->op_stream[v];
-        if (d->op_kind[v] == ECHO_COMM) ++cl_off[k + 1];
-        else if (d->op_kind[v] == ECHO_COMPUTE) ++cp_off[k + 1];
-    }
-    for (int64_t k = 0; k < R * kStreams; ++k) {
-        cl_off[k + 1] += cl_off[k];
-        cp_off[k + 1] += cp_off[k];
-    }
-    int32_t max_comm_streams = 0;
-    for (int64_t r = 0; r < R; ++r) {
-        int32_t k = 0;
-        for (int st = 0; st < kStreams; ++st) k += cl_off[r * kStreams + st + 1] > cl_off[r * kStreams + st];
-        max_comm_streams = std::max(max_comm_streams, k);
-    }
+    // comm ops of each (rank, stream) in program order
+    std::vector<int64_t> cl_off(R * kStreams + 1, 0);
+    for (int64_t v = 0; v < n; ++v)
+        if (d->op_kind[v] == ECHO_COMM) ++cl_off[(int64_t)d->op_rank[v] * kStreams + d->op_stream[v] + 1];
+    for (int64_t k = 0; k < R * kStreams; ++k) cl_off[k + 1] += cl_off[k];
     std::vector<int32_t> cl(cl_off.back()), cl_coll(cl_off.back());
+    std::vector<int32_t> cl_pos(n, -1);               // position of a comm op in the lists
     std::vector<uint8_t> cl_type(cl_off.back());
-    std::vector<ComputeRec> cp(cp_off.back());
-    std::vector<int32_t> cp_pos(cp_off.back());
     {
-        // overlap detection writes its per-op outputs where the walk reads them: at the
-        // row of the op's item (resolve items aside, every op has exactly one)
-        std::vector<int32_t> item_pos(n, -1);
-        for (size_t i = 0; i < items.size(); ++i)
-            if (item_kind(items[i].meta) != kResolve) item_pos[items[i].op] = (int32_t)i;
-        std::vector<int64_t> fl(cl_off.begin(), cl_off.end() - 1), fp(cp_off.begin(), cp_off.end() - 1);
-        std::vector<int32_t> prev_on_stream(R * kStreams, -1);
+        std::vector<int64_t> fl(cl_off.begin(), cl_off.end() - 1);
         for (int64_t v = 0; v < n; ++v) {
-            const int64_t k = (int64_t)d->op_rank[v] * kStreams + d->op_stream[v];
-            const int32_t prev = prev_on_stream[k];
-            prev_on_stream[k] = (int32_t)v;
-            if (d->op_kind[v] == ECHO_COMM) {
-                cl_type[fl[k]] = d->coll_type[d->op_coll[v]];
-                cl_coll[fl[k]] = (int32_t)d->op_coll[v];
-                cl[fl[k]++] = (int32_t)v;
-            } else if (d->op_kind[v] == ECHO_COMPUTE) {
-                // chained: the only predecessor is the previous op of the stream, a compute op
-                const bool chained = prev >= 0 && d->op_kind[prev] == ECHO_COMPUTE && poff[v + 1] - poff[v] == 1 &&
-                                     preds[poff[v]] == prev;
-                cp_pos[fp[k]] = item_pos[v];
-                cp[fp[k]++] = ComputeRec{(int32_t)v, (uint32_t)d->op_class[v] | (chained ? kChained : 0u),
-                                         d->op_dur_ns[v]};
-            }
+            if (d->op_kind[v] != ECHO_COMM) continue;
+            const int64_t i = fl[(int64_t)d->op_rank[v] * kStreams + d->op_stream[v]]++;
+            cl_type[i] = d->coll_type[d->op_coll[v]];
+            cl_coll[i] = (int32_t)d->op_coll[v];
+            cl[i] = (int32_t)v;
+            cl_pos[v] = (int32_t)i;
         }
     }
+    std::vector<OverlapSeg> osegs;
+    std::vector<CommRange> ranges;
+    int32_t max_ranges = 0;
+    overlap_ranges(d, poff, preds, seg_of, seg_off, recs, cl_off, cl, cl_pos, &osegs, &ranges, &max_ranges);
+    if ((int64_t)ranges.size() > kI32Max) return fail(ECHO_ERR_RANGE, "overlap ranges exceed 2^31 entries");
+
+    // chunks of whole segments, at most 64 records each
+    std::vector<RecChunk> chunks(1, RecChunk{0, 0});
+    for (int64_t k = 0, os = 0; k < n_segs; ++k) {
+        if (seg_off[k + 1] - chunks.back().rec0 > kLanes) chunks.push_back(RecChunk{seg_off[k], (int32_t)os});
+        if (os < (int64_t)osegs.size() && osegs[os].rec0 == seg_off[k]) {
+            recs[seg_off[k]].meta |= kRecCand;
+            ++os;
+        }
+    }
+    const int64_t n_chunks = n_segs > 0 ? (int64_t)chunks.size() : 0;
+    chunks.resize(n_chunks);
+    chunks.push_back(RecChunk{(int32_t)recs.size(), (int32_t)osegs.size()});
     HostCollTable colls(nc), cls((int64_t)classes.size());
     for (int64_t c = 0; c < nc; ++c) colls.set(c, d->coll_type[c], d->coll_bytes[c], kN[c], kM[c], kK[c]);
     for (size_t k = 0; k < classes.size(); ++k)
@@ -792,7 +928,7 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
     g->device = device;
     g->n_ops = n;
     g->n_items = (int64_t)items.size();
-    g->n_compute = (int64_t)cp.size();
+    g->n_steps = n + (int64_t)mem.size();
     g->n_colls = nc;
     g->n_levels = n_levels;
     g->n_ranks = (int32_t)R;
@@ -807,7 +943,10 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
     dg.n_ranks = (int32_t)R;
     dg.n_walkers = (int32_t)W;
     dg.n_blocks = (int32_t)nblk;
-    dg.max_comm_streams = max_comm_streams;
+    dg.n_recs = (int64_t)recs.size();
+    dg.n_chunks = n_chunks;
+    dg.n_osegs = (int64_t)osegs.size();
+    dg.max_ranges = max_ranges;
     dg.n_slots = n_slots;
     dg.n_counted = (int64_t)counted_coll.size();
     g->counted_coll = std::move(counted_coll);
@@ -822,7 +961,8 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
         }                                                                   \
     } while (0)
     UP(dg.items, items);
-    UP(dg.walk_off, walk_off);
+    UP(dg.round_off, round_off);
+    UP(dg.walk_rows, rows);
     UP(dg.far, far);
     for (int t = 0; t < 2; ++t) {
         HostCollTable &h = t == 0 ? colls : cls;
@@ -840,13 +980,13 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
     UP(dg.members, cN);
     UP(dg.counted_members, counted_N);
     UP(dg.block_class, block_class);
-    UP(dg.cl_off, cl_off);
+    UP(dg.recs, recs);
+    UP(dg.chunks, chunks);
+    UP(dg.osegs, osegs);
+    UP(dg.ranges, ranges);
     UP(dg.cl, cl);
     UP(dg.cl_type, cl_type);
     UP(dg.cl_coll, cl_coll);
-    UP(dg.cp_off, cp_off);
-    UP(dg.cp, cp);
-    UP(dg.cp_pos, cp_pos);
     UP(dg.status, std::vector<unsigned>(1, 0u));
 #undef UP
     *out = g;
@@ -859,9 +999,9 @@ struct Workspace {
     unsigned long long *arrive = nullptr;  // [coll][scen] latest member launch
     unsigned *count = nullptr;             // [coll][tile] members arrived
     int64_t *slots = nullptr;              // [slot][scen] member launch times (slot collectives)
-    uint8_t *tmask = nullptr;              // [item + kBlock][mstride] overlap masks (refined passes)
+    uint8_t *tmask = nullptr;              // [segment record][mstride] overlap masks (refined passes)
     uint32_t *ext = nullptr;               // same rows: prorated / ensemble extra times
-    uint8_t *xflag = nullptr;              // [row][tile]: the row has a nonzero mask or extra time
+    uint8_t *xflag = nullptr;              // [overlap segment][tile]: it has a nonzero mask or extra time
     unsigned *chg = nullptr;               // [scen] change flags + 1 stability word (until_stable)
     int64_t *start = nullptr, *finish = nullptr, *step = nullptr;   // timelines (caller's or workspace)
 };
@@ -887,10 +1027,9 @@ int check_compose(echo_graph g, const echo_scenario *d_scen, int32_t n_scen, con
         return fail(ECHO_ERR_ARG, "n_scen must be >= 1 and 0 <= n_refine <= 64 (got %d, %d)", n_scen, n_refine);
     sh->ns = n_scen;
     sh->n_tiles = (int32_t)((sh->ns + kLanes - 1) / kLanes);
-    // per-item outputs of overlap detection: whole tiles of columns, and one round of
-    // rows past the last item (the walk fetches a round's rows at once)
+    // per-op outputs of overlap detection: whole tiles of columns
     sh->mstride = (int64_t)sh->n_tiles * kLanes;
-    sh->mrows = g->n_items + kBlock;
+    sh->mrows = g->dg.n_recs;
     return ECHO_OK;
 }
 
@@ -903,11 +1042,10 @@ int ensure_workspace(echo_graph g, const ComposeShape &sh, int32_t n_refine, int
     if ((rc = ensure(&g->arrive, &g->arrive_n, (size_t)(g->dg.n_counted * ns), "arrivals"))) return rc;
     if ((rc = ensure(&g->count, &g->count_n, (size_t)(g->dg.n_counted * sh.n_tiles), "arrival counts"))) return rc;
     if ((rc = ensure(&g->slots, &g->slots_n, (size_t)(g->dg.n_slots * ns), "member slots"))) return rc;
-    // overlap masks, then one flag byte per (item row, tile): whether the row has a nonzero one
+    // overlap masks (extra times), then one flag byte per (segment, tile): whether it has a nonzero one
     if (n_refine > 0 && !sh.ext &&
         (rc = ensure(&g->tmask, &g->tmask_n, (size_t)(sh.mrows * (sh.mstride + sh.n_tiles)), "overlap masks")))
         return rc;
-    // extra times, then one flag byte per (item row, tile): whether the row has a nonzero one
     if (sh.ext && (rc = ensure(&g->ext, &g->ext_n,
                                (size_t)(sh.mrows * sh.mstride + (sh.mrows * sh.n_tiles + 3) / 4), "extra times")))
         return rc;
@@ -934,7 +1072,7 @@ int ensure_workspace(echo_graph g, const ComposeShape &sh, int32_t n_refine, int
 // Enqueue one compose: init, class costs, pass 1, then per refinement overlap
 // detection (+ settle) and the refined pass.  `timed`: record kernel events.
 int enqueue_compose(echo_graph g, const echo_scenario *d_scen, int32_t n_scen, const echo_validator &val,
-                    const ComposeShape &sh, const Workspace &ws, bool store_all, uint64_t *d_digest,
+                    const ComposeShape &sh, const Workspace &ws, bool timelines, uint64_t *d_digest,
                     int32_t *d_refinements, hipStream_t stream, bool timed) {
     const int32_t n_refine = val.max_refine;
     const int64_t ns = sh.ns;
@@ -961,42 +1099,26 @@ int enqueue_compose(echo_graph g, const echo_scenario *d_scen, int32_t n_scen, c
         return hip_fail(e, "fill kernel");
     if (d_refinements && (e = launch_fill_i32(d_refinements, ns, until_stable ? 0 : n_refine, stream)))
         return hip_fail(e, "fill kernel");
-    // extra-time row flags start clear; overlap detection only sets them
-    if (ext && n_refine > 0 &&
-        (e = launch_fill_i32(reinterpret_cast<int32_t *>(ws.xflag), (sh.mrows * sh.n_tiles + 3) / 4, 0, stream)))
-        return hip_fail(e, "fill kernel");
-
     for (int32_t p = 0; p <= n_refine; ++p) {
-        // tiles per walk launch: every rank block of a tile must be co-resident (a final mask
-        // pass may run either mask variant, so both count)
-        const bool fin = p == n_refine, mask_pass = p > 0 && !ext;
-        int64_t cap = g->capacity[walk_variant(walk_input(p > 0, ext, false), fin, d_digest != nullptr)];
-        if (fin && mask_pass)
-            cap = std::min(cap, g->capacity[walk_variant(kInMaskFlags, true, d_digest != nullptr)]);
+        // tiles per walk launch: every rank block of a tile must be co-resident
+        const bool fin = p == n_refine;
+        const int64_t cap = g->capacity[walk_variant(walk_input(p > 0, ext, false), fin, d_digest != nullptr)];
         int64_t per_launch = std::max<int64_t>(1, std::min<int64_t>(n_tiles, cap / g->dg.n_blocks));
         if (g->max_launch_tiles > 0) per_launch = std::min<int64_t>(per_launch, g->max_launch_tiles);
-        // A final mask pass whose launches average at least kFlagRowTiles tiles writes enough
-        // timelines per unit of its chain of items for the fetched bytes to count, and fetches
-        // only the flagged mask rows; with fewer tiles per launch it is bound by the chain and
-        // fetches whole rows (measured on the 1024-rank graph: three tiles in one launch gain
-        // 1.35 ms, four 1.3 ms, two neither gain nor lose; one-tile 32-scenario graphs lose
-        // 0.5-2 ms, the 8192-rank graph's one tile per launch 1.1 ms per launch).
-        const int64_t n_launches = (n_tiles + per_launch - 1) / per_launch;
-        const bool flag_rows = fin && n_tiles >= kFlagRowTiles * n_launches;
         if (p > 0) {
             OverlapArgs o{};
-            o.cl_off = g->dg.cl_off;
-            o.cp_off = g->dg.cp_off;
+            o.osegs = g->dg.osegs;
+            o.ranges = g->dg.ranges;
+            o.n_osegs = g->dg.n_osegs;
+            o.recs = g->dg.recs;
             o.cl = g->dg.cl;
             o.cl_type = g->dg.cl_type;
-            o.cp = g->dg.cp;
             o.scen = d_scen;
             o.start = ws.start;
             o.finish = ws.finish;
             o.tmask = ext ? nullptr : ws.tmask;
             o.ext = ext ? ws.ext : nullptr;
             o.xflag = ws.xflag;
-            o.cp_pos = g->dg.cp_pos;
             o.mstride = sh.mstride;
             o.chg = until_stable ? ws.chg : nullptr;
             o.stable = stable;
@@ -1015,11 +1137,9 @@ int enqueue_compose(echo_graph g, const echo_scenario *d_scen, int32_t n_scen, c
             o.prorate = prorate;
             o.n_scen = n_scen;
             o.n_tiles = n_tiles;
-            o.n_ranks = g->n_ranks;
             o.prev_refined = p > 1;
-            o.max_comm_streams = g->dg.max_comm_streams;
             o.status = g->dg.status;
-            TIMED(ECHO_K_OVERLAP, launch_overlap(o, g->n_ranks, stream), "overlap kernel");
+            TIMED(ECHO_K_OVERLAP, launch_overlap(o, g->dg.max_ranges, stream), "overlap kernel");
             if (until_stable && (e = launch_settle(ws.chg, n_scen, d_refinements, stable, stream)))
                 return hip_fail(e, "settle kernel");
             TIMED(ECHO_K_CLEAR, launch_clear(ws.arrive, n_arrive, ws.count, n_count, ws.slots, n_slot_values, stream),
@@ -1028,7 +1148,11 @@ int enqueue_compose(echo_graph g, const echo_scenario *d_scen, int32_t n_scen, c
         for (int64_t t0 = 0; t0 < n_tiles; t0 += per_launch) {
             WalkArgs a;
             a.items = g->dg.items;
-            a.walk_off = g->dg.walk_off;
+            a.round_off = g->dg.round_off;
+            a.rows = g->dg.walk_rows;
+            a.recs = g->dg.recs;
+            a.chunks = g->dg.chunks;
+            a.n_chunks = g->dg.n_chunks;
             a.far = g->dg.far;
             a.c_N = g->dg.counted_members;
             a.block_class = g->dg.block_class;
@@ -1053,9 +1177,9 @@ int enqueue_compose(echo_graph g, const echo_scenario *d_scen, int32_t n_scen, c
             a.tile0 = (int32_t)t0;
             a.tiles = (int32_t)std::min<int64_t>(per_launch, n_tiles - t0);
             a.n_walkers = g->n_walkers;
-            a.final_pass = p == n_refine;
-            a.store_all = p == n_refine && store_all;
-            a.flag_rows = flag_rows;
+            a.in = walk_input(p > 0, ext, fin && n_tiles >= kFlagRowTiles * ((n_tiles + per_launch - 1) / per_launch));
+            a.final_pass = fin;
+            a.timelines = fin && timelines;
             if (g->n_ranks == 0 || g->n_ops == 0) continue;
             TIMED(ECHO_K_WALK, launch_walk(a, g->dg.n_blocks, stream), "walk kernel");
         }
@@ -1094,12 +1218,13 @@ int walk_chain(echo_graph g, const int64_t w[3], int64_t out[4]) {
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     if (n_items > 0 && (e = hipMemcpy(items.data(), g->dg.items, n_items * sizeof(WalkItem), hipMemcpyDeviceToHost)))
         return hip_fail(e, "walk list download");
-    if (W > 0 && (e = hipMemcpy(off.data(), g->dg.walk_off, (W + 1) * sizeof(int64_t), hipMemcpyDeviceToHost)))
+    if (W > 0 && (e = hipMemcpy(off.data(), g->dg.round_off, (W + 1) * sizeof(int64_t), hipMemcpyDeviceToHost)))
         return hip_fail(e, "walk offsets download");
     if (nc > 0 && (e = hipMemcpy(members.data(), g->dg.members, nc * sizeof(int32_t), hipMemcpyDeviceToHost)))
         return hip_fail(e, "member counts download");
     std::vector<Pt> cur(W), cmax(nc);
     std::vector<int32_t> arrived(nc, 0), wait_head(nc, -1), wait_next(W, -1);
+    for (int64_t &x : off) x *= kBlock;
     std::vector<int64_t> pos(off.begin(), off.end() - (W > 0 ? 1 : 0));
     std::vector<int32_t> runnable;
     for (int64_t x = W - 1; x >= 0; --x) runnable.push_back((int32_t)x);
@@ -1110,6 +1235,10 @@ int walk_chain(echo_graph g, const int64_t w[3], int64_t out[4]) {
         for (; pos[x] < off[x + 1]; ++pos[x]) {
             WalkItem it = items[pos[x]];
             const int kind = item_kind(it.meta);
+            if (it.meta & kEmpty) {
+                ++done;
+                continue;
+            }
             if ((kind == ECHO_COMM || kind == kResolve) && !((uint32_t)it.aux & (kAuxLocal | kAuxSlots))) {
                 if (it.coll < 0 || it.coll >= (int32_t)g->counted_coll.size())
                     return fail(ECHO_ERR_ARG, "internal: walk item of op %d has no counted collective", it.op);
@@ -1127,9 +1256,9 @@ int walk_chain(echo_graph g, const int64_t w[3], int64_t out[4]) {
                 p.len += w[0] + (local ? w[1] : w[2]);
                 (local ? p.loc : p.glob) += 1;
             } else {
-                p.len += w[0];
+                p.len += w[0] * (kind == ECHO_COMM ? 1 : it.aux);     // a segment: one item per op
             }
-            p.items += 1;
+            p.items += kind == ECHO_COMM || kind == kResolve ? 1 : it.aux;
             cur[x] = p;
             ++done;
             if (kind == ECHO_COMM) {
@@ -1245,7 +1374,7 @@ int echo_compose_batch_static(echo_graph g, const echo_scenario *d_scen, int32_t
             g->dg.classes.n * sh.ns * (int64_t)sizeof(int64_t),              // class costs
             g->dg.n_counted * sh.ns * (int64_t)sizeof(unsigned long long),   // arrival maxima
             g->dg.n_counted * sh.n_tiles * (int64_t)sizeof(unsigned),         // arrival counts
-            n_refine > 0 ? sh.mrows * (sh.mstride + sh.n_tiles) : 0,         // overlap masks and row flags
+            n_refine > 0 ? (g->n_steps + kBlock) * (sh.mstride + sh.n_tiles) : 0,   // overlap masks and flags
             g->dg.n_slots * sh.ns * (int64_t)sizeof(int64_t),               // member slots
         };
         int64_t offs[5], total = 0;
@@ -1261,7 +1390,7 @@ int echo_compose_batch_static(echo_graph g, const echo_scenario *d_scen, int32_t
             return fail(ECHO_ERR_RANGE,
                         "the allocation-free compose needs more workspace than its fixed %lld-byte array "
                         "(%lld scenarios, %lld collectives, %lld walk items)",
-                        (long long)kCap, (long long)sh.ns, (long long)g->n_colls, (long long)g->n_items);
+                        (long long)kCap, (long long)sh.ns, (long long)g->n_colls, (long long)g->n_steps);
         hipError_t e = hipSetDevice(g->device);
         if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
         uint8_t *const base = static_cast<uint8_t *>(g->scratch);
@@ -1460,13 +1589,13 @@ static int set_forest(echo_graph g, const echo_tree_node *nodes, int64_t n_nodes
         if ((e = upload(&fx.words, words)) || (e = upload(&fx.thr, thr)) || (e = upload(&fx.cbin, cbin)) ||
             (e = hipMalloc(reinterpret_cast<void **>(&fx.coll_bin), sizeof(int32_t) * 2 * std::max<int64_t>(g->n_colls, 1))) ||
             (e = hipMalloc(reinterpret_cast<void **>(&fx.cp_bin),
-                           sizeof(int32_t) * std::max<int64_t>(g->n_compute, 1)))) {
+                           sizeof(int32_t) * std::max<int64_t>(g->dg.n_recs, 1)))) {
             free_compact(fx);
             return nomem(e);
         }
-        // per-collective and per-compute-record bins, computed on the device where the
+        // per-collective and per-record bins, computed on the device where the
         // graph's sizes and durations live
-        if ((e = launch_forest_bins(g->dg, g->n_compute, fx, nullptr)) || (e = hipDeviceSynchronize())) {
+        if ((e = launch_forest_bins(g->dg, g->dg.n_recs, fx, nullptr)) || (e = hipDeviceSynchronize())) {
             free_compact(fx);
             return hip_fail(e, "ensemble bins");
         }

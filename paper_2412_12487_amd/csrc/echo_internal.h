@@ -1,16 +1,22 @@
 // echo_internal.h -- device data layout and kernel launchers of libecho.so.
 //
-// The loader turns the caller's per-rank graphs into one "walk list" per
-// walker: a walker is a group of consecutive ranks (one rank unless the graph
-// has more ranks than the device holds co-resident wavefronts), and its list
-// holds their ops ordered by (key, rank, program order) where key is the op's
-// topological level in the merged graph (a collective merged into one barrier
-// node) -- for a comm op, the level at which it can launch.  A wavefront walks
-// one walker for 64 scenarios (one lane each); predecessors that are the
-// latest op of a register slot stay in registers, the rest are read back from
-// the finish array.  Collective barriers are met through per-(collective,
-// scenario) arrival maxima and per-(collective, scenario tile) arrival counts,
-// or in LDS when every member sits in one workgroup.
+// The loader first cuts every (rank, stream) into segments: runs of compute and
+// memcpy ops in which each op's only predecessor is the one before it and nothing
+// else waits for an op inside the run.  A segment starts when its first op may and
+// then runs for the sum of its ops' durations, so the composer's sweep walks
+// segments instead of ops; the ops' own times are prefix sums from the segment's
+// start, written by a parallel kernel after the last sweep.
+//
+// The sweep follows one "walk list" per walker: a walker is a group of consecutive
+// ranks (one rank unless the graph has more ranks than the device holds co-resident
+// wavefronts), and its list holds their segments and comm ops ordered by (key, rank,
+// program order) where key is the first op's topological level in the merged graph (a
+// collective merged into one barrier node) -- for a comm op, the level at which it can
+// launch.  A wavefront walks one walker for 64 scenarios (one lane each); predecessors
+// that are the latest op of a register slot stay in registers, the rest are read back
+// from the finish array.  Collective barriers are met through per-(collective,
+// scenario) arrival maxima and per-(collective, scenario tile) arrival counts, through
+// member slots, or in LDS when every member sits in one workgroup.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -32,44 +38,62 @@ constexpr unsigned kStatusOverflow = 2u;         // a time reached 2^62
 constexpr unsigned kStatusTimeout = 4u;          // a barrier wait exceeded the spin limit
 constexpr unsigned kStatusAbort = 8u;            // stop all waits (set with timeout)
 
-// One entry of a walk list (32 bytes, read wave-uniformly).  The (rank,
-// stream) pairs of a walker are mapped to eight register "slots": slot 0 is
-// its busiest compute/memcpy stream, so most items only touch slot 0.  Pairs
+// Ops of a segment, at most.  Longer runs are cut into consecutive segments: 32 keeps
+// the parallel kernels' units even (two segments fill a 64-record chunk) while the sweep
+// already skips nearly every op of the GPT graphs' runs of 8 to 30 ops.
+constexpr int kSegOps = 32;
+
+// One op of a segment (16 bytes); the records of a segment are contiguous, in order.
+struct SegRec {
+    int32_t op;
+    uint32_t meta;      // class | kRecCompute | kRecFirst | kRecLast | kRecCand
+    int64_t dur;        // base duration
+};
+static_assert(sizeof(SegRec) == 16, "segment record must stay 16 bytes");
+constexpr uint32_t kRecCompute = 8u;     // a compute op (else memcpy: never inflated)
+constexpr uint32_t kRecFirst = 16u;      // first op of its segment
+constexpr uint32_t kRecLast = 32u;       // last op of its segment
+constexpr uint32_t kRecCand = 64u;       // on a first op: overlap detection looks at the segment
+
+// One entry of a walk list (32 bytes, read wave-uniformly): a segment or a comm op.
+// The (rank, stream) pairs of a walker are mapped to eight register "slots": slot 0
+// is its busiest compute/memcpy stream, so most items only touch slot 0.  Pairs
 // left without a slot (a walker of several ranks) keep nothing in registers:
 // their ops carry kNoReg and their successors read them back from memory.
 // A comm op's launch item publishes its arrival; a resolve item placed right
 // before its first successor waits for the barrier and writes its finish (to its
 // slot, or only to memory without one).
 struct WalkItem {
-    int32_t op;         // op id: row of the [op][scenario] outputs
-    uint32_t meta;      // kind | slot << 2 | class << 5 | regmask << 8 | fast << 16 | noreg << 17
-                        // | need start << 18 | need finish << 19 | fold << 20
+    int32_t op;         // op id: row of the [op][scenario] outputs (a segment: its first op)
+    uint32_t meta;      // kind | slot << 2 | regmask << 8 | has far << 16 | noreg << 17
+                        // | linked << 18 | need finish << 19 | fold << 20 | empty << 31
     int32_t far_off;    // predecessors read back from memory: far[far_off .. +nfar)
-    int32_t coll;       // collective of a comm op, -1 otherwise; of a collective met by counting
-                        // arrivals in device memory (neither in LDS nor through member slots),
-                        // its index among those collectives
-    int64_t dur;        // base duration of compute / memcpy ops; resolve item: cost class
+    int32_t coll;       // segment: its last op.  Comm op: its collective; of a collective met
+                        // by counting arrivals in device memory (neither in LDS nor through
+                        // member slots), its index among those collectives
+    int64_t dur;        // sum of a segment's base durations; resolve item: cost class
     int32_t nfar;
-    int32_t aux;
+    int32_t aux;        // segment: number of ops
 };
 static_assert(sizeof(WalkItem) == 32, "walk item must stay 32 bytes");
 
-// A "fast" item is a compute/memcpy op on slot 0 whose start is slot 0's value:
-// its only predecessors are the previous op of slot 0 and comm ops whose resolve
-// items, right before it, folded their finishes into slot 0 (kFold).
-constexpr uint32_t kFast = 1u << 16;
+// The item has predecessors to read back from memory.
+constexpr uint32_t kHasFar = 1u << 16;
 // The op's (rank, stream) pair has no register slot.
 constexpr uint32_t kNoReg = 1u << 17;
-// A pass that does not produce the caller's timelines stores only what later
-// steps read back: the start (kNeedS) of comm ops and of compute ops that do not
-// simply follow the previous compute op of their stream (overlap detection
-// rebuilds the others), and the finish (kNeedF) of comm ops and of ops read as
-// far predecessors.
-constexpr uint32_t kNeedS = 1u << 18;
+// Comm op linked to the comm op before it on its stream: the launch item publishes a launch
+// time that leaves that op's finish out (and stores it in the start row), the resolve item
+// takes the finish from the stream's slot (without one, from the row of op nfar) and
+// applies it.
+constexpr uint32_t kLinked = 1u << 18;
+// The op's finish is read as a far predecessor: stored also by a pass that stores nothing
+// else (the last one, when neither timelines nor digests are asked for).
 constexpr uint32_t kNeedF = 1u << 19;
 // Resolve item: after writing the comm op's finish, raise slot 0 to it.
 constexpr uint32_t kFold = 1u << 20;
-// Item kind (besides compute/comm/memcpy) that finishes a kNoReg comm op:
+// Padding at the end of a round.
+constexpr uint32_t kEmpty = 1u << 31;
+// Item kind (besides compute/comm/memcpy) that finishes a comm op:
 // wait for its barrier, then write its finish.
 constexpr int kResolve = 3;
 
@@ -80,8 +104,16 @@ constexpr int kResolve = 3;
 // looked up per cost class -- the (type, S, N, M, K) tuple that fixes T(c, s)
 // for a scenario -- and a block stages its most used classes in LDS.
 constexpr int kBlockWalkers = 8;
-constexpr int kFlagRowTiles = 2;    // final mask passes of this many tiles per launch fetch only flagged rows
-constexpr int kBlock = 32;          // walk items fetched (and overlap masks staged) per round
+constexpr int kFlagRowTiles = 2;    // a final mask pass of this many tiles per launch is labelled kInMaskFlags
+constexpr int kWalkersPerCu = 16;   // wavefronts of a walk launch per compute unit, at most
+// A walk list is cut into rounds of kBlock items (padded with empty ones) of which at most
+// kDurs are segments: a round's items and its segments' durations are fetched a round ahead,
+// into registers that the loop over the round's items only reads.  (A register written
+// inside that loop while its load is in flight is copied at every join of the loop's
+// branches, and each copy waits for the load: with the durations refilled inside the loop,
+// eight at a time, the refined pass of a 96-rank job took 7.4 instead of 4.7 ms.)
+constexpr int kBlock = 32;
+constexpr int kDurs = 8;
 constexpr int kChannels = 8;          // LDS barrier channels per block
 constexpr int kClassSlots = 8;        // LDS cost classes per block
 constexpr uint32_t kNoSlot = 15;
@@ -105,27 +137,43 @@ __host__ __device__ inline unsigned aux_expected(uint32_t x) { return x >> 9; }
 
 __host__ __device__ inline int item_kind(uint32_t m) { return int(m & 3u); }
 __host__ __device__ inline int item_stream(uint32_t m) { return int((m >> 2) & 7u); }
-__host__ __device__ inline int item_class(uint32_t m) { return int((m >> 5) & 7u); }
 __host__ __device__ inline unsigned item_regmask(uint32_t m) { return (m >> 8) & 0xffu; }
 
 // Overlap detection records, per compute op and scenario, which collective
 // types overlap it as a 4-bit mask (bit t: some comm op of type t on the same
 // rank overlaps).  The slowdown factor is the largest table entry
 // slowdown_q16[class][t] over the set bits, 65536 for an empty mask.
-// Compute op of a (rank, stream) list for overlap detection (16 bytes).
-struct ComputeRec {
-    int32_t op;
-    uint32_t meta;      // class | kChained
-    int64_t dur;        // base duration
+//
+// A segment it looks at (32 bytes), and per comm stream of the rank the comm ops that
+// may overlap it: positions [lo, hi) of the stream's list.  Those before lo finish before
+// the segment can start (one of them is a predecessor of an op of its stream up to its
+// first), those from hi on launch after its last op (some op from it on in its stream is
+// a predecessor).  Segments without any such comm op overlap nothing and have no entry.
+struct OverlapSeg {
+    int32_t rec0, n;        // its records
+    int32_t first, last;    // its first and last op
+    int32_t cand0, ncand;   // its ranges of comm ops
+    int32_t pad[2];
 };
-static_assert(sizeof(ComputeRec) == 16, "compute record must stay 16 bytes");
-// Compute op whose only predecessor is the previous compute op of its stream:
-// it starts exactly when that op finishes.
-constexpr uint32_t kChained = 0x80;
-// Overlap detection checks compute ops in blocks of kOverlapBlock (per (rank, stream)
-// list, from its start): the walk stores the finish of every block's last op, and a
-// block that ends before every comm cursor starts overlaps nothing.
-constexpr int kOverlapBlock = 8;
+static_assert(sizeof(OverlapSeg) == 32, "overlap segment must stay 32 bytes");
+struct CommRange {
+    int32_t lo, hi;         // positions in the comm lists
+    int32_t last_op;        // the comm op at hi - 1
+    int32_t pad;
+};
+static_assert(sizeof(CommRange) == 16, "comm range must stay 16 bytes");
+constexpr int kOverlapGroup = 8;    // segments a wavefront of overlap detection takes at a time
+
+// First and last op of a segment: the rows its start and finish live in.
+struct RowPair {
+    int32_t first, last;
+};
+
+// Chunk of segment records, the unit of the kernels that sum durations and write
+// timelines: whole segments, at most 64 records (one vector load).
+struct RecChunk {
+    int32_t rec0, cand0;    // first record; overlap segments before it
+};
 
 // Inputs of the CC model for a table of collectives (or of cost classes).
 struct CollTable {
@@ -171,26 +219,31 @@ struct CompactForest {
     int32_t *cbin = nullptr;                 // [class][kFxFeatures]: bins of the class's own features
     int32_t tbin[4] = {};                    // bin of each collective type
     int32_t *coll_bin = nullptr;             // [coll][2]: bins of S and of the N its cost uses
-    int32_t *cp_bin = nullptr;               // [compute record]: bin of the base duration
+    int32_t *cp_bin = nullptr;               // [segment record]: bin of the base duration
 };
 
 struct DeviceGraph {
     int64_t n_ops = 0, n_colls = 0;
     int32_t n_ranks = 0, n_walkers = 0, n_blocks = 0;
     WalkItem *items = nullptr;       // walk lists, walker-major
-    int64_t *walk_off = nullptr;     // [n_walkers + 1] offsets into items
+    int64_t *round_off = nullptr;    // [n_walkers + 1] rounds of each walker: kBlock items, kDurs rows each
+    RowPair *walk_rows = nullptr;    // first and last op of the rounds' segments
     int32_t *far = nullptr;          // far predecessor op ids
     CollTable colls;                 // every collective
     int32_t *members = nullptr;      // [n_colls] member ops present: arrivals that complete a barrier
     CollTable classes;               // every cost class
     int32_t *block_class = nullptr;  // [n_blocks][kClassSlots] class staged in each LDS slot, -1 = none
-    // overlap detection: comm / compute ops of each (rank, stream), program order
-    int64_t *cl_off = nullptr;       // [n_ranks * 8 + 1]
+    // segments: their ops, and the chunks of records
+    SegRec *recs = nullptr;
+    RecChunk *chunks = nullptr;      // [n_chunks + 1]
+    int64_t n_recs = 0, n_chunks = 0;
+    // overlap detection: the segments it looks at, and the comm ops of each (rank, stream)
+    // in program order
+    OverlapSeg *osegs = nullptr;
+    CommRange *ranges = nullptr;
+    int64_t n_osegs = 0;
     int32_t *cl = nullptr;
     uint8_t *cl_type = nullptr;      // collective type of each listed comm op
-    int64_t *cp_off = nullptr;       // [n_ranks * 8 + 1]
-    ComputeRec *cp = nullptr;
-    int32_t *cp_pos = nullptr;       // [compute record] position of the op's item in the walk lists
     unsigned *status = nullptr;      // device status word
     echo_cc_table *cc_tables = nullptr;   // CC parameter tables (echo_set_cc_tables)
     int32_t n_cc_tables = 0;
@@ -202,7 +255,7 @@ struct DeviceGraph {
     int64_t *class_metrics = nullptr;  // [8][4]
     int32_t n_trees = 0, forest_base = 65536;
     CompactForest fx;                  // the ensemble in LDS form, when it fits
-    int32_t max_comm_streams = 0;    // the most streams with comm ops on one rank
+    int32_t max_ranges = 0;          // the most comm ranges of one overlap segment
     int64_t n_slots = 0;             // member slots of the collectives met through slots
     int64_t n_counted = 0;           // collectives met by counting arrivals in device memory
     int32_t *counted_members = nullptr;   // [n_counted] their member ops present
@@ -210,19 +263,31 @@ struct DeviceGraph {
 
 constexpr int kClassMetrics = 4;
 
+// One pass over a range of scenario tiles: in the first pass the segments' jittered
+// durations are summed, then the sweep, and after the last one the ops' times.
+//
+// Where the sweep finds a segment's duration (other than the sum of its base durations,
+// in the first pass of a tile without jitter): the first pass of a tile with jitter in the
+// finish row of its last op; a refined pass as the difference of that row and the start
+// row of its first op, both left by the previous pass (overlap detection moves the finish
+// of a segment whose durations it changes).
 struct WalkArgs {
     const WalkItem *items;
-    const int64_t *walk_off;
+    const int64_t *round_off;        // [walker + 1]
+    const RowPair *rows;             // [round][kDurs] first and last op of its segments
     const int32_t *far;
     const int32_t *c_N;              // [counted coll] member ops present (arrivals that complete the barrier)
     const int32_t *block_class;
     const echo_scenario *scen;
     const int64_t *class_cost;       // [class][scen]
-    // Per-item outputs of overlap detection, one row per walk item (rows of items that are
-    // not compute ops unused), mstride columns (the tiles' scenarios, padded to whole tiles):
-    const uint8_t *tmask;            // overlap type masks, or null (pass 1)
+    const SegRec *recs;
+    const RecChunk *chunks;
+    int64_t n_chunks;
+    // Per-op outputs of overlap detection, one row per segment record of a flagged segment,
+    // mstride columns (the tiles' scenarios, padded to whole tiles):
+    const uint8_t *tmask;            // overlap type masks, or null
     const uint32_t *ext;             // extra times (prorating, ensemble factors), or null
-    const uint8_t *xflag;            // [item row][tile]: nonzero when some mask (extra time) of the row is
+    const uint8_t *xflag;            // [overlap segment][tile]: nonzero when some mask (extra time) of it is
     int64_t mstride;
     const unsigned *stable;          // non-null: skip the pass when *stable (every scenario at its fixed point)
     int64_t *start, *finish;         // [op][scen]
@@ -236,24 +301,25 @@ struct WalkArgs {
     int32_t n_scen, n_tiles;
     int32_t tile0, tiles;            // tiles handled by this launch
     int32_t n_walkers;
+    int32_t in;                      // what the pass is refined by (kIn*)
     int32_t final_pass;              // accumulate step time (and digest)
-    int32_t store_all;               // store every start and finish (else only kNeedS / kNeedF)
-    int32_t flag_rows;               // final mask pass: the variant that fetches only flagged rows (kInMaskFlags)
+    int32_t timelines;               // final pass: write every op's start and finish
 };
 
 
 struct OverlapArgs {
-    const int64_t *cl_off, *cp_off;
+    const OverlapSeg *osegs;
+    const CommRange *ranges;
+    int64_t n_osegs;
+    const SegRec *recs;
     const int32_t *cl;
     const uint8_t *cl_type;
-    const ComputeRec *cp;
     const echo_scenario *scen;
-    const int64_t *start, *finish;
-    // rows of the walk items (cp_pos), mstride columns, as the walk reads them
+    int64_t *start, *finish;         // in: the previous pass's times; out: finish of a segment's last op
+    // rows of the segment records, mstride columns
     uint8_t *tmask;                  // in: masks of the previous pass (if it was refined), out: new ones
     uint32_t *ext;                   // prorating: in/out like tmask, the extra time q16(o, F) - o
-    uint8_t *xflag;                  // out, [item row][tile]: nonzero when some mask (extra time) of the row is
-    const int32_t *cp_pos;
+    uint8_t *xflag;                  // in/out, [overlap segment][tile]: nonzero when some mask (extra time) of it is
     int64_t mstride;
     unsigned *chg;                   // non-null: [scen] set when some duration changes
     const unsigned *stable;          // non-null: skip when *stable
@@ -268,9 +334,8 @@ struct OverlapArgs {
     int32_t n_trees, forest_base;
     CompactForest fx;                // n_words > 0: the compact ensemble (LDS variant)
     int32_t prorate;                 // inflate only the overlapped part (extra times in ext)
-    int32_t n_scen, n_tiles, n_ranks;
+    int32_t n_scen, n_tiles;
     int32_t prev_refined;            // the previous pass inflated its compute ops
-    int32_t max_comm_streams;        // the most streams with comm ops on one rank (kernel variant)
     unsigned *status;
 };
 
@@ -284,9 +349,10 @@ hipError_t launch_clear(unsigned long long *arrive, int64_t n_arrive, unsigned *
 hipError_t launch_cc_cost(const CollTable &t, const echo_cc_table *tables, const echo_scenario *scen,
                           int32_t n_scen, int64_t *cost, unsigned *status, hipStream_t stream);
 hipError_t launch_walk(const WalkArgs &a, int32_t n_blocks, hipStream_t stream);
-hipError_t launch_overlap(const OverlapArgs &a, int32_t n_ranks, hipStream_t stream);
-// Bins of the compact ensemble's per-collective (S, N) and per-compute-record (base
-// duration) features.
+// max_ranges: the most comm ranges of one segment (selects the kernel variant)
+hipError_t launch_overlap(const OverlapArgs &a, int32_t max_ranges, hipStream_t stream);
+// Bins of the compact ensemble's per-collective (S, N) and per-record (base duration)
+// features.
 hipError_t launch_forest_bins(const DeviceGraph &g, int64_t n_compute, const CompactForest &fx,
                               hipStream_t stream);
 // After an overlap pass: count the refinement of every scenario whose durations changed,
@@ -295,16 +361,20 @@ hipError_t launch_settle(unsigned *chg, int32_t n_scen, int32_t *refinements, un
                          hipStream_t stream);
 // Fill n int32 with v (a kernel, so the sequence stays capturable).
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t stream);
-// Per-item input of a walk pass, the walk kernel's first template argument.
-constexpr int kInNone = 0;        // first pass: base durations only
-constexpr int kInMasks = 1;       // overlap masks, every row, fetched a round ahead into registers
-constexpr int kInMaskFlags = 2;   // overlap masks, only flagged rows, staged in LDS (final passes)
-constexpr int kInExtFlags = 3;    // prorated extra times, only flagged rows, staged in LDS
-inline int walk_input(bool refined, bool prorate, bool flag_rows) {
-    return !refined ? kInNone : prorate ? kInExtFlags : flag_rows ? kInMaskFlags : kInMasks;
+// What a pass is refined by, the walk kernel's first template argument.  The sweep itself
+// only tells the first pass from the others; the rest is a label that keeps the passes
+// apart in kernel traces: refined by masks (a final pass over many tiles, whose timelines
+// fill the memory system, under a name of its own) or by extra times.
+constexpr int kInNone = 0;        // first pass: base durations
+constexpr int kInMasks = 1;       // overlap masks
+constexpr int kInMaskFlags = 2;   // overlap masks, final pass of kFlagRowTiles tiles per launch or more
+constexpr int kInExtFlags = 3;    // prorated or ensemble extra times
+inline int walk_input(bool refined, bool ext, bool many_tiles) {
+    return !refined ? kInNone : ext ? kInExtFlags : many_tiles ? kInMaskFlags : kInMasks;
 }
 // Co-resident walk workgroups (kBlockWalkers wavefronts each) the device can hold,
-// for each kernel variant (bits 0-1 input, bit 2 final, bit 3 digest).
+// for each kernel variant (bits 0-1 input, bit 2 final, bit 3 digest); at most
+// kWalkersPerCu / kBlockWalkers per compute unit.
 constexpr int kWalkVariants = 16;
 hipError_t walk_capacity(int device, int64_t workgroups[kWalkVariants]);
 inline int walk_variant(int in, bool final_pass, bool digest) {

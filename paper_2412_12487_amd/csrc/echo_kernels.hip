@@ -3,16 +3,22 @@
 //   k_init     clear barrier state and outputs, check scenario ranges
 //   k_clear    clear barrier state between passes
 //   k_cc_cost  CC estimator (Sec. 5.3, Eq. 2-5): one lane per (collective, scenario)
+//   k_sum      what-if durations: per segment and scenario, the sum of its ops' jittered
+//              base durations (first pass)
 //   k_walk     timeline composer (Sec. 4.2) with the collective synchronisation
 //              rule (Sec. 5.2): one wavefront per (walker, 64-scenario tile) walks
-//              the ops of its ranks in level order, max-plus relaxation in registers
+//              the segments and comm ops of its ranks in level order, max-plus
+//              relaxation in registers
 //   k_overlap  validator input (Sec. 6): per compute op and scenario, the mask of
-//              collective types among the comm ops of its rank that overlap it
+//              collective types among the comm ops of its rank that overlap it, and the
+//              segments' new durations
+//   k_expand   the ops' starts and finishes (and their digest) from the segments' starts
 //
 // Everything is int64 nanoseconds and Q16 factors, bit-exact by construction:
 // max, add, 64-bit multiply and shifts only (no floating point on the path).
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "echo_internal.h"
 
@@ -266,21 +272,22 @@ __device__ bool wait_arrivals(const unsigned *cnt, unsigned need, unsigned *stat
 }
 
 // Barrier of a collective met through member slots: the latest launch time over
-// its n members' slots p[m * ns] (m < n <= kSlotMembers), once every member of every
+// its n members' slots p[m * ns] (m < n <= MOST), once every member of every
 // lane's scenario has stored its launch (a slot reads -1 until then).  All slots are
 // read in one memory round trip per poll.  Bounded like wait_arrivals; on giving up
 // it returns 0 and clears *ok.
+template <int MOST>
 __device__ int64_t wait_slots(const int64_t *p, unsigned n, int64_t ns, unsigned *status, int64_t limit, bool *ok) {
     WaitClock clk;
     for (unsigned poll = 0;; ++poll) {
-        int64_t v[kSlotMembers];
+        int64_t v[MOST];
 #pragma unroll
-        for (int m = 0; m < kSlotMembers; ++m)
+        for (int m = 0; m < MOST; ++m)
             v[m] = m < (int)n ? __hip_atomic_load(p + m * ns, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
         int64_t mx = 0;
         bool all = true;
 #pragma unroll
-        for (int m = 0; m < kSlotMembers; ++m) {
+        for (int m = 0; m < MOST; ++m) {
             all = all && v[m] >= 0;
             mx = v[m] > mx ? v[m] : mx;
         }
@@ -303,33 +310,19 @@ __device__ int64_t wait_slots(const int64_t *p, unsigned n, int64_t ns, unsigned
 // (a far predecessor) or by the next kernel.
 __device__ __forceinline__ void put(int64_t *p, int64_t v) { __builtin_nontemporal_store(v, p); }
 
-// Duration d inflated by the slowdown factor of overlap mask m (Sec. 6): the
-// largest entry of the op's class row over the collective types in m; an empty
-// mask is factor 65536, which q16 maps to d itself.  tbl: the lane's table in
-// LDS, entry e at tbl[e * 64 + lane].
-__device__ __forceinline__ int64_t inflate(int64_t d, uint32_t m, const uint32_t *tbl, int cls, int lane) {
-    if (m == 0) return d;
-    uint32_t F = 65536u;
-#pragma unroll
-    for (int t = 0; t < kTypes; ++t)
-        if ((m >> t) & 1u) {
-            const uint32_t x = tbl[(cls * kTypes + t) * kLanes + lane];
-            F = x > F ? x : F;
-        }
-    return q16(d, F);
-}
-// The same for a mask whose class row (entries t = 0..3 of the op's class) was read
-// ahead: no branch, an empty mask keeps F = 65536.  Entry t takes part through an AND
-// with bit t of m widened to a whole word (all ones or zero), and the largest is taken
-// three at a time.
-__device__ __forceinline__ int64_t inflate_row(int64_t d, uint32_t m, const uint32_t x[kTypes]) {
+// Duration d inflated by the slowdown factor of overlap mask m (Sec. 6): the largest entry
+// of the op's class row x over the collective types in m; an empty mask keeps factor 65536,
+// which q16 maps to d itself.  Entry t takes part through an AND with bit t of m widened to
+// a whole word (all ones or zero), and the largest is taken three at a time.
+__device__ __forceinline__ int64_t inflate_row(int64_t d, uint32_t m, uint4 x) {
     static_assert(kTypes == 4, "two three-way maxima cover 65536 and four entries");
-    uint32_t a[kTypes];
-#pragma unroll
-    for (int t = 0; t < kTypes; ++t) a[t] = x[t] & (uint32_t)__builtin_amdgcn_sbfe((int)m, t, 1);
-    const uint32_t F0 = a[0] > 65536u ? a[0] : 65536u;
-    const uint32_t F1 = F0 > a[1] ? F0 : a[1];
-    const uint32_t F2 = a[2] > a[3] ? a[2] : a[3];
+    const uint32_t a0 = x.x & (uint32_t)__builtin_amdgcn_sbfe((int)m, 0, 1);
+    const uint32_t a1 = x.y & (uint32_t)__builtin_amdgcn_sbfe((int)m, 1, 1);
+    const uint32_t a2 = x.z & (uint32_t)__builtin_amdgcn_sbfe((int)m, 2, 1);
+    const uint32_t a3 = x.w & (uint32_t)__builtin_amdgcn_sbfe((int)m, 3, 1);
+    const uint32_t F0 = a0 > 65536u ? a0 : 65536u;
+    const uint32_t F1 = F0 > a1 ? F0 : a1;
+    const uint32_t F2 = a2 > a3 ? a2 : a3;
     return q16(d, F1 > F2 ? F1 : F2);
 }
 // s_waitcnt immediate for "lgkmcnt(0)" on gfx9-family targets (vmcnt and expcnt left at their maxima)
@@ -354,43 +347,56 @@ __device__ bool wait_local(const unsigned *cnt, unsigned need, unsigned *status,
     }
 }
 
+// The scenario knobs a lane needs to draw durations, and what it reads and writes: lane l of a
+// tile's wavefront is scenario tile * 64 + l.  Idle lanes of the last tile mirror its last
+// scenario: they compute the same values and store them to the same places; only active
+// lanes issue global atomics.
+struct Lane {
+    int32_t col, sigma;      // column within the tile, scenario
+    bool active;
+    bool any_jitter;         // some lane draws jitter (a lane without draws the identity factor:
+                             // amplitude 0 gives f = 65536 and q16(d, 65536) = d)
+    Jitter jt;
+};
+__device__ __forceinline__ Lane make_lane(const echo_scenario *scen, int32_t n_scen, int32_t tile, int lane) {
+    Lane x;
+    x.active = tile * kLanes + lane < n_scen;
+    x.col = x.active ? lane : n_scen - 1 - tile * kLanes;
+    x.sigma = tile * kLanes + x.col;
+    const echo_scenario *sc = scen + x.sigma;
+    const int32_t amp = sc->jitter_amp_q16;
+    x.jt = make_jitter(sc->jitter_seed, sc->jitter_stream, amp);
+    x.any_jitter = __builtin_amdgcn_readfirstlane(__ballot(amp != 0) != 0);
+    return x;
+}
+
 // A workgroup of kBlockWalkers wavefronts walks the walkers of one block for
-// one 64-scenario tile; wavefront w walks walker block * kBlockWalkers + w.  REFINED:
-// the pass inflates compute ops by the factors of the previous pass's
-// overlaps.  FINAL: the pass produces the step time (and DIGEST: the digest).
-// IN (kIn*): the pass's per-item input -- none (the first pass), overlap masks (REFINED)
-// or prorated extra times (PRORATE), and whether only flagged rows are fetched.
-// Every variant must fit two workgroups per CU (at most 128 registers): the loader sizes
-// walkers to the fewest co-resident workgroups of any variant, so one variant over the
-// limit would make the largest graphs walk more ranks per wavefront in every pass.
+// one 64-scenario tile; wavefront w walks walker block * kBlockWalkers + w.  IN (kIn*):
+// what the pass is refined by.  FINAL: the pass produces the step time (and DIGEST: the comm ops'
+// share of the digest).
+//
+// What bounds it: latency.  The sweep is one chain of segments and barriers per
+// scenario tile (on the 1024-rank workload 1.5 thousand segments and 2.7 thousand
+// barriers long), and a wavefront runs its items one after the other.  So an item costs its
+// instructions, and everything an item could wait for is fetched well before: items a round
+// (32) ahead, segment durations a group (kDurs) ahead, both settled by one wait each.
 template <int IN, bool FINAL, bool DIGEST>
 __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per_eu(4))) void k_walk(WalkArgs a) {
     constexpr bool REFINED = IN != kInNone;
-    constexpr bool PRORATE = IN == kInExtFlags;
-    constexpr bool kFlagged = IN == kInMaskFlags || IN == kInExtFlags;
-    // staged per item and lane: overlap masks (one byte) or, prorating, extra times (32 bits)
-    __shared__ __align__(16) uint32_t fstage[REFINED ? kBlockWalkers * kBlock * kLanes / (PRORATE ? 1 : 4) : 1];
     __shared__ unsigned long long lbar[kChannels][2][kLanes];   // per channel and slot: latest launch per lane
     __shared__ unsigned lcnt[kChannels][2];                      // per channel and slot: members arrived
     __shared__ int64_t ccost[kClassSlots][kLanes];               // staged class costs of this tile
-    // slots 1..7 of every wave (slot 0 stays in a register); the prorating refined
-    // pass has no LDS left for them and keeps them in registers
-    constexpr bool kLdsSlots = !(REFINED && PRORATE);
-    __shared__ int64_t slotmem[kLdsSlots ? kBlockWalkers * kStreams * kLanes : 1];
-    __shared__ uint32_t slow[REFINED && !PRORATE ? kClasses * kTypes * kLanes : 1];   // lanes' slowdown tables
-    static_assert(kBlockWalkers * 4 == kClasses * kTypes, "one 16-byte table slice per wavefront");
+    __shared__ int64_t slotmem[kBlockWalkers * kStreams * kLanes];   // slots 1..7 of every wave (slot 0 stays in a register)
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform within a wavefront
     const int32_t blk = blockIdx.x / a.tiles;
     const int32_t tile = a.tile0 + blockIdx.x % a.tiles;
     const int32_t w = blk * kBlockWalkers + wave;
-    const bool active = tile * kLanes + lane < a.n_scen;
-    // Idle lanes of the last tile mirror its last scenario: they compute the same
-    // values and store them to the same places; only active lanes issue global atomics.
-    const int32_t col = active ? lane : a.n_scen - 1 - tile * kLanes;
+    const Lane ln = make_lane(a.scen, a.n_scen, tile, lane);
+    const int32_t col = ln.col, sigma = ln.sigma;
+    const bool active = ln.active;
     const bool mirror = (tile + 1) * kLanes > a.n_scen;
-    const int32_t sigma = tile * kLanes + col;
     const int64_t ns = a.n_scen;
 
     // block set-up: clear the barrier channels, stage the block's class costs
@@ -400,14 +406,6 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
         const int32_t cls = a.block_class[(int64_t)blk * kClassSlots + wave];
         ccost[wave][lane] = cls >= 0 ? a.class_cost[(int64_t)cls * ns + sigma] : 0;
     }
-    if (REFINED && !PRORATE) {
-        // entry e of the table for lane l at slow[e * 64 + l]: lanes hit distinct banks
-        const uint4 t4 = reinterpret_cast<const uint4 *>(&a.scen[sigma].slowdown_q16[0][0])[wave];
-        slow[(4 * wave + 0) * kLanes + lane] = t4.x;
-        slow[(4 * wave + 1) * kLanes + lane] = t4.y;
-        slow[(4 * wave + 2) * kLanes + lane] = t4.z;
-        slow[(4 * wave + 3) * kLanes + lane] = t4.w;
-    }
     __syncthreads();
     if (w >= a.n_walkers) return;
     // every scenario reached its fixed point in an earlier pass: nothing left to refine
@@ -415,40 +413,19 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
                                                                       __HIP_MEMORY_SCOPE_AGENT)))
         return;
 
-    const echo_scenario *sc = a.scen + sigma;
-    const int32_t amp = sc->jitter_amp_q16;
-    const Jitter jt = make_jitter(sc->jitter_seed, sc->jitter_stream, amp);
-    // one branch for the whole wavefront: a lane without jitter draws the identity factor
-    // (amplitude 0 gives f = 65536 and q16(d, 65536) = d)
-    const bool any_jitter = __builtin_amdgcn_readfirstlane(__ballot(amp != 0) != 0);
     int64_t *const sbase = a.start + (int64_t)tile * kLanes;    // row v of tile: sbase + v * ns
     int64_t *const fbase = a.finish + (int64_t)tile * kLanes;
     const unsigned *tile_count = a.count + tile;
-    uint8_t *const fst = reinterpret_cast<uint8_t *>(fstage) + (REFINED && !PRORATE ? wave * kBlock * kLanes : 0);
-    uint32_t *const fst32 = fstage + (REFINED && PRORATE ? wave * kBlock * kLanes : 0);
+    // every pass but a last one without timelines or digest stores the segments' and comm
+    // ops' times: overlap detection, the next pass's durations and k_expand read them
+    const bool keep = !FINAL || DIGEST || a.timelines;
 
     // Per slot: finish of the latest op (of a comm op: once its resolve item ran;
     // no item reads the slot in between).
-    // (entry kStreams: where ops without a slot put their finish; never read as a slot)
     int64_t lf0 = 0;
-    int64_t lf[kLdsSlots ? 1 : kStreams + 1];
-    int64_t *const smem = slotmem + (kLdsSlots ? wave * kStreams * kLanes + lane : 0);
-    if (kLdsSlots) {
+    int64_t *const smem = slotmem + wave * kStreams * kLanes + lane;
 #pragma unroll
-        for (int j = 1; j < kStreams; ++j) smem[j * kLanes] = 0;
-    } else {
-#pragma unroll
-        for (int j = 0; j <= kStreams; ++j) lf[j] = 0;
-    }
-    // slot q (q >= 1, wave-uniform); q == kStreams: the entry of ops without a slot
-    auto slot_get = [&](int q) -> int64_t { return kLdsSlots ? smem[q * kLanes] : lf[q]; };
-    auto slot_set = [&](int q, int64_t f) {
-        if (kLdsSlots) {
-            if (q < kStreams) smem[q * kLanes] = f;
-        } else {
-            lf[q] = f;
-        }
-    };
+    for (int j = 1; j < kStreams; ++j) smem[j * kLanes] = 0;
     // A wait that gave up (timeout or abort) marks the wave dead: it finishes its
     // list without waiting again; the times it writes are meaningless and the
     // status word already reports the failure.
@@ -457,293 +434,155 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
     uint64_t dig = 0;
     uint32_t hi_or = 0;          // OR of the high words of every time: bit 30 set <=> some time >= 2^62
     unsigned err = 0;
-    const int64_t beg = a.walk_off[w], end = a.walk_off[w + 1];
-    const uint32_t keep = a.store_all ? (kNeedS | kNeedF) : 0u;    // stores beyond each item's own needs
+    const int64_t beg = a.round_off[w], end = a.round_off[w + 1];
     // lane j < 32 holds the first half of item j of the round, lane 32 + j its second half
-    const int4 *items4 = reinterpret_cast<const int4 *>(a.items);
-    const int half = lane >> 5, slotl = lane & 31;
-    // lanes past the end of the list hold op 0
-    int4 nxt = beg + slotl < end ? items4[2 * (beg + slotl) + half] : make_int4(0, 0, 0, 0);
-
-// Finish f_ of comm op v_ (collective c_, aux word x_): its barrier -- the
-// latest member launch -- plus the collective's cost; written to the finish array.
-#define MEET(c_, v_, x_, k_, f_, s_base_)                                                        \
-    {                                                                                            \
-        uint64_t b_ = 0;                                                                         \
-        if ((x_) & kAuxLocal) {                                                                  \
-            const int ch_ = aux_channel(x_), par_ = aux_parity(x_);                              \
-            if (!dead && !__builtin_amdgcn_readfirstlane(                                        \
-                             wait_local(&lcnt[ch_][par_], aux_expected(x_), a.status, a.spin_limit))) \
-                dead = true;                                                                     \
-            b_ = lbar[ch_][par_][lane];                                                          \
-        } else if ((x_) & kAuxSlots) {                                                           \
-            bool ok_ = true;                                                                     \
-            if (!dead)                                                                           \
-                b_ = (uint64_t)wait_slots(a.slots + (int64_t)(s_base_) * ns + sigma, aux_expected(x_), ns, \
-                                          a.status, a.spin_limit, &ok_);                         \
-            __builtin_amdgcn_s_waitcnt(kWaitVm0);    /* settled on this path, not at the join */ \
-            if (!__builtin_amdgcn_readfirstlane(ok_)) dead = true;                               \
-        } else {                                                                                 \
-            if (!dead && !__builtin_amdgcn_readfirstlane(wait_arrivals(tile_count + (int64_t)(c_) * a.n_tiles, \
-                                                                       (unsigned)a.c_N[c_], a.status, \
-                                                                       a.spin_limit)))           \
-                dead = true;                                                                     \
-            if (active)                                                                          \
-                b_ = __hip_atomic_fetch_max(a.arrive + (int64_t)(c_) * ns + sigma, 0ull,         \
-                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);         \
-            __builtin_amdgcn_s_waitcnt(kWaitVm0);    /* settled on this path, not at the join */ \
-            b_ = mirror ? (uint64_t)__shfl((long long)b_, col) : b_;                             \
-        }                                                                                        \
-        const int sl_ = aux_slot(x_);                                                            \
-        /* The cost: from the workgroup's LDS slot, read first on every path; a class without  \
-           a slot then reads device memory and waits for that load inside its own branch, so   \
-           the common path carries no wait on vector memory (which on this target would also  \
-           wait for every timeline store still in flight).  Distinct load kinds keep the two  \
-           reads from merging into one flat load. */                                            \
-        int64_t t_ = ccost[sl_ & (kClassSlots - 1)][lane];                                       \
-        if (sl_ >= kClassSlots) {                                                                \
-            t_ = __hip_atomic_load(a.class_cost + (int64_t)(k_) * ns + sigma, __ATOMIC_RELAXED,  \
-                                   __HIP_MEMORY_SCOPE_AGENT);                                    \
-            __builtin_amdgcn_s_waitcnt(kWaitVm0);                                                \
-        }                                                                                        \
-        f_ = (int64_t)b_ + t_;                                                                   \
-        hi_or |= (uint32_t)((uint64_t)(f_) >> 32);                                               \
-        put(fbase + (int64_t)(v_) * ns + col, f_);                                               \
-        if (DIGEST) {                                                                            \
-            const int64_t s_ = (sbase + (int64_t)(v_) * ns)[col];                                \
-            dig += mix64(mix64((uint64_t)(v_) ^ (uint64_t)s_) ^ (uint64_t)(f_));                 \
-        }                                                                                        \
-    }
-
-    // The refined passes' per-item inputs (overlap masks, one byte per scenario, or extra
-    // times, four bytes), one row per walk item with this tile's 64 columns, staged in LDS
-    // in [item][lane] order: half a round of rows at a time, loaded straight from memory into
-    // LDS (no registers), one half ahead of its use -- the first half of a round during the
-    // previous round's second half, the second half during its own first half -- so that
-    // the wait for a half finds it arrived long ago.  (The arrays have a round of rows past
-    // the last item.)  Only rows that overlap detection flagged as holding a nonzero value
-    // are fetched (an unflagged compute item is not inflated): `want` has bit q set for
-    // item q of the round.
-    // Where the pass is bound by HBM -- a final pass over many scenario tiles, whose timeline
-    // stores fill the memory system -- the bytes of every row count; the masks of a pass bound
-    // by its chain of items (not the final one, or few tiles) are instead fetched whole, a
-    // round ahead in registers (lane l: 16 bytes, row l / 4, +16 in the second half, quarter
-    // l % 4), because there a second wait in the middle of a round costs more than the bytes.
-    // Extra times are always fetched by flag.
-    const uint4 *const mrow4 = reinterpret_cast<const uint4 *>(a.tmask + (int64_t)tile * kLanes) + (lane & 3);
-    const int64_t mst4 = a.mstride / 16;
-    uint4 mnx0 = make_uint4(0, 0, 0, 0), mnx1 = mnx0;
-    if (REFINED && !kFlagged) {
-        mnx0 = mrow4[(beg + (lane >> 2)) * mst4];
-        mnx1 = mrow4[(beg + 16 + (lane >> 2)) * mst4];
-    }
-    constexpr int kHalf = kBlock / 2;
-    const uint32_t *const erow = a.ext + (int64_t)tile * kLanes + col;
-    const uint32_t *const mrow = reinterpret_cast<const uint32_t *>(a.tmask + (int64_t)tile * kLanes) + lane;
-    auto stage_rows = [&](int64_t row0, int h, uint32_t want) {
-        for (uint32_t m = (want >> h) & ((1u << kHalf) - 1); m; m &= m - 1) {
-            const int q = __builtin_ctz(m);
-            if (PRORATE) {
-                __builtin_amdgcn_global_load_lds(erow + (row0 + q) * a.mstride,
-                                                 fstage + (wave * kBlock + h + q) * kLanes, 4, 0, 0);
-            } else if (lane < kLanes / 4) {
-                // a mask row is 64 bytes: sixteen lanes load four each
-                __builtin_amdgcn_global_load_lds(mrow + (row0 + q) * (a.mstride / 4),
-                                                 fstage + (wave * kBlock + h + q) * (kLanes / 4), 4, 0, 0);
-            }
-        }
+    const int4 *items4 = reinterpret_cast<const int4 *>(a.items) + 2 * (lane & 31) + (lane >> 5);
+    auto load_items = [&](int64_t r) -> int4 {
+        return r < end ? items4[2 * kBlock * r] : make_int4(0, (int)kEmpty, 0, 0);
     };
-    // a round's flags of its compute items: lane q < 32 holds item q's flag byte
-    auto round_flags = [&](uint32_t fl, int4 items, int n) -> uint32_t {
-        return (uint32_t)__ballot(lane < n && lane < 32 && fl != 0 && item_kind((uint32_t)items.y) == ECHO_COMPUTE);
+    // Segment durations (see WalkArgs): lane q < kDurs holds the rows of the round's segment q
+    // (unused ones name op 0), fetched a round before the durations they name.
+    const bool load_d = REFINED || ln.any_jitter;
+    auto load_rows = [&](int64_t r) -> int2 {
+        return load_d && r < end ? reinterpret_cast<const int2 *>(a.rows)[r * kDurs + (lane & (kDurs - 1))]
+                                 : make_int2(0, 0);
     };
-    auto load_flags = [&](int64_t row0) -> uint32_t {
-        return lane < 32 && row0 + lane < end ? (uint32_t)a.xflag[(row0 + lane) * a.n_tiles + tile] : 0u;
-    };
-    uint32_t fl_now = 0, fl_next = 0;     // this round's and the next round's flag bytes
-    uint32_t want = 0;                    // this round's flagged compute items
-    // A compute item's staged mask (wave-uniform test: a compute op whose row was staged) is
-    // read before its jitter draw, so that the LDS latency hides behind the draw, and for a
-    // flagged row (some nonzero mask) the class row of the lane's slowdown table with it.  An
-    // extra time is read after the draw: held across it, it took the prorating variants past
-    // 128 registers, and the fewer co-resident workgroups made the largest graphs walk more
-    // ranks per wavefront.
-    uint32_t sm = 0, srow[kTypes] = {};
-    auto staged = [&](uint32_t meta, int j) -> bool {
-        return REFINED && item_kind(meta) == ECHO_COMPUTE && ((want >> j) & 1u);
-    };
-    auto read_staged = [&](int j, uint32_t meta) {
-        if (PRORATE) return;
-        sm = fst[j * kLanes + col];
-        if (IN == kInMaskFlags) {
+    typedef int64_t Durs __attribute__((ext_vector_type(kDurs)));
+    int64_t in_f[kDurs] = {}, in_s[kDurs] = {};
+    auto load_durs = [&](int2 rows) {
+        if (!load_d) return;
 #pragma unroll
-            for (int t = 0; t < kTypes; ++t) srow[t] = slow[(item_class(meta) * kTypes + t) * kLanes + lane];
+        for (int q = 0; q < kDurs; ++q) {
+            const int64_t l = __builtin_amdgcn_readlane(rows.y, q);
+            in_f[q] = (fbase + l * ns)[col];
+            if (REFINED) {
+                const int64_t f = __builtin_amdgcn_readlane(rows.x, q);
+                in_s[q] = (sbase + f * ns)[col];
+            }
         }
     };
-    auto apply_staged = [&](int64_t d, uint32_t meta, int j) -> int64_t {
-        if (PRORATE) return d + fst32[j * kLanes + lane];
-        if (IN == kInMaskFlags) return inflate_row(d, sm, srow);
-        return inflate(d, sm, slow, item_class(meta), lane);
-    };
-    if (kFlagged && beg < end) {
-        fl_now = load_flags(beg);
-        __builtin_amdgcn_s_waitcnt(kWaitVm0);
-        const int n0 = end - beg < kBlock ? int(end - beg) : kBlock;
-        stage_rows(beg, 0, round_flags(fl_now, nxt, n0));
-    }
-    for (int64_t blk0 = beg; blk0 < end; blk0 += kBlock) {
+    int4 nxt = load_items(beg);
+    int2 rows = load_rows(beg);
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    load_durs(rows);
+    rows = load_rows(beg + 1);
+
+    for (int64_t r = beg; r < end; ++r) {
+        // Everything fetched for this round is settled here, once; then the next round's items
+        // and durations are fetched, and the rows of the one after.
         const int4 cur = nxt;
-        const int nb = end - blk0 < kBlock ? int(end - blk0) : kBlock;
-        // This round's items and its first half of staged rows (fetched during the last
-        // round) are settled first: a wait at their first use would also wait for the
-        // fetches issued below.
         __builtin_amdgcn_s_waitcnt(kWaitVm0);
-        if (REFINED && !kFlagged) {
-            uint4 *const f4 = reinterpret_cast<uint4 *>(fst);
-            f4[lane] = mnx0;
-            f4[kLanes + lane] = mnx1;
-        }
-        // the round's second half of rows is fetched now, into rows the last round's second
-        // half has finished with, and the next round's flags with it
-        if (kFlagged) {
-            want = round_flags(fl_now, cur, nb);
-            if (nb > kHalf) stage_rows(blk0 + kHalf, kHalf, want);
-            fl_next = load_flags(blk0 + kBlock);
-        }
-        nxt = blk0 + kBlock + slotl < end ? items4[2 * (blk0 + kBlock + slotl) + half] : make_int4(0, 0, 0, 0);
-        if (REFINED && !kFlagged && blk0 + kBlock < end) {
-            mnx0 = mrow4[(blk0 + kBlock + (lane >> 2)) * mst4];
-            mnx1 = mrow4[(blk0 + kBlock + 16 + (lane >> 2)) * mst4];
-        }
-        if (REFINED && !kFlagged) want = ~0u;     // every row staged
-        // fast flags of the round, one bit per item
-        const uint64_t fast_bits = __builtin_amdgcn_read_exec() &
-                                   __ballot((lane < nb) && (lane < 32) && (cur.y & kFast));
-        // What a fast item needs besides its op and duration, as bits of the round taken
-        // once, so that its loop reads two lanes per item instead of four: the items that
-        // store a start or finish of their own (passes that do not store every one), the
-        // compute items with a staged row, and whether every duration of the round fits
-        // 32 bits (lane 32 + j holds the high word of item j's).
-        const uint32_t need_bits = (uint32_t)(__builtin_amdgcn_read_exec() &
-                                              __ballot(lane < 32 && ((uint32_t)cur.y & (kNeedS | kNeedF))));
-        const uint32_t stg_bits =
-            !REFINED ? 0u
-            : kFlagged ? want
-                       : (uint32_t)(__builtin_amdgcn_read_exec() &
-                                    __ballot(lane < 32 && item_kind((uint32_t)cur.y) == ECHO_COMPUTE));
-        const bool small_round =
-            __builtin_amdgcn_readfirstlane((__builtin_amdgcn_read_exec() & __ballot(lane >= 32 && cur.y != 0)) == 0);
-        int j = 0;
-        bool second_half = false;     // the round's second half of staged rows settled
-        while (j < nb) {
-            if (kFlagged && j == kHalf && !second_half) {
-                // the second half was fetched at the round's start; the next round's first
-                // half goes into the rows the first half has finished with
-                __builtin_amdgcn_s_waitcnt(kWaitVm0);
-                if (blk0 + kBlock < end) {
-                    const int nn = end - blk0 - kBlock < kBlock ? int(end - blk0 - kBlock) : kBlock;
-                    // The next round's flags and items arrived with the wait above.  The empty asm
-                    // keeps their use here: left free, the compiler computes the per-lane test
-                    // where they are fetched, at the round's start, and waits for them there.
-                    uint32_t fl = fl_next;
-                    int4 it = nxt;
-                    asm volatile("" : "+v"(fl), "+v"(it.y));
-                    stage_rows(blk0 + kBlock, 0, round_flags(fl, it, nn));
-                }
-                second_half = true;
-            }
-            // a run of fast items: compute/memcpy ops right after the previous op of slot 0
-            // (fast bits exist only below nb, so the run ends there at the latest; with extra
-            // times it also stops where the second half begins)
-            int run_end = j + (int)__builtin_ctzll(~(fast_bits >> j));
-            if (kFlagged && j < kHalf && run_end > kHalf) run_end = kHalf;
-            int64_t s0 = lf0;
-// ALL: the pass stores every start and finish, so the items' own needs are not consulted;
-// JIT: some lane draws jitter (the branch stays out of the loop); SMALL: every duration
-// of the round is below 2^32 ns.  The item's metadata word, and without jitter its op, are
-// read only where they are used (a staged row's class, an item's own stores).
-#define FAST_RUN(ALL, JIT, SMALL)                                                                \
-            for (; j < run_end; ++j) {                                                           \
-                const int32_t op = ((JIT) || (ALL) || DIGEST) ? __builtin_amdgcn_readlane(cur.x, j) : 0; \
-                const uint32_t dlo = (uint32_t)__builtin_amdgcn_readlane(cur.x, j + 32);         \
-                const int64_t dur = (SMALL) ? (int64_t)dlo                                       \
-                    : (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(cur.y, j + 32) << 32) | dlo); \
-                const bool stg = REFINED && ((stg_bits >> j) & 1u);                              \
-                uint32_t meta = 0;                                                               \
-                if (stg) {                                                                       \
-                    if (!PRORATE) meta = (uint32_t)__builtin_amdgcn_readlane(cur.y, j);          \
-                    read_staged(j, meta);                                                        \
-                }                                                                                \
-                int64_t d = !(JIT) ? dur : (SMALL) ? jittered32(dlo, op, jt) : jittered(dur, op, jt); \
-                if (stg) d = apply_staged(d, meta, j);                                           \
-                const int64_t f = s0 + d;                                                        \
-                if (ALL) {                                                                       \
-                    put(sbase + (int64_t)op * ns + col, s0);                                     \
-                    put(fbase + (int64_t)op * ns + col, f);                                      \
-                } else if ((need_bits >> j) & 1u) {                                              \
-                    const int32_t sop = ((JIT) || DIGEST) ? op : __builtin_amdgcn_readlane(cur.x, j); \
-                    const uint32_t nm = (uint32_t)__builtin_amdgcn_readlane(cur.y, j);           \
-                    if (nm & kNeedS) put(sbase + (int64_t)sop * ns + col, s0);                   \
-                    if (nm & kNeedF) put(fbase + (int64_t)sop * ns + col, f);                    \
-                }                                                                                \
-                if (DIGEST) dig += mix64(mix64((uint64_t)op ^ (uint64_t)s0) ^ (uint64_t)f);     \
-                s0 = f;                                                                          \
-            }
-            if (keep) {
-                // (stores every start and finish: the high word's read is not worth a variant)
-                if (!any_jitter) FAST_RUN(true, false, false)
-                else if (small_round) FAST_RUN(true, true, true)
-                else FAST_RUN(true, true, false)
-            } else {
-                if (small_round) {
-                    if (any_jitter) FAST_RUN(false, true, true) else FAST_RUN(false, false, true)
-                } else {
-                    if (any_jitter) FAST_RUN(false, true, false) else FAST_RUN(false, false, false)
-                }
-            }
-#undef FAST_RUN
-            // durations are never negative: the run's last finish is its latest time
-            hi_or |= (uint32_t)((uint64_t)s0 >> 32);
-            lf0 = s0;
-            if (j >= nb) break;
-            if (kFlagged && j == kHalf && !second_half) continue;   // settle it first
+        Durs dur;
+#pragma unroll
+        for (int q = 0; q < kDurs; ++q) dur[q] = REFINED ? in_f[q] - in_s[q] : in_f[q];
+        nxt = load_items(r + 1);
+        load_durs(rows);
+        rows = load_rows(r + 2);
+        const int nb = __builtin_popcountll(__builtin_amdgcn_read_exec() &
+                                            __ballot(lane < kBlock && !((uint32_t)cur.y & kEmpty)));
+        // the round's segments (the durations' index is a count of bits: kept in scalar registers)
+        const uint32_t seg_bits = (uint32_t)(__builtin_amdgcn_read_exec() &
+                                             __ballot(lane < kBlock && ((uint32_t)cur.y & (kEmpty | 1u)) == 0));
+        for (int j = 0; j < nb; ++j) {
             const int32_t op = __builtin_amdgcn_readlane(cur.x, j);
             const uint32_t meta = (uint32_t)__builtin_amdgcn_readlane(cur.y, j);
-            const int64_t dur = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(cur.y, j + 32) << 32) |
-                                          (uint32_t)__builtin_amdgcn_readlane(cur.x, j + 32));
+            const int32_t coll = __builtin_amdgcn_readlane(cur.w, j);       // a segment's last op
             const int kind = item_kind(meta);
-            const int32_t far_off = __builtin_amdgcn_readlane(cur.z, j);
-            const int32_t coll = __builtin_amdgcn_readlane(cur.w, j);
-            const int32_t nfar = __builtin_amdgcn_readlane(cur.z, j + 32);
-            const uint32_t aux = (uint32_t)__builtin_amdgcn_readlane(cur.w, j + 32);
-            const int st = item_stream(meta);
+            const int sq = (meta & kNoReg) ? kStreams : item_stream(meta);  // kStreams: no slot
+            const bool storef = keep || (meta & kNeedF);
             if (kind == kResolve) {
-                // a comm op's barrier, due right before its first successor
-                int64_t f;
-                MEET(coll, op, aux, (int32_t)dur, f, far_off)
+                // a comm op's barrier, due right before its first successor: its finish is the
+                // latest member launch plus the collective's cost
+                const uint32_t aux = (uint32_t)__builtin_amdgcn_readlane(cur.w, j + 32);
+                uint64_t b = 0;
+                if (aux & kAuxLocal) {
+                    const int ch = aux_channel(aux), par = aux_parity(aux);
+                    if (!dead && !__builtin_amdgcn_readfirstlane(
+                                     wait_local(&lcnt[ch][par], aux_expected(aux), a.status, a.spin_limit)))
+                        dead = true;
+                    b = lbar[ch][par][lane];
+                } else if (aux & kAuxSlots) {
+                    bool ok = true;
+                    if (!dead) {
+                        const int64_t *p = a.slots + (int64_t)__builtin_amdgcn_readlane(cur.z, j) * ns + sigma;
+                        const unsigned n = aux_expected(aux);
+                        b = n <= 2 ? (uint64_t)wait_slots<2>(p, n, ns, a.status, a.spin_limit, &ok)
+                                   : (uint64_t)wait_slots<kSlotMembers>(p, n, ns, a.status, a.spin_limit, &ok);
+                    }
+                    __builtin_amdgcn_s_waitcnt(kWaitVm0);    // settled on this path, not at the join
+                    if (!__builtin_amdgcn_readfirstlane(ok)) dead = true;
+                } else {
+                    if (!dead && !__builtin_amdgcn_readfirstlane(wait_arrivals(tile_count + (int64_t)coll * a.n_tiles,
+                                                                               (unsigned)a.c_N[coll], a.status,
+                                                                               a.spin_limit)))
+                        dead = true;
+                    if (active)
+                        b = __hip_atomic_fetch_max(a.arrive + (int64_t)coll * ns + sigma, 0ull, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+                    __builtin_amdgcn_s_waitcnt(kWaitVm0);    // settled on this path, not at the join
+                    b = mirror ? (uint64_t)__shfl((long long)b, col) : b;
+                }
+                const int sl = aux_slot(aux);
+                // The cost: from the workgroup's LDS slot, read first on every path; a class without
+                // a slot then reads device memory and waits for that load inside its own branch, so
+                // the common path carries no wait on vector memory (which on this target would also
+                // wait for every timeline store still in flight).  Distinct load kinds keep the two
+                // reads from merging into one flat load.
+                int64_t t = ccost[sl & (kClassSlots - 1)][lane];
+                if (sl >= kClassSlots) {
+                    const int64_t cls = __builtin_amdgcn_readlane(cur.x, j + 32);
+                    t = __hip_atomic_load(a.class_cost + cls * ns + sigma, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+                }
+                if (meta & kLinked) {
+                    // the op it is linked to finished at p: the barrier, and this member's own
+                    // launch, are no earlier
+                    int64_t own = keep ? (sbase + (int64_t)op * ns)[col] : 0, p;
+                    if (sq < kStreams) {
+                        p = smem[sq * kLanes];
+                    } else {
+                        p = (fbase + (int64_t)__builtin_amdgcn_readlane(cur.z, j + 32) * ns)[col];
+                    }
+                    __builtin_amdgcn_s_waitcnt(kWaitVm0);    // settled on this path, not at the join
+                    if (sq == 0) p = lf0;
+                    b = (uint64_t)p > b ? (uint64_t)p : b;
+                    own = p > own ? p : own;
+                    if (keep) put(sbase + (int64_t)op * ns + col, own);
+                }
+                const int64_t f = (int64_t)b + t;
+                hi_or |= (uint32_t)((uint64_t)f >> 32);
+                if (storef) put(fbase + (int64_t)op * ns + col, f);
+                if (DIGEST) {
+                    const int64_t s = (sbase + (int64_t)op * ns)[col];
+                    dig += mix64(mix64((uint64_t)op ^ (uint64_t)s) ^ (uint64_t)f);
+                }
                 xmax = f > xmax ? f : xmax;
-                const int sq = __builtin_amdgcn_readfirstlane((meta & kNoReg) ? kStreams : st);
                 if (sq == 0) lf0 = f;
-                else slot_set(sq, f);
+                else if (sq < kStreams) smem[sq * kLanes] = f;
                 if (meta & kFold) lf0 = f > lf0 ? f : lf0;
-                ++j;
                 continue;
             }
             const unsigned mask = item_regmask(meta);
             int64_t ready = 0;
             if (mask & 1u) ready = lf0;
             for (unsigned m = mask & ~1u; m; m &= m - 1) {
-                const int64_t x = slot_get(__builtin_amdgcn_readfirstlane(__builtin_ctz(m)));
+                const int64_t x = smem[__builtin_ctz(m) * kLanes];
                 ready = x > ready ? x : ready;
             }
-            for (int32_t q = 0; q < nfar; ++q) {
-                const int64_t u = a.far[far_off + q];
-                const int64_t fu = (fbase + u * ns)[col];
-                ready = fu > ready ? fu : ready;
+            if (meta & kHasFar) {
+                const int32_t far_off = __builtin_amdgcn_readlane(cur.z, j);
+                const int32_t nfar = __builtin_amdgcn_readlane(cur.z, j + 32);
+                for (int32_t q = 0; q < nfar; ++q) {
+                    const int64_t u = a.far[far_off + q];
+                    const int64_t fu = (fbase + u * ns)[col];
+                    ready = fu > ready ? fu : ready;
+                }
+                __builtin_amdgcn_s_waitcnt(kWaitVm0);        // settled on this path, not at the join
             }
-            if ((meta | keep) & kNeedS) put(sbase + (int64_t)op * ns + col, ready);
+            if (keep) put(sbase + (int64_t)op * ns + col, ready);
             if (kind == ECHO_COMM) {
                 // launch: publish this member's launch time, then count the arrival
+                const uint32_t aux = (uint32_t)__builtin_amdgcn_readlane(cur.w, j + 32);
                 if (aux & kAuxLocal) {
                     const int ch = aux_channel(aux), par = aux_parity(aux);
                     __hip_atomic_fetch_max(&lbar[ch][par][lane], (unsigned long long)ready, __ATOMIC_RELAXED,
@@ -754,8 +593,10 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
                 } else if (aux & kAuxSlots) {
                     // this member's slot (its index is in the item's duration field): one store,
                     // no wait -- the value is its own arrival flag
+                    const int64_t slot = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(cur.y, j + 32) << 32) |
+                                                   (uint32_t)__builtin_amdgcn_readlane(cur.x, j + 32));
                     if (active)
-                        __hip_atomic_store(a.slots + dur * ns + sigma, ready, __ATOMIC_RELAXED,
+                        __hip_atomic_store(a.slots + slot * ns + sigma, ready, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
                 } else {
                     if (active)
@@ -767,24 +608,22 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
                                                __HIP_MEMORY_SCOPE_AGENT);
                 }
             } else {
-                const bool stg = staged(meta, j);
-                if (stg) read_staged(j, meta);
-                int64_t d = any_jitter ? jittered(dur, op, jt) : dur;
-                if (stg) d = apply_staged(d, meta, j);
+                int64_t d;
+                if (load_d) {
+                    d = dur[__builtin_amdgcn_readfirstlane(__builtin_popcount(seg_bits & ((1u << j) - 1)))];
+                } else {
+                    d = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(cur.y, j + 32) << 32) |
+                                  (uint32_t)__builtin_amdgcn_readlane(cur.x, j + 32));
+                }
                 const int64_t f = ready + d;
                 hi_or |= (uint32_t)((uint64_t)f >> 32);
-                if ((meta | keep) & kNeedF) put(fbase + (int64_t)op * ns + col, f);
-                if (DIGEST) dig += mix64(mix64((uint64_t)op ^ (uint64_t)ready) ^ (uint64_t)f);
+                if (storef) put(fbase + (int64_t)coll * ns + col, f);
                 xmax = f > xmax ? f : xmax;
-                const int sq = __builtin_amdgcn_readfirstlane((meta & kNoReg) ? kStreams : st);
                 if (sq == 0) lf0 = f;
-                else slot_set(sq, f);
+                else if (sq < kStreams) smem[sq * kLanes] = f;
             }
-            ++j;
         }
-        fl_now = fl_next;    // loaded at the round's start, settled by the wait at its second half
     }
-#undef MEET
     if (hi_or >> 30) err |= kStatusOverflow;
     if (active && err) __hip_atomic_fetch_or(a.status, err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (FINAL && active && !dead) {
@@ -792,7 +631,7 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
         // maximum; ops without a slot went into xmax
         int64_t smax = lf0 > xmax ? lf0 : xmax;
 #pragma unroll
-        for (int q = 1; q < kStreams; ++q) smax = slot_get(q) > smax ? slot_get(q) : smax;
+        for (int q = 1; q < kStreams; ++q) smax = smem[q * kLanes] > smax ? smem[q * kLanes] : smax;
         __hip_atomic_fetch_max(reinterpret_cast<unsigned long long *>(a.step) + sigma, (unsigned long long)smax,
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (DIGEST)
@@ -803,7 +642,7 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
 
 using WalkKernel = void (*)(WalkArgs);
 WalkKernel walk_kernel(int in, bool final_pass, bool digest) {
-    // flagged mask rows only in a final pass, a digest only in a final pass
+    // a digest only in a final pass, kInMaskFlags too
     if (!final_pass) {
         if (in == kInNone) return k_walk<kInNone, false, false>;
         return in == kInExtFlags ? k_walk<kInExtFlags, false, false> : k_walk<kInMasks, false, false>;
@@ -816,20 +655,200 @@ WalkKernel walk_kernel(int in, bool final_pass, bool digest) {
     }
 }
 
+// ------------------------------------------------------------------ the ops of segments
+// One wavefront per (part, tile): the chunks part, part + parts, ... of segment records for
+// one tile.  Consecutive wavefronts take the tiles of one chunk, so that a row is written
+// whole by one workgroup at about one time, and each keeps its tile's scenario knobs.
+constexpr int kRecWaves = 4;             // wavefronts per workgroup
+constexpr int64_t kRecParts = 8192;      // wavefronts of a launch, unless there are more tiles
+
+__device__ __forceinline__ int4 load_chunk(const WalkArgs &a, int64_t chunk, int lane, int *n) {
+    *n = 0;
+    if (chunk >= a.n_chunks) return make_int4(0, 0, 0, 0);
+    const int32_t r0 = __builtin_amdgcn_readfirstlane(a.chunks[chunk].rec0);
+    *n = __builtin_amdgcn_readfirstlane(a.chunks[chunk + 1].rec0) - r0;
+    return lane < *n ? reinterpret_cast<const int4 *>(a.recs)[r0 + lane] : make_int4(0, 0, 0, 0);
+}
+
+// First pass, tiles with jitter: the sum of each segment's jittered durations, into the
+// finish row of its last op.  Bound by the draws (21 vector instructions per op and
+// scenario); the records of the next chunk are fetched while the current one is summed.
+__global__ __launch_bounds__(kRecWaves * 64) void k_sum(WalkArgs a, int64_t parts) {
+    const int lane = threadIdx.x & 63;
+    const int64_t unit = (int64_t)blockIdx.x * kRecWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t tile = a.tile0 + (int32_t)(unit % a.tiles);
+    const int64_t part = unit / a.tiles;
+    if (part >= parts) return;
+    const Lane ln = make_lane(a.scen, a.n_scen, tile, lane);
+    if (!ln.any_jitter) return;
+    const int64_t ns = a.n_scen;
+    int64_t *const fbase = a.finish + (int64_t)tile * kLanes + ln.col;
+    int nn;
+    int4 nxt = load_chunk(a, part, lane, &nn);
+    for (int64_t chunk = part; chunk < a.n_chunks; chunk += parts) {
+        const int4 cur = nxt;
+        const int n = nn;
+        __builtin_amdgcn_s_waitcnt(kWaitVm0);
+        nxt = load_chunk(a, chunk + parts, lane, &nn);
+        const uint64_t last_bits = __builtin_amdgcn_read_exec() & __ballot((uint32_t)cur.y & kRecLast);
+        const bool small = __builtin_amdgcn_readfirstlane((__builtin_amdgcn_read_exec() & __ballot(cur.w != 0)) == 0);
+        int64_t sum = 0;
+        auto body = [&](auto is_small) {
+            for (int j = 0; j < n; ++j) {
+                const int32_t op = __builtin_amdgcn_readlane(cur.x, j);
+                const uint32_t dlo = (uint32_t)__builtin_amdgcn_readlane(cur.z, j);
+                if (decltype(is_small)::value) {
+                    sum += jittered32(dlo, op, ln.jt);
+                } else {
+                    const uint32_t dhi = (uint32_t)__builtin_amdgcn_readlane(cur.w, j);
+                    sum += jittered((int64_t)(((uint64_t)dhi << 32) | dlo), op, ln.jt);
+                }
+                if ((last_bits >> j) & 1u) {
+                    fbase[(int64_t)op * ns] = sum;
+                    sum = 0;
+                }
+            }
+        };
+        if (small) body(std::true_type{});
+        else body(std::false_type{});
+    }
+}
+
+// After the last pass: the start and finish of every op that the sweep has not written (all
+// but each segment's first start and last finish), and with DIGEST the segments' share of
+// the digest.  IN: what flagged segments carry per op -- nothing (no refinement), overlap
+// masks, or extra times.  Bound by the timeline stores.
+template <int IN, bool DIGEST>
+__global__ __launch_bounds__(kRecWaves * 64) void k_expand(WalkArgs a, int64_t parts) {
+    const int lane = threadIdx.x & 63;
+    const int64_t unit = (int64_t)blockIdx.x * kRecWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t tile = a.tile0 + (int32_t)(unit % a.tiles);
+    const int64_t part = unit / a.tiles;
+    if (part >= parts) return;
+    const Lane ln = make_lane(a.scen, a.n_scen, tile, lane);
+    const int64_t ns = a.n_scen;
+    int64_t *const sbase = a.start + (int64_t)tile * kLanes + ln.col;
+    int64_t *const fbase = a.finish + (int64_t)tile * kLanes + ln.col;
+    const uint4 *const slow = reinterpret_cast<const uint4 *>(&a.scen[ln.sigma].slowdown_q16[0][0]);
+    uint64_t dig = 0;
+    typedef int64_t Starts __attribute__((ext_vector_type(8)));
+    typedef uint32_t Ins __attribute__((ext_vector_type(8)));
+    int nn;
+    int4 nxt = load_chunk(a, part, lane, &nn);
+    for (int64_t chunk = part; chunk < a.n_chunks; chunk += parts) {
+        const int4 cur = nxt;
+        const int n = nn;
+        const uint64_t first_bits = __builtin_amdgcn_read_exec() & __ballot((uint32_t)cur.y & kRecFirst);
+        const uint64_t last_bits = __builtin_amdgcn_read_exec() & __ballot((uint32_t)cur.y & kRecLast);
+        const bool small = __builtin_amdgcn_readfirstlane((__builtin_amdgcn_read_exec() & __ballot(cur.w != 0)) == 0);
+        const uint64_t cand_bits = IN == kInNone ? 0 : __builtin_amdgcn_read_exec() & __ballot((uint32_t)cur.y & kRecCand);
+        const int64_t rec0 = __builtin_amdgcn_readfirstlane(a.chunks[chunk].rec0);
+        uint64_t flag_bits = 0;                   // flags of the chunk's overlap segments, in order
+        if (cand_bits) {
+            const int64_t c0 = __builtin_amdgcn_readfirstlane(a.chunks[chunk].cand0);
+            const int nc = __builtin_popcountll(cand_bits);
+            const uint8_t fl = lane < nc ? a.xflag[(c0 + lane) * a.n_tiles + tile] : 0;
+            flag_bits = __ballot(fl != 0);
+        }
+        // starts of the chunk's next eight segments, fetched together
+        uint64_t todo = first_bits;
+        Starts s8 = 0;
+        int is = 8, ic = 0;
+        int64_t s = 0;
+        Ins x8 = 0;
+        bool flagged = false;
+        int j0 = 0;
+        auto body = [&](auto jit, auto is_small) {
+            for (int j = 0; j < n; ++j) {
+                const int32_t op = __builtin_amdgcn_readlane(cur.x, j);
+                const uint32_t dlo = (uint32_t)__builtin_amdgcn_readlane(cur.z, j);
+                const bool first = (first_bits >> j) & 1u, last = (last_bits >> j) & 1u;
+                if (first) {
+                    if (is == 8) {
+#pragma unroll
+                        for (int q = 0; q < 8; ++q)
+                            if (todo) {
+                                const int64_t v = __builtin_amdgcn_readlane(cur.x, __builtin_ctzll(todo));
+                                todo &= todo - 1;
+                                s8[q] = sbase[v * ns];
+                            }
+                        is = 0;
+                    }
+                    s = s8[is];
+                    ++is;
+                    if (IN != kInNone) {
+                        flagged = false;
+                        if ((cand_bits >> j) & 1u) {
+                            flagged = (flag_bits >> ic) & 1u;
+                            ++ic;
+                        }
+                        j0 = j;
+                    }
+                }
+                int64_t d;
+                if (decltype(is_small)::value) {
+                    d = decltype(jit)::value ? jittered32(dlo, op, ln.jt) : (int64_t)dlo;
+                } else {
+                    const uint32_t dhi = (uint32_t)__builtin_amdgcn_readlane(cur.w, j);
+                    const int64_t d0 = (int64_t)(((uint64_t)dhi << 32) | dlo);
+                    d = decltype(jit)::value ? jittered(d0, op, ln.jt) : d0;
+                }
+                if (IN != kInNone && flagged) {
+                    const int q0 = (j - j0) & 7;
+                    if (q0 == 0) {
+                        // the segment's next eight masks (extra times), in one round trip
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) {
+                            if (j + q >= n) continue;
+                            const int64_t at = (rec0 + j + q) * a.mstride + (int64_t)tile * kLanes + ln.col;
+                            x8[q] = IN == kInExtFlags ? a.ext[at] : (uint32_t)a.tmask[at];
+                        }
+                    }
+                    const uint32_t meta = (uint32_t)__builtin_amdgcn_readlane(cur.y, j);
+                    if (meta & kRecCompute) {
+                        const uint32_t x = x8[q0];
+                        if (IN == kInExtFlags) {
+                            d += x;
+                        } else if (__ballot(x != 0)) {
+                            const uint4 row = slow[meta & 7u];
+                            d = inflate_row(d, x, row);
+                        }
+                    }
+                }
+                const int64_t f = s + d;
+                if (a.timelines) {
+                    if (!first) put(sbase + (int64_t)op * ns, s);
+                    if (!last) put(fbase + (int64_t)op * ns, f);
+                }
+                if (DIGEST) dig += mix64(mix64((uint64_t)op ^ (uint64_t)s) ^ (uint64_t)f);
+                s = f;
+            }
+        };
+        nxt = load_chunk(a, chunk + parts, lane, &nn);
+        if (ln.any_jitter) {
+            if (small) body(std::true_type{}, std::true_type{});
+            else body(std::true_type{}, std::false_type{});
+        } else {
+            body(std::false_type{}, std::false_type{});
+        }
+    }
+    if (DIGEST && ln.active)
+        __hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(a.digest) + ln.sigma, (unsigned long long)dig,
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // ------------------------------------------------------------------ overlap detection
-// One wavefront per (rank, tile).  Compute ops of one stream run back to back,
-// and so do the comm ops of one stream, so for each comm stream a cursor that
-// only moves forward finds every comm op overlapping the current compute op.
-// After compute op v the cursor of each comm stream sits on a comm op that ends
-// after v started (at or after v finished, once v had to look at that stream:
-// every later compute op of v's stream starts at or after v's finish); for the next
-// compute op v', "that comm op starts at or after v' ends" proves both "no
-// overlap" and "cursor stays" -- one compare per comm stream in the common
-// case.  A compute op's interval is
-// rebuilt rather than read: a chained op starts where the previous compute op
-// of its stream finished, and every finish is start + base duration (the same
-// jitter draw as the composer pass, inflated by the factor that pass used);
-// only unchained ops read their start.
+// A wavefront takes groups of kOverlapGroup segments for one tile.  Comm ops of a stream
+// finish in order, so a segment overlaps none of a range's comm ops when the range's last
+// one finishes by the segment's start: one load per range settles most segments, which
+// then cost nothing more.  For the others the range's first comm op that ends after the
+// segment's start is searched (backwards from the last, in doubling steps), and from
+// there a cursor that only moves forward meets every comm op overlapping the segment's
+// ops in turn.  The ops' intervals are rebuilt, not read: the first starts with the segment,
+// each later one where the one before finished, and a finish is start + base duration (the
+// same jitter draw as the composer pass, inflated by the factor that pass used).  With
+// the new factors the segment's new duration is known at once; its finish row is moved to
+// start + that duration, where the next pass takes it from.
 // Factor of a class-cls compute op overlapping the collective types in mask m:
 // the largest entry of the scenario's table row over them, 65536 for none.
 __device__ __forceinline__ uint32_t factor_of(uint32_t m, const uint32_t *slow, int cls) {
@@ -850,8 +869,6 @@ __device__ __forceinline__ uint32_t factor_of(uint32_t m, const uint32_t *slow, 
 // needs a type shares one feature vector, once for the wavefront with one tree
 // per lane, else per lane.
 constexpr int kForestLanes = 16;
-constexpr int kPre = 8;          // unchained starts prefetched per round of overlap detection
-constexpr int kIdStage = 1024;   // comm ops of a rank whose ids overlap detection keeps in LDS
 
 // feat: this wavefront's LDS feature rows, feature k of lane l at feat[k * 64 + l].
 __device__ uint32_t forest_factor(const OverlapArgs &a, uint32_t m, const int64_t *smax, const int32_t *nmax,
@@ -944,9 +961,9 @@ __device__ __forceinline__ int32_t fx_bin(const int64_t *T, int32_t n, int64_t x
     return lo;
 }
 
-// Bins of every collective's S and cost N (features 3 and 4) and of every compute
+// Bins of every collective's S and cost N (features 3 and 4) and of every segment
 // record's base duration (feature 1).
-__global__ void k_forest_bins(CollTable colls, const ComputeRec *cp, int64_t n_cp, CompactForest fx) {
+__global__ void k_forest_bins(CollTable colls, const SegRec *recs, int64_t n_recs, CompactForest fx) {
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t nth = (int64_t)gridDim.x * blockDim.x;
     const int64_t *T1 = fx.thr + fx.thr_off[1], *T3 = fx.thr + fx.thr_off[3], *T4 = fx.thr + fx.thr_off[4];
@@ -956,7 +973,7 @@ __global__ void k_forest_bins(CollTable colls, const ComputeRec *cp, int64_t n_c
         fx.coll_bin[2 * c] = fx_bin(T3, n3, colls.bytes[c]);
         fx.coll_bin[2 * c + 1] = fx_bin(T4, n4, colls.N[c]);
     }
-    for (int64_t i = tid; i < n_cp; i += nth) fx.cp_bin[i] = fx_bin(T1, n1, cp[i].dur);
+    for (int64_t i = tid; i < n_recs; i += nth) fx.cp_bin[i] = fx_bin(T1, n1, recs[i].dur);
 }
 
 // Ensemble prediction from the compact LDS form, for the collective types in mask m
@@ -1046,76 +1063,45 @@ __device__ uint32_t forest_factor_compact(const OverlapArgs &a, uint32_t m, cons
 // order), and record the extra time q16(min(o, D), F) - min(o, D) instead of a mask.
 // DETECT: flag the scenarios whose durations change (fixed-point iteration).
 // FOREST: the factor is the tree ensemble's prediction (recorded as an extra time):
-// 1 walks the ensemble from device memory, 2 from its compact form in LDS (a workgroup
-// of kFxWaves wavefronts, one (rank, tile) each, shares one copy of the nodes).
-// NC: room for this many comm streams per rank (the cursor and merge state scale with it).
-constexpr int kFxWaves = 4;
-// The fixed-point prorating variant with four comm streams is held to four waves per SIMD
-// (at most 128 registers; left free it took 142, three waves per SIMD, and its 4,096
-// wavefronts on the 1024-rank workload ran in two rounds): a few spilled registers cost far
-// less than the second round.
+// 1 walks the ensemble from device memory, 2 from its compact form in LDS (the
+// workgroup's wavefronts share one copy of the nodes).
+// NC: room for this many comm ranges per segment (the cursor and merge state scale with it).
+constexpr int kOverlapWaves = 4;         // wavefronts per workgroup
 template <bool PRORATE, bool DETECT, int FOREST, int NC>
-__global__ __launch_bounds__(64 * (FOREST == 2 ? kFxWaves : 1))
-__attribute__((amdgpu_waves_per_eu(PRORATE && DETECT && FOREST == 0 && NC == 4 ? 4 : 1))) void k_overlap(OverlapArgs a) {
+__global__ __launch_bounds__(64 * kOverlapWaves) void k_overlap(OverlapArgs a, int64_t parts) {
     constexpr bool EXT = PRORATE || FOREST != 0;  // output: extra time per op instead of a mask
-    constexpr int W = FOREST == 2 ? kFxWaves : 1;      // wavefronts per workgroup
-    constexpr int STAGE = FOREST == 2 ? kIdStage / 4 : kIdStage;
-    // unchained starts prefetched per round: as many as the registers allow while the
-    // variants with four comm streams keep four wavefronts per SIMD (the prorating and
-    // fixed-point variants hold more state for their block checks and interval merges)
-    constexpr int NPRE = FOREST ? kPre : PRORATE ? kPre / 4 : DETECT ? (NC == 4 ? kPre / 2 : kPre / 4) : NC == 4 ? kPre : kPre / 2;
-    __shared__ int64_t feat[FOREST == 1 ? 12 * kLanes : 1];   // the ensemble's feature vectors, one per lane
+    constexpr int W = kOverlapWaves;
+    __shared__ int64_t feat_all[FOREST == 1 ? W * 12 * kLanes : 1];   // the ensemble's feature vectors, one per lane
     __shared__ uint16_t fbin[FOREST == 2 ? W * kFxRows * kLanes : 1];   // compact: bin rows per lane
     extern __shared__ uint32_t fwords[];         // compact: the ensemble's nodes
-    __shared__ int32_t sid_all[W * STAGE];       // the rank's comm op ids and collective types, staged
-    __shared__ uint8_t stype_all[W * STAGE];
-    // masks of the round's ops, [op][lane]: written out row by row once per round
-    __shared__ __align__(16) uint8_t mstage[EXT ? 16 : kLanes * kLanes];
     if (a.stable && __builtin_amdgcn_readfirstlane(__hip_atomic_load(a.stable, __ATOMIC_RELAXED,
                                                                       __HIP_MEMORY_SCOPE_AGENT)))
         return;                                  // every scenario is at its fixed point
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t unit = (int64_t)blockIdx.x * W + wave;       // (rank, tile) of this wavefront
-    const bool valid = unit < (int64_t)a.n_ranks * a.n_tiles;
-    const int32_t r = valid ? (int32_t)(unit / a.n_tiles) : 0;
-    const int32_t tile = valid ? (int32_t)(unit % a.n_tiles) : 0;
-    int32_t *const sid = sid_all + wave * STAGE;
-    uint8_t *const stype = stype_all + wave * STAGE;
+    const int64_t unit = (int64_t)blockIdx.x * W + wave;
+    const int32_t tile = (int32_t)(unit % a.n_tiles);
+    const int64_t part = unit / a.n_tiles;
     if (FOREST == 2) {
         // the nodes, then the roots of the trees
         for (int i = threadIdx.x; i < a.fx.n_words; i += 64 * W) fwords[i] = a.fx.words[i];
         for (int i = threadIdx.x; i < a.n_trees; i += 64 * W) fwords[a.fx.n_words + i] = (uint32_t)a.forest_roots[i];
+        __syncthreads();
     }
-    const bool active = tile * kLanes + lane < a.n_scen;
-    const int32_t col = active ? lane : a.n_scen - 1 - tile * kLanes;
-    const int32_t sigma = tile * kLanes + col;
+    if (part >= parts) return;                   // after the shared fill
+    const Lane ln = make_lane(a.scen, a.n_scen, tile, lane);
+    const int32_t col = ln.col, sigma = ln.sigma;
+    const bool any_jitter = ln.any_jitter;
     const int64_t ns = a.n_scen;
-    const int64_t *const sbase = a.start + (int64_t)tile * kLanes;
-    const int64_t *const fbase = a.finish + (int64_t)tile * kLanes;
-    uint8_t *const obase = a.tmask + (int64_t)tile * kLanes;
-    uint32_t *const ebase = a.ext + (int64_t)tile * kLanes;
+    const int64_t *const sbase = a.start + (int64_t)tile * kLanes + col;
+    int64_t *const fbase = a.finish + (int64_t)tile * kLanes + col;
+    uint8_t *const obase = a.tmask + (int64_t)tile * kLanes + col;
+    uint32_t *const ebase = a.ext + (int64_t)tile * kLanes + col;
     const echo_scenario *sc = a.scen + sigma;
     const uint32_t *slow = &sc->slowdown_q16[0][0];
-    const int32_t amp = sc->jitter_amp_q16;
-    const Jitter jt = make_jitter(sc->jitter_seed, sc->jitter_stream, amp);
-    // one branch for the wavefront: a lane without jitter draws the identity factor
-    const bool any_jitter = __builtin_amdgcn_readfirstlane(__ballot(amp != 0) != 0);
-    const int64_t *cl_off = a.cl_off + (int64_t)r * kStreams;
-    const int64_t *cp_off = a.cp_off + (int64_t)r * kStreams;
     bool changed = false;                        // some duration differs from the previous pass's
     bool ext_over = false;                       // a prorated extra time does not fit 32 bits
-
-    // Stage the rank's comm lists in LDS: a cursor move then costs one memory round trip
-    // (the comm op's interval) instead of two (its id, then the interval).
-    const int64_t cbase = cl_off[0];
-    const int64_t nstage = !valid ? 0 : cl_off[kStreams] - cbase < STAGE ? cl_off[kStreams] - cbase : STAGE;
-    for (int64_t i = lane; i < nstage; i += kLanes) {
-        sid[i] = a.cl[cbase + i];
-        stype[i] = a.cl_type[cbase + i];
-    }
-    __syncthreads();
-    if (!valid) return;                          // past the last (rank, tile); after the shared fill
+    int64_t *const feat = feat_all + (FOREST == 1 ? wave * 12 * kLanes : 0);
     // compact ensemble: this wavefront's bin rows; the scenario knobs' rows are fixed
     uint16_t *const fb = fbin + (FOREST == 2 ? wave * kFxRows * kLanes : 0);
     bool knobs_uniform = false;
@@ -1136,212 +1122,106 @@ __attribute__((amdgpu_waves_per_eu(PRORATE && DETECT && FOREST == 0 && NC == 4 ?
         knobs_uniform = __ballot(k5 != __builtin_amdgcn_readfirstlane(k5) || k6 != __shfl(k6, 0) ||
                                  k7 != __shfl(k7, 0)) == 0;
     }
-    // comm op at position x of the rank's lists and its collective type
-    auto comm_id = [&](int64_t x) -> int64_t {
-        const int64_t o = x - cbase;
-        if (o < nstage) return sid[o];
-        return __hip_atomic_load(a.cl + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-    auto comm_type = [&](int64_t x) -> uint32_t {
-        const int64_t o = x - cbase;
-        if (o < nstage) return stype[o];
-        // an atomic load keeps this read and the LDS one from merging into a flat load
-        return __hip_atomic_load(a.cl_type + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
+    typedef uint32_t Olds __attribute__((ext_vector_type(8)));
 
-    // comm streams of this rank that carry comm ops, packed to the front
-    int64_t kb[NC];
-    int32_t nk[NC];
-    int ncs = 0;
+    const int4 *const osegs4 = reinterpret_cast<const int4 *>(a.osegs);
+    const int64_t groups = (a.n_osegs + kOverlapGroup - 1) / kOverlapGroup;
+    for (int64_t grp = part; grp < groups; grp += parts) {
+        const int64_t o0 = grp * kOverlapGroup;
+        const int no = a.n_osegs - o0 < kOverlapGroup ? (int)(a.n_osegs - o0) : kOverlapGroup;
+        // lane 2q holds the first half of segment q, lane 2q + 1 the second
+        const int4 os = lane < 2 * no ? osegs4[2 * o0 + lane] : make_int4(0, 0, 0, 0);
+        uint8_t *const flag = a.xflag + (o0 + lane) * a.n_tiles + tile;      // of segment `lane`
+        // segments inflated in the previous pass
+        uint32_t was = 0;
+        if (a.prev_refined) was = (uint32_t)__ballot(lane < no && *flag != 0);
+        uint32_t now = 0;
+        for (int q = 0; q < no; ++q) {
+            const int32_t first = __builtin_amdgcn_readlane(os.z, 2 * q), last = __builtin_amdgcn_readlane(os.w, 2 * q);
+            const int32_t cand0 = __builtin_amdgcn_readlane(os.x, 2 * q + 1);
+            const int ncand = __builtin_amdgcn_readlane(os.y, 2 * q + 1);
+            const bool was_on = (was >> q) & 1u;
+            const int64_t s = sbase[(int64_t)first * ns];
+            bool late[NC];                       // the range's last comm op finishes after s
+            bool any = false;
 #pragma unroll
-    for (int k = 0; k < NC; ++k) {
-        kb[k] = 0;
-        nk[k] = 0;
-    }
-    for (int k = 0; k < kStreams; ++k) {
-        const int64_t b = cl_off[k], n = cl_off[k + 1] - b;
-        if (n == 0) continue;
-#pragma unroll
-        for (int q = 0; q < NC; ++q)
-            if (q == ncs) {
-                kb[q] = b;
-                nk[q] = (int32_t)n;
-            }
-        ++ncs;
-    }
-    if (ncs > NC) {
-        // more comm streams than this variant holds: the loader counts them, so never
-        if (lane == 0) __hip_atomic_fetch_or(a.status, kStatusRange, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return;
-    }
-
-    for (int s = 0; s < kStreams; ++s) {
-        const int64_t b0 = cp_off[s], b1 = cp_off[s + 1];
-        if (b0 == b1) continue;
-        int32_t p[NC];
-        int64_t cs[NC], cf[NC];
-#pragma unroll
-        for (int k = 0; k < NC; ++k) {
-            p[k] = 0;
-            cs[k] = kInf;
-            cf[k] = kInf;
-            if (k < ncs) {
-                const int64_t c = a.cl[kb[k]];
-                cs[k] = (sbase + c * ns)[col];
-                cf[k] = (fbase + c * ns)[col];
-            }
-        }
-        // earliest start among the cursors: an op ending by then overlaps nothing
-        int64_t cmin = kInf;
-#pragma unroll
-        for (int k = 0; k < NC; ++k) cmin = cs[k] < cmin ? cs[k] : cmin;
-        int64_t fprev = 0;
-        // lane j holds compute record i0 + j of the current round of 64
-        const int4 *recs = reinterpret_cast<const int4 *>(a.cp);
-        int4 nxt = b0 + lane < b1 ? recs[b0 + lane] : make_int4(0, 0, 0, 0);
-        int32_t nxt_pos = b0 + lane < b1 ? a.cp_pos[b0 + lane] : 0;
-        for (int64_t i0 = b0; i0 < b1; i0 += kLanes) {
-            const int4 cur = nxt;
-            const int32_t cur_pos = nxt_pos;
-            // settle the round's records here, once, so the per-op loop below carries
-            // no memory wait (a wait there would also wait for the previous op's store)
-            __builtin_amdgcn_s_waitcnt(kWaitVm0);
-            nxt = i0 + kLanes + lane < b1 ? recs[i0 + kLanes + lane] : make_int4(0, 0, 0, 0);
-            nxt_pos = i0 + kLanes + lane < b1 ? a.cp_pos[i0 + kLanes + lane] : 0;
-            const int nr = b1 - i0 < kLanes ? int(b1 - i0) : kLanes;
-            // the starts of the round's first NPRE unchained ops, fetched together
-            const uint64_t unchained = __builtin_amdgcn_read_exec() &
-                                       __ballot(lane < nr && !((uint32_t)cur.y & kChained));
-            int64_t pre[NPRE];
-            // finishes of the round's blocks' last ops (stored by the walk): a block ending
-            // before every cursor starts is skipped whole
-            constexpr int kBlocks = kLanes / kOverlapBlock;
-            int64_t ck[kBlocks];
-            // the fixed-point variants (every pass after the first reads the previous pass's
-            // values): the current block's previous masks or extra times
-            uint32_t old8[DETECT ? kOverlapBlock : 1];
-#pragma unroll
-            for (int b = 0; b < kBlocks; ++b) {
-                ck[b] = kInf;
-                if (b * kOverlapBlock < nr) {
-                    const int jl = (b + 1) * kOverlapBlock - 1 < nr ? (b + 1) * kOverlapBlock - 1 : nr - 1;
-                    const int64_t vl = __builtin_amdgcn_readlane(cur.x, jl);
-                    ck[b] = (fbase + vl * ns)[col];
+            for (int k = 0; k < NC; ++k) {
+                late[k] = false;
+                if (k < ncand) {
+                    const int64_t c = __builtin_amdgcn_readfirstlane(a.ranges[cand0 + k].last_op);
+                    late[k] = fbase[c * ns] > s;
+                    any = any || late[k];
                 }
             }
-            {
-                uint64_t um = unchained;
+            if (!was_on && !__builtin_amdgcn_readfirstlane(__ballot(any) != 0)) continue;
+
+            // some lane's segment may overlap: cursors at the first comm op ending after s
+            const int32_t rec0 = __builtin_amdgcn_readlane(os.x, 2 * q);
+            const int nr = __builtin_amdgcn_readlane(os.y, 2 * q);
+            const int4 cur = lane < nr ? reinterpret_cast<const int4 *>(a.recs)[rec0 + lane] : make_int4(0, 0, 0, 0);
+            int32_t p[NC], hi[NC];
+            int64_t cs[NC], cf[NC];
+            int64_t cmin = kInf;                 // earliest start among the cursors: an op ending by then overlaps nothing
 #pragma unroll
-                for (int q = 0; q < NPRE; ++q) {
-                    pre[q] = 0;
-                    if (um) {
-                        const int jq = __builtin_ctzll(um);
-                        um &= um - 1;
-                        const int64_t vq = __builtin_amdgcn_readlane(cur.x, jq);
-                        pre[q] = (sbase + vq * ns)[col];
-                    }
-                }
-                __builtin_amdgcn_s_waitcnt(kWaitVm0);
-            }
-            for (int j = 0; j < nr; ++j) {
-                if ((j & (kOverlapBlock - 1)) == 0) {
-                    if (DETECT && a.prev_refined) {
-                        // the previous pass's masks (extra times) of the block's ops, fetched
-                        // together: one memory round trip per block instead of one per op
-#pragma unroll
-                        for (int q = 0; q < kOverlapBlock; ++q) {
-                            old8[q] = 0;
-                            if (j + q < nr) {
-                                const int64_t rq = (int64_t)__builtin_amdgcn_readlane(cur_pos, j + q) * a.mstride;
-                                old8[q] = EXT ? (ebase + rq)[col] : (uint32_t)(obase + rq)[col];
-                            }
-                        }
-                        __builtin_amdgcn_s_waitcnt(kWaitVm0);
-                    }
-                    int64_t c = kInf;
-#pragma unroll
-                    for (int b = 0; b < kBlocks; ++b)
-                        if (b == (j >> 3)) c = ck[b];
-                    if (!__builtin_amdgcn_readfirstlane(__ballot(c > cmin) != 0)) {
-                        // every op of the block ends by cmin: no overlaps, no cursor moves
-                        const int je = j + kOverlapBlock < nr ? j + kOverlapBlock : nr;
-                        if (EXT) {
-                            // no extra times; DETECT: a duration changes where the previous
-                            // pass added one
-                            if (DETECT && a.prev_refined) {
-                                uint32_t eo = 0;
-#pragma unroll
-                                for (int q = 0; q < kOverlapBlock; ++q) eo |= old8[q];
-                                changed |= eo != 0;
-                            }
-                            for (int jj = j; jj < je; ++jj)
-                                (ebase + (int64_t)__builtin_amdgcn_readlane(cur_pos, jj) * a.mstride)[col] = 0;
+            for (int k = 0; k < NC; ++k) {
+                p[k] = hi[k] = 0;
+                cs[k] = cf[k] = kInf;
+                if (k < ncand) {
+                    int32_t lo = __builtin_amdgcn_readfirstlane(a.ranges[cand0 + k].lo);
+                    hi[k] = __builtin_amdgcn_readfirstlane(a.ranges[cand0 + k].hi);
+                    // finishes before lo are by s, those from x on after it
+                    int32_t x = late[k] ? hi[k] - 1 : lo, step = 1;
+                    while (lo < x) {
+                        const int32_t m = step ? (x - step > lo ? x - step : lo) : lo + (x - lo) / 2;
+                        if (fbase[(int64_t)a.cl[m] * ns] > s) {
+                            x = m;
+                            step *= 2;
                         } else {
-                            for (int jj = j; jj < je; ++jj) mstage[jj * kLanes + lane] = 0;
-                            if (DETECT && a.prev_refined) {
-                                // an op inflated in the previous pass runs with D now: a change
-                                // unless its factor left D as it was
-                                const uint32_t *const mo = old8;
-#pragma unroll
-                                for (int q = 0; q < kOverlapBlock; ++q) {
-                                    if (!__builtin_amdgcn_readfirstlane(__ballot(mo[q] != 0) != 0)) continue;
-                                    const int64_t vq = __builtin_amdgcn_readlane(cur.x, j + q);
-                                    const int mq = __builtin_amdgcn_readlane(cur.y, j + q);
-                                    const int64_t dq = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(cur.w, j + q) << 32) |
-                                                                 (uint32_t)__builtin_amdgcn_readlane(cur.z, j + q));
-                                    const int64_t Dq = any_jitter ? jittered(dq, (int32_t)vq, jt) : dq;
-                                    if (mo[q] != 0) changed |= q16(Dq, factor_of(mo[q], slow, mq & 7)) != Dq;
-                                }
-                            }
+                            lo = m + 1;
+                            step = 0;            // bracketed: bisect
                         }
-                        fprev = c;
-                        j = je - 1;
-                        continue;
                     }
+                    p[k] = late[k] ? x : hi[k];
+                    if (late[k]) {
+                        const int64_t c = a.cl[x];
+                        cs[k] = sbase[c * ns];
+                        cf[k] = fbase[c * ns];
+                    }
+                    cmin = cs[k] < cmin ? cs[k] : cmin;
                 }
-                const int64_t v = __builtin_amdgcn_readlane(cur.x, j);
-                // v's row of the per-item outputs (computed where used: the common path needs none)
-                auto row = [&]() { return (int64_t)__builtin_amdgcn_readlane(cur_pos, j) * a.mstride; };
-                const int meta = __builtin_amdgcn_readlane(cur.y, j);
-                const int cls = meta & 7;
+            }
+            int64_t fprev = s;                   // the next op's start
+            int64_t total = 0;                   // the segment's new duration
+            bool hit = false;
+            Olds old8 = 0;
+            for (int j = 0; j < nr; ++j) {
+                const int32_t v = __builtin_amdgcn_readlane(cur.x, j);
+                const uint32_t meta = (uint32_t)__builtin_amdgcn_readlane(cur.y, j);
+                const int cls = (int)(meta & 7u);
                 const int64_t d0 = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(cur.w, j) << 32) |
                                              (uint32_t)__builtin_amdgcn_readlane(cur.z, j));
-                // Loads in this loop are waited for on their own path (explicit vmcnt(0)):
-                // left pending, they would make the compiler wait at the next join, on
-                // every path, for the previous op's store as well.
-                int64_t sv = fprev;
-                if (__builtin_expect(!(meta & kChained), 0)) {
-                    const int ord = __builtin_popcountll(unchained & ((uint64_t(1) << j) - 1));
-                    if (ord < NPRE) {
+                const int64_t row = (int64_t)(rec0 + j) * a.mstride;
+                uint32_t ov = 0;                 // the previous pass's mask (extra time)
+                if (was_on) {
+                    if ((j & 7) == 0) {
+                        // of the next eight ops, in one memory round trip
 #pragma unroll
-                        for (int q = 0; q < NPRE; ++q)
-                            if (q == ord) sv = pre[q];
-                    } else {
-                        sv = (sbase + v * ns)[col];
-                        __builtin_amdgcn_s_waitcnt(kWaitVm0);
+                        for (int i = 0; i < 8; ++i)
+                            if (j + i < nr) old8[i] = EXT ? ebase[row + i * a.mstride] : (uint32_t)obase[row + i * a.mstride];
                     }
+                    ov = old8[j & 7];
                 }
-                const int64_t D = any_jitter ? jittered(d0, (int32_t)v, jt) : d0;
+                const int64_t sv = fprev;
+                const int64_t D = any_jitter ? jittered(d0, v, ln.jt) : d0;
+                if (!(meta & kRecCompute)) {     // a memcpy runs for its base duration
+                    if (EXT) ebase[row] = 0;
+                    else obase[row] = 0;
+                    fprev = sv + D;
+                    total += D;
+                    continue;
+                }
                 int64_t d = D;                   // the duration v ran with in the previous pass
-                uint32_t m_old = 0, e_old = 0;
-                if (a.prev_refined) {
-                    uint32_t ov = 0;
-                    if (DETECT) {
-#pragma unroll
-                        for (int q = 0; q < kOverlapBlock; ++q)
-                            if (q == (j & (kOverlapBlock - 1))) ov = old8[q];
-                    } else {
-                        ov = EXT ? (ebase + row())[col] : (uint32_t)(obase + row())[col];
-                        __builtin_amdgcn_s_waitcnt(kWaitVm0);
-                    }
-                    if (EXT) {
-                        e_old = ov;
-                        d = D + e_old;
-                    } else {
-                        m_old = ov;
-                        if (m_old != 0) d = q16(D, factor_of(m_old, slow, cls));
-                    }
-                }
+                if (was_on) d = EXT ? D + ov : ov != 0 ? q16(D, factor_of(ov, slow, cls)) : D;
                 const int64_t fv = sv + d;
                 fprev = fv;
                 const bool busy = cmin < fv;
@@ -1349,7 +1229,7 @@ __attribute__((amdgpu_waves_per_eu(PRORATE && DETECT && FOREST == 0 && NC == 4 ?
                 int64_t o = 0;                             // covered length (PRORATE)
                 int64_t smax[kTypes];                      // FOREST: largest S per overlapping type
                 int32_t nmax[kTypes];                      //         and most members (compact: their bins)
-    #pragma unroll
+#pragma unroll
                 for (int tt = 0; tt < kTypes; ++tt) {
                     smax[tt] = 0;
                     nmax[tt] = 0;
@@ -1366,42 +1246,29 @@ __attribute__((amdgpu_waves_per_eu(PRORATE && DETECT && FOREST == 0 && NC == 4 ?
         }                                                                                        \
     }
                 if (busy) {
-    #pragma unroll
+#pragma unroll
                     for (int k = 0; k < NC; ++k) {
-                        if (k >= ncs) break;
+                        if (k >= ncand) break;
                         if (!(cs[k] < fv)) continue;
-                        if (!PRORATE) {
-                            // The cursor walks the intervals that start before v ends; one
-                            // that also ends before then is behind every later op of this
-                            // compute stream (each starts at or after v's finish) and is
-                            // passed for good, so every comm interval is loaded once, when the
-                            // cursor reaches it.
-                            while (cs[k] < fv) {
-                                const int64_t lo = sv > cs[k] ? sv : cs[k], hi = fv < cf[k] ? fv : cf[k];
-                                if (lo < hi) {
-                                    const uint32_t ty = comm_type(kb[k] + p[k]);
+                        // The cursor walks the intervals that start before v ends; one that also
+                        // ends before then is behind every later op of the segment (each starts at
+                        // or after v's finish) and is passed for good.  Prorating, the merge below
+                        // walks the overlapping ones: the cursor passes only those ending by sv.
+                        while (PRORATE ? cf[k] <= sv : cs[k] < fv) {
+                            if (!PRORATE) {
+                                const int64_t lo = sv > cs[k] ? sv : cs[k], up = fv < cf[k] ? fv : cf[k];
+                                if (lo < up) {
+                                    const uint32_t ty = a.cl_type[p[k]];
                                     m |= 1u << ty;
-                                    NOTE_FOREST(kb[k] + p[k], ty)
+                                    NOTE_FOREST(p[k], ty)
                                 }
                                 if (cf[k] >= fv) break;    // reaches v's end: later ops may overlap it
-                                ++p[k];
-                                if (p[k] < nk[k]) {
-                                    const int64_t c = comm_id(kb[k] + p[k]);
-                                    cs[k] = (sbase + c * ns)[col];
-                                    cf[k] = (fbase + c * ns)[col];
-                                } else {
-                                    cs[k] = kInf;
-                                    cf[k] = kInf;
-                                }
                             }
-                            continue;
-                        }
-                        while (cf[k] <= sv) {              // ends before v starts: never again
                             ++p[k];
-                            if (p[k] < nk[k]) {
-                                const int64_t c = comm_id(kb[k] + p[k]);
-                                cs[k] = (sbase + c * ns)[col];
-                                cf[k] = (fbase + c * ns)[col];
+                            if (p[k] < hi[k]) {
+                                const int64_t c = a.cl[p[k]];
+                                cs[k] = sbase[c * ns];
+                                cf[k] = fbase[c * ns];
                             } else {
                                 cs[k] = kInf;
                                 cf[k] = kInf;
@@ -1409,58 +1276,57 @@ __attribute__((amdgpu_waves_per_eu(PRORATE && DETECT && FOREST == 0 && NC == 4 ?
                         }
                     }
                     if (PRORATE) {
-                        // merge the streams' overlapping intervals in start order; every one of
+                        // merge the ranges' overlapping intervals in start order; every one of
                         // them ends after sv (each stream's intervals are disjoint and sorted)
-                        int32_t q[NC];
+                        int32_t x[NC];
                         int64_t qs[NC], qf[NC];
-    #pragma unroll
+#pragma unroll
                         for (int k = 0; k < NC; ++k) {
-                            q[k] = p[k];
-                            qs[k] = k < ncs ? cs[k] : kInf;
-                            qf[k] = k < ncs ? cf[k] : kInf;
+                            x[k] = p[k];
+                            qs[k] = cs[k];
+                            qf[k] = cf[k];
                         }
                         int64_t t = sv;                    // covered up to here
                         for (;;) {
                             int bk = -1;
                             int64_t bs = fv;
-    #pragma unroll
+#pragma unroll
                             for (int k = 0; k < NC; ++k)
                                 if (qs[k] < bs) {
                                     bs = qs[k];
                                     bk = k;
                                 }
                             if (bk < 0) break;
-    #pragma unroll
+#pragma unroll
                             for (int k = 0; k < NC; ++k) {
                                 if (k != bk) continue;
-                                const int64_t lo = sv > qs[k] ? sv : qs[k], hi = fv < qf[k] ? fv : qf[k];
-                                if (lo < hi) {
-                                    const uint32_t ty = comm_type(kb[k] + q[k]);
+                                const int64_t lo = sv > qs[k] ? sv : qs[k], up = fv < qf[k] ? fv : qf[k];
+                                if (lo < up) {
+                                    const uint32_t ty = a.cl_type[x[k]];
                                     m |= 1u << ty;
-                                    NOTE_FOREST(kb[k] + q[k], ty)
+                                    NOTE_FOREST(x[k], ty)
                                     const int64_t from = lo > t ? lo : t;
-                                    if (hi > from) {
-                                        o += hi - from;
-                                        t = hi;
+                                    if (up > from) {
+                                        o += up - from;
+                                        t = up;
                                     }
                                 }
-                                if (++q[k] < nk[k]) {
-                                    const int64_t c = comm_id(kb[k] + q[k]);
-                                    qs[k] = (sbase + c * ns)[col];
-                                    qf[k] = (fbase + c * ns)[col];
-                                    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+                                if (++x[k] < hi[k]) {
+                                    const int64_t c = a.cl[x[k]];
+                                    qs[k] = sbase[c * ns];
+                                    qf[k] = fbase[c * ns];
                                 } else {
                                     qs[k] = kInf;
                                 }
                             }
                         }
                     }
-                    __builtin_amdgcn_s_waitcnt(kWaitVm0);
                     cmin = kInf;
 #pragma unroll
                     for (int k = 0; k < NC; ++k) cmin = cs[k] < cmin ? cs[k] : cmin;
                 }
 #undef NOTE_FOREST
+                int64_t dn;                                // v's duration in the next pass
                 if (EXT) {
                     uint32_t e = 0;
                     if (m != 0) {
@@ -1469,7 +1335,7 @@ __attribute__((amdgpu_waves_per_eu(PRORATE && DETECT && FOREST == 0 && NC == 4 ?
                             int32_t bS[kTypes];
 #pragma unroll
                             for (int tt = 0; tt < kTypes; ++tt) bS[tt] = (int32_t)smax[tt];
-                            const int32_t bd0 = a.fx.cp_bin[i0 + j];
+                            const int32_t bd0 = a.fx.cp_bin[rec0 + j];
                             F = forest_factor_compact(a, m, bS, nmax, cls, bd0, fwords,
                                                       reinterpret_cast<const int32_t *>(fwords) + a.fx.n_words, fb,
                                                       knobs_uniform, lane);
@@ -1483,38 +1349,26 @@ __attribute__((amdgpu_waves_per_eu(PRORATE && DETECT && FOREST == 0 && NC == 4 ?
                         ext_over |= x >= (int64_t)kExtLimit;
                         e = x >= (int64_t)kExtLimit ? kExtLimit : (uint32_t)x;
                     }
-                    if (DETECT) changed |= e != e_old;
-                    (ebase + row())[col] = e;
-                    // flag the row (the walk fetches only flagged rows); flags are cleared once
-                    // per compose and only ever set, so a row flagged by an earlier refinement
-                    // whose extra times are zero now is fetched and adds zero
-                    if (__builtin_amdgcn_readfirstlane(__ballot(e != 0) != 0) && lane == 0)
-                        a.xflag[(int64_t)__builtin_amdgcn_readlane(cur_pos, j) * a.n_tiles + tile] = 1;
+                    ebase[row] = e;
+                    hit |= e != 0;
+                    dn = D + e;
                 } else {
-                    if (DETECT && m != m_old)
-                        changed |= (m == 0 ? D : q16(D, factor_of(m, slow, cls))) != d;
-                    mstage[j * kLanes + lane] = (uint8_t)m;
+                    obase[row] = (uint8_t)m;
+                    hit |= m != 0;
+                    dn = m != 0 ? q16(D, factor_of(m, slow, cls)) : D;
                 }
+                if (DETECT) changed |= dn != d;
+                total += dn;
             }
-            if (!EXT && lane < nr) {
-                // lane L writes the 64 masks of the round's op L to that op's row, and the
-                // row's flag: whether any of them is nonzero (the walk fetches only those rows)
-                const uint4 *const src = reinterpret_cast<const uint4 *>(mstage + lane * kLanes);
-                uint4 *const dst = reinterpret_cast<uint4 *>(obase + (int64_t)cur_pos * a.mstride);
-                uint32_t any = 0;
-#pragma unroll
-                for (int q = 0; q < kLanes / 16; ++q) {
-                    const uint4 v = src[q];
-                    dst[q] = v;
-                    any |= v.x | v.y | v.z | v.w;
-                }
-                a.xflag[(int64_t)cur_pos * a.n_tiles + tile] = any != 0;
-            }
+            fbase[(int64_t)last * ns] = s + total;
+            if (__builtin_amdgcn_readfirstlane(__ballot(hit) != 0)) now |= 1u << q;
         }
+        if (lane < no) *flag = (now >> lane) & 1u;
     }
-    if (DETECT && active && changed)
+    if (DETECT && ln.active && changed)
         __hip_atomic_fetch_or(a.chg + sigma, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (active && ext_over) __hip_atomic_fetch_or(a.status, kStatusRange, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (ln.active && ext_over)
+        __hip_atomic_fetch_or(a.status, kStatusRange, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Count the refinement of each scenario whose durations changed; flag stability.
@@ -1575,55 +1429,72 @@ hipError_t launch_cc_cost(const CollTable &t, const echo_cc_table *tables, const
     return hipGetLastError();
 }
 
-hipError_t launch_walk(const WalkArgs &a, int32_t n_blocks, hipStream_t stream) {
-    WalkArgs args = a;
-    void *params[] = {&args};
-    const WalkKernel k = walk_kernel(walk_input(a.tmask != nullptr || a.ext != nullptr, a.ext != nullptr,
-                                                a.flag_rows != 0),
-                                     a.final_pass != 0, a.digest != nullptr);
-    return hipLaunchCooperativeKernel(reinterpret_cast<const void *>(k), dim3((unsigned)(n_blocks * a.tiles)),
-                                      dim3(kBlockWalkers * kLanes), params, 0, stream);
-}
-
-template <bool PRORATE, bool DETECT, int FOREST, int NC>
-void launch_overlap_kernel(const OverlapArgs &a, dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
-    hipLaunchKernelGGL((k_overlap<PRORATE, DETECT, FOREST, NC>), grid, block, lds, stream, a);
-}
-
-template <int NC>
-hipError_t launch_overlap_nc(const OverlapArgs &a, int32_t n_ranks, hipStream_t stream) {
-    const int64_t units = (int64_t)n_ranks * a.n_tiles;
-    const dim3 grid((unsigned)units), block(kLanes);
-    // a.ext: extra-time output (prorating and/or ensemble factors); a.forest_nodes: ensemble
-    const bool forest = a.forest_nodes != nullptr, prorate = a.prorate != 0;
-    if (forest && a.fx.n_words > 0) {
-        // compact ensemble in LDS: kFxWaves (rank, tile) units per workgroup share its nodes
-        const dim3 g2((unsigned)((units + kFxWaves - 1) / kFxWaves)), b2(kLanes * kFxWaves);
-        const size_t lds = sizeof(uint32_t) * ((size_t)a.fx.n_words + (size_t)a.n_trees);
-        if (prorate && a.chg) launch_overlap_kernel<true, true, 2, NC>(a, g2, b2, lds, stream);
-        else if (prorate) launch_overlap_kernel<true, false, 2, NC>(a, g2, b2, lds, stream);
-        else if (a.chg) launch_overlap_kernel<false, true, 2, NC>(a, g2, b2, lds, stream);
-        else launch_overlap_kernel<false, false, 2, NC>(a, g2, b2, lds, stream);
-    } else if (forest) {
-        if (prorate && a.chg) launch_overlap_kernel<true, true, 1, NC>(a, grid, block, 0, stream);
-        else if (prorate) launch_overlap_kernel<true, false, 1, NC>(a, grid, block, 0, stream);
-        else if (a.chg) launch_overlap_kernel<false, true, 1, NC>(a, grid, block, 0, stream);
-        else launch_overlap_kernel<false, false, 1, NC>(a, grid, block, 0, stream);
-    } else if (prorate && a.chg) launch_overlap_kernel<true, true, 0, NC>(a, grid, block, 0, stream);
-    else if (prorate) launch_overlap_kernel<true, false, 0, NC>(a, grid, block, 0, stream);
-    else if (a.chg) launch_overlap_kernel<false, true, 0, NC>(a, grid, block, 0, stream);
-    else launch_overlap_kernel<false, false, 0, NC>(a, grid, block, 0, stream);
+template <int IN>
+hipError_t launch_expand(const WalkArgs &a, int64_t parts, hipStream_t stream) {
+    const dim3 grid((unsigned)((parts * a.tiles + kRecWaves - 1) / kRecWaves)), block(kRecWaves * kLanes);
+    if (a.digest) hipLaunchKernelGGL((k_expand<IN, true>), grid, block, 0, stream, a, parts);
+    else hipLaunchKernelGGL((k_expand<IN, false>), grid, block, 0, stream, a, parts);
     return hipGetLastError();
 }
 
-hipError_t launch_overlap(const OverlapArgs &a, int32_t n_ranks, hipStream_t stream) {
-    if (a.max_comm_streams > 4) return launch_overlap_nc<kStreams>(a, n_ranks, stream);
-    return launch_overlap_nc<4>(a, n_ranks, stream);
+hipError_t launch_walk(const WalkArgs &a, int32_t n_blocks, hipStream_t stream) {
+    hipError_t e;
+    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(a.n_chunks, kRecParts / a.tiles));
+    if (a.in == kInNone && a.n_chunks > 0) {
+        const dim3 grid((unsigned)((parts * a.tiles + kRecWaves - 1) / kRecWaves));
+        hipLaunchKernelGGL(k_sum, grid, dim3(kRecWaves * kLanes), 0, stream, a, parts);
+        if ((e = hipGetLastError())) return e;
+    }
+    WalkArgs args = a;
+    void *params[] = {&args};
+    const WalkKernel k = walk_kernel(a.in, a.final_pass != 0, a.digest != nullptr);
+    e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(k), dim3((unsigned)(n_blocks * a.tiles)),
+                                   dim3(kBlockWalkers * kLanes), params, 0, stream);
+    if (e != hipSuccess || a.n_chunks == 0 || !a.final_pass || !(a.timelines || a.digest)) return e;
+    if (a.ext) return launch_expand<kInExtFlags>(a, parts, stream);
+    return a.tmask ? launch_expand<kInMasks>(a, parts, stream) : launch_expand<kInNone>(a, parts, stream);
 }
 
-hipError_t launch_forest_bins(const DeviceGraph &g, int64_t n_cp, const CompactForest &fx, hipStream_t stream) {
-    const int64_t n = std::max<int64_t>(g.colls.n, n_cp);
-    hipLaunchKernelGGL(k_forest_bins, dim3(grid_for(n, 256)), dim3(256), 0, stream, g.colls, g.cp, n_cp, fx);
+template <bool PRORATE, bool DETECT, int FOREST, int NC>
+void launch_overlap_kernel(const OverlapArgs &a, size_t lds, hipStream_t stream) {
+    const int64_t groups = (a.n_osegs + kOverlapGroup - 1) / kOverlapGroup;
+    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(groups, kRecParts / a.n_tiles));
+    const dim3 grid((unsigned)((parts * a.n_tiles + kOverlapWaves - 1) / kOverlapWaves)), block(kOverlapWaves * kLanes);
+    hipLaunchKernelGGL((k_overlap<PRORATE, DETECT, FOREST, NC>), grid, block, lds, stream, a, parts);
+}
+
+template <int NC>
+hipError_t launch_overlap_nc(const OverlapArgs &a, hipStream_t stream) {
+    // a.ext: extra-time output (prorating and/or ensemble factors); a.forest_nodes: ensemble
+    const bool forest = a.forest_nodes != nullptr, prorate = a.prorate != 0;
+    if (forest && a.fx.n_words > 0) {
+        // compact ensemble in LDS: the workgroup's wavefronts share its nodes
+        const size_t lds = sizeof(uint32_t) * ((size_t)a.fx.n_words + (size_t)a.n_trees);
+        if (prorate && a.chg) launch_overlap_kernel<true, true, 2, NC>(a, lds, stream);
+        else if (prorate) launch_overlap_kernel<true, false, 2, NC>(a, lds, stream);
+        else if (a.chg) launch_overlap_kernel<false, true, 2, NC>(a, lds, stream);
+        else launch_overlap_kernel<false, false, 2, NC>(a, lds, stream);
+    } else if (forest) {
+        if (prorate && a.chg) launch_overlap_kernel<true, true, 1, NC>(a, 0, stream);
+        else if (prorate) launch_overlap_kernel<true, false, 1, NC>(a, 0, stream);
+        else if (a.chg) launch_overlap_kernel<false, true, 1, NC>(a, 0, stream);
+        else launch_overlap_kernel<false, false, 1, NC>(a, 0, stream);
+    } else if (prorate && a.chg) launch_overlap_kernel<true, true, 0, NC>(a, 0, stream);
+    else if (prorate) launch_overlap_kernel<true, false, 0, NC>(a, 0, stream);
+    else if (a.chg) launch_overlap_kernel<false, true, 0, NC>(a, 0, stream);
+    else launch_overlap_kernel<false, false, 0, NC>(a, 0, stream);
+    return hipGetLastError();
+}
+
+hipError_t launch_overlap(const OverlapArgs &a, int32_t max_ranges, hipStream_t stream) {
+    if (a.n_osegs == 0) return hipSuccess;
+    if (max_ranges > 4) return launch_overlap_nc<kStreams>(a, stream);
+    return launch_overlap_nc<4>(a, stream);
+}
+
+hipError_t launch_forest_bins(const DeviceGraph &g, int64_t n_recs, const CompactForest &fx, hipStream_t stream) {
+    const int64_t n = std::max<int64_t>(g.colls.n, n_recs);
+    hipLaunchKernelGGL(k_forest_bins, dim3(grid_for(n, 256)), dim3(256), 0, stream, g.colls, g.recs, n_recs, fx);
     return hipGetLastError();
 }
 
@@ -1673,7 +1544,7 @@ hipError_t walk_capacity(int device, int64_t workgroups[kWalkVariants]) {
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(k),
                                                          kBlockWalkers * kLanes, 0);
         if (e != hipSuccess) return e;
-        workgroups[v] = (int64_t)per_cu * cus;
+        workgroups[v] = (int64_t)std::min(per_cu, kWalkersPerCu / kBlockWalkers) * cus;
     }
     return hipSuccess;
 }
