@@ -922,6 +922,9 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
         cls.set((int64_t)k, (int)classes[k][0], classes[k][1], (int32_t)classes[k][2], (int32_t)classes[k][3],
                 (int32_t)classes[k][4]);
 
+    std::vector<int32_t> class_row(classes.size(), -1);     // each class's first collective
+    for (int64_t c = nc - 1; c >= 0; --c) class_row[ccls[c]] = (int32_t)c;
+
     // upload
     echo_graph g = new (std::nothrow) echo_graph_s();
     if (!g) return fail(ECHO_ERR_NOMEM, "host allocation");
@@ -977,6 +980,9 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
         UP(dt.K, h.K);
         UP(dt.type, h.type);
     }
+    UP(dg.classes.row, class_row);
+    UP(dg.classes.class_of, ccls);
+    dg.classes.n_out = nc;
     UP(dg.members, cN);
     UP(dg.counted_members, counted_N);
     UP(dg.block_class, block_class);
@@ -1093,7 +1099,9 @@ int enqueue_compose(echo_graph g, const echo_scenario *d_scen, int32_t n_scen, c
     } while (0)
     TIMED(ECHO_K_INIT, launch_init(g->dg, d_scen, n_scen, ws.arrive, n_arrive, ws.count, n_count, ws.slots,
                                    n_slot_values, ws.step, d_digest, stream), "init kernel");
-    TIMED(ECHO_K_CC_COST, launch_cc_cost(g->dg.classes, g->dg.cc_tables, d_scen, n_scen, ws.class_cost,
+    CollTable classes = g->dg.classes;             // one row per class
+    classes.row = nullptr;
+    TIMED(ECHO_K_CC_COST, launch_cc_cost(classes, g->dg.cc_tables, d_scen, n_scen, ws.class_cost,
                                          g->dg.status, stream), "cc_cost kernel");
     if (until_stable && (e = launch_fill_i32(reinterpret_cast<int32_t *>(ws.chg), ns + 1, 0, stream)))
         return hip_fail(e, "fill kernel");
@@ -1316,7 +1324,7 @@ int echo_cc_cost(echo_graph g, const echo_scenario *d_scen, int32_t n_scen, int6
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     if ((e = launch_init(g->dg, d_scen, n_scen, nullptr, 0, nullptr, 0, nullptr, 0, nullptr, nullptr, s)))
         return hip_fail(e, "init kernel");
-    if ((e = launch_cc_cost(g->dg.colls, g->dg.cc_tables, d_scen, n_scen, d_cost, g->dg.status, s)))
+    if ((e = launch_cc_cost(g->dg.classes, g->dg.cc_tables, d_scen, n_scen, d_cost, g->dg.status, s)))
         return hip_fail(e, "cc_cost kernel");
     return ECHO_OK;
 }

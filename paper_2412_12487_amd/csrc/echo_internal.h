@@ -184,6 +184,11 @@ struct CollTable {
     int64_t *eta_chunks = nullptr;   // ceil(S / chunk)
     int32_t *N = nullptr, *M = nullptr, *K = nullptr;
     uint8_t *type = nullptr;
+    // cost classes only, to cost every collective through its class: class k's cost goes to
+    // row row[k] (its first collective) of n_out rows, and from there to the row of every
+    // other collective c of class class_of[c]
+    int32_t *row = nullptr, *class_of = nullptr;
+    int64_t n_out = 0;
 };
 
 // Device copy of a loaded graph (all pointers are device memory).

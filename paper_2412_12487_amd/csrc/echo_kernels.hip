@@ -145,10 +145,11 @@ __global__ void k_clear(unsigned long long *arrive, int64_t n_arrive, unsigned *
 }
 
 // ------------------------------------------------------------------ CC estimator
-// One block per collective (or cost class); lanes stride over scenarios.
+// One block per cost class; lanes stride over scenarios.  Row of class c: t.row[c], or c.
 __global__ __launch_bounds__(64) void k_cc_cost(CollTable t, const echo_cc_table *tables, const echo_scenario *scen,
                                                 int32_t n_scen, int64_t *cost, unsigned *status) {
     const int64_t c = blockIdx.x;
+    const int64_t row = t.row ? t.row[c] : c;
     const int type = t.type[c];
     const int64_t S = t.bytes[c];
     const int64_t N = t.N[c], M = t.M[c], K = t.K[c];
@@ -225,7 +226,27 @@ __global__ __launch_bounds__(64) void k_cc_cost(CollTable t, const echo_cc_table
             __hip_atomic_fetch_or(status, kStatusOverflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             T = (unsigned __int128)(kTimeLimit - 1);
         }
-        cost[c * n_scen + s] = (int64_t)T;
+        cost[row * n_scen + s] = (int64_t)T;
+    }
+}
+
+// Cost of every collective: its class's, from the row of the class's first collective.  The
+// 64-bit divisions and 128-bit products of the model (about a thousand instructions per
+// class and scenario) then run once per class; what is left is bound by the stores (23,808
+// collectives of 19 classes x 4000 scenarios, 762 MB: 1.88 ms when every collective was
+// costed by itself, 0.14 now).  T: two scenarios per store where rows are 16-byte aligned.
+template <class T>
+__global__ __launch_bounds__(256) void k_cc_spread(const int32_t *class_of, const int32_t *row, int64_t n,
+                                                   int32_t per_row, T *cost) {
+    const int lane = threadIdx.x & 63;
+    const int64_t step = (int64_t)gridDim.x * 4;
+    for (int64_t c = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); c < n; c += step) {
+        const int64_t from = __builtin_amdgcn_readfirstlane(row[class_of[c]]);
+        if (from == c) continue;
+        const T *const src = cost + from * per_row;
+        T *const dst = cost + c * per_row;
+#pragma unroll 4
+        for (int32_t i = lane; i < per_row; i += 64) dst[i] = src[i];
     }
 }
 
@@ -1426,6 +1447,15 @@ hipError_t launch_cc_cost(const CollTable &t, const echo_cc_table *tables, const
     const unsigned tiles = (unsigned)std::min<int64_t>((n_scen + 63) / 64, 65535);
     hipLaunchKernelGGL(k_cc_cost, dim3((unsigned)t.n, tiles), dim3(64), 0, stream, t, tables, scen, n_scen, cost,
                        status);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !t.row) return e;
+    // 8 workgroups per compute unit keep enough stores in flight
+    const dim3 grid((unsigned)std::min<int64_t>((t.n_out + 3) / 4, 2048));
+    if (n_scen % 2 == 0 && reinterpret_cast<uintptr_t>(cost) % sizeof(longlong2) == 0)
+        hipLaunchKernelGGL(k_cc_spread<longlong2>, grid, dim3(256), 0, stream, t.class_of, t.row, t.n_out, n_scen / 2,
+                           reinterpret_cast<longlong2 *>(cost));
+    else
+        hipLaunchKernelGGL(k_cc_spread<int64_t>, grid, dim3(256), 0, stream, t.class_of, t.row, t.n_out, n_scen, cost);
     return hipGetLastError();
 }
 
