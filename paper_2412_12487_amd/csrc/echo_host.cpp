@@ -589,8 +589,7 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
                 if (used[b0] >= kChannels) continue;                 // out of channels: meet globally
                 it = channel.emplace(std::make_pair(b0, cid[c]), used[b0]++).first;
             }
-            coll_aux[c] = kAuxLocal | ((uint32_t)it->second << 1) | ((uint32_t)(pos[c] & 1) << 4) |
-                          ((uint32_t)expected << 9);
+            coll_aux[c] = aux_local(it->second, pos[c] & 1) | ((uint32_t)expected << 9);
         }
         // a communicator is local for all its collectives or none: drop channels whose
         // communicator also has a collective that could not be met locally
@@ -696,6 +695,9 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
         std::vector<int32_t> latest(kStreams);
         std::vector<int64_t> busy(npair), total(npair);
         std::vector<int> slot(npair);
+        // comm ops that a segment of slot 0 has waited for: whatever waits for the latest op of
+        // slot 0 after that need not wait for them as well
+        std::vector<uint8_t> covered(n, 0);
         std::vector<int32_t> first_succ(n, -1);         // walk position of a comm op's first successor
         std::vector<std::pair<int32_t, int32_t>> sched; // (position, comm op) of the resolve items
         int32_t in_round = kBlock, segs_in_round = kDurs;   // of the walker's current round
@@ -734,6 +736,15 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
             it.dur = ccls[c];    // the cost class its finish reads
             it.nfar = link_prev[v];
             it.aux = coll_aux[d->op_coll[v]] | ((uint32_t)op_slot[v] << 5);
+            // right after its own launch at slot 0's value: one item
+            if ((it.aux & kAuxLocal) && in_round > 0 && !items.empty()) {
+                const WalkItem &l = items.back();
+                if (item_kind(l.meta) == ECHO_COMM && l.op == v && item_regmask(l.meta) == 1u && !(l.meta & kHasFar)) {
+                    it.meta |= kLaunch;
+                    items.back() = it;
+                    return;
+                }
+            }
             emit(it, false);
         };
         for (int64_t w = 0; w < W; ++w) {
@@ -805,15 +816,20 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
                     emit_resolve(u, slot[pair_of(u, r0)], fold);
                 }
                 unsigned mask = fold ? 1u : 0u;
+                bool on_slot0 = fold;                              // v waits for the latest op of slot 0
+                for (int32_t j = poff[v]; j < poff[v + 1]; ++j) on_slot0 = on_slot0 || preds[j] == latest[0];
                 const int64_t f0 = (int64_t)far.size();
                 for (int32_t j = poff[v]; j < poff[v + 1]; ++j) {
                     const int32_t u = preds[j];
                     if (u == link_prev[v]) continue;               // applied by the resolve item
+                    if (on_slot0 && u != latest[0] && covered[u]) continue;
                     if (fold && u != latest[0]) continue;          // folded into slot 0
                     const int su = slot[pair_of(u, r0)];
                     if (su >= 0 && latest[su] == u) mask |= 1u << su;
                     else far.push_back(u);
                 }
+                if (sv == 0)
+                    for (int32_t j = poff[v]; j < poff[v + 1]; ++j) covered[preds[j]] = 1;
                 if (sv >= 0) latest[sv] = tail_of(v);
                 WalkItem it{};
                 it.op = v;
@@ -1231,6 +1247,7 @@ int walk_chain(echo_graph g, const int64_t w[3], int64_t out[4]) {
     if (nc > 0 && (e = hipMemcpy(members.data(), g->dg.members, nc * sizeof(int32_t), hipMemcpyDeviceToHost)))
         return hip_fail(e, "member counts download");
     std::vector<Pt> cur(W), cmax(nc);
+    std::vector<uint8_t> launched(W, 0);      // the walker's current item is a resolve whose own launch is done
     std::vector<int32_t> arrived(nc, 0), wait_head(nc, -1), wait_next(W, -1);
     for (int64_t &x : off) x *= kBlock;
     std::vector<int64_t> pos(off.begin(), off.end() - (W > 0 ? 1 : 0));
@@ -1253,6 +1270,15 @@ int walk_chain(echo_graph g, const int64_t w[3], int64_t out[4]) {
                 it.coll = g->counted_coll[it.coll];
             }
             Pt p = cur[x];
+            if (kind == kResolve && (it.meta & kLaunch) && !launched[x]) {   // its launch first, as an item of its own
+                p.len += w[0];
+                p.items += 1;
+                cur[x] = p;
+                launched[x] = 1;
+                cmax[it.coll] = later(cmax[it.coll], p);
+                if (++arrived[it.coll] == members[it.coll])
+                    for (int32_t y = wait_head[it.coll]; y >= 0; y = wait_next[y]) runnable.push_back(y);
+            }
             if (kind == kResolve) {
                 if (arrived[it.coll] < members[it.coll]) {     // some member has not launched yet
                     wait_next[x] = wait_head[it.coll];
@@ -1269,6 +1295,7 @@ int walk_chain(echo_graph g, const int64_t w[3], int64_t out[4]) {
             p.items += kind == ECHO_COMM || kind == kResolve ? 1 : it.aux;
             cur[x] = p;
             ++done;
+            launched[x] = 0;
             if (kind == ECHO_COMM) {
                 cmax[it.coll] = later(cmax[it.coll], p);
                 if (++arrived[it.coll] == members[it.coll])

@@ -66,7 +66,8 @@ constexpr uint32_t kRecCand = 64u;       // on a first op: overlap detection loo
 struct WalkItem {
     int32_t op;         // op id: row of the [op][scenario] outputs (a segment: its first op)
     uint32_t meta;      // kind | slot << 2 | regmask << 8 | has far << 16 | noreg << 17
-                        // | linked << 18 | need finish << 19 | fold << 20 | empty << 31
+                        // | linked << 18 | need finish << 19 | fold << 20 | launch << 21
+                        // | empty << 31
     int32_t far_off;    // predecessors read back from memory: far[far_off .. +nfar)
     int32_t coll;       // segment: its last op.  Comm op: its collective; of a collective met
                         // by counting arrivals in device memory (neither in LDS nor through
@@ -91,6 +92,10 @@ constexpr uint32_t kLinked = 1u << 18;
 constexpr uint32_t kNeedF = 1u << 19;
 // Resolve item: after writing the comm op's finish, raise slot 0 to it.
 constexpr uint32_t kFold = 1u << 20;
+// Resolve item of a collective met in LDS that also is the comm op's launch, at slot 0's
+// value: the launch item right before it, waiting for nothing but the latest op of slot 0,
+// left out (a blocking all-reduce after a segment).
+constexpr uint32_t kLaunch = 1u << 21;
 // Padding at the end of a round.
 constexpr uint32_t kEmpty = 1u << 31;
 // Item kind (besides compute/comm/memcpy) that finishes a comm op:
@@ -117,7 +122,7 @@ constexpr int kDurs = 8;
 constexpr int kChannels = 8;          // LDS barrier channels per block
 constexpr int kClassSlots = 8;        // LDS cost classes per block
 constexpr uint32_t kNoSlot = 15;
-// Comm item aux word: bit 0 local barrier | channel << 1 | slot parity << 4 |
+// Comm item aux word: bit 0 local barrier | slot parity << 1 | channel << 2 |
 // class slot << 5 (kNoSlot: read the class's cost from global memory) | expected count << 9.
 constexpr uint32_t kAuxLocal = 1u;
 constexpr int kExpectedBits = 23;
@@ -126,12 +131,14 @@ constexpr int kExpectedBits = 23;
 // into its own slot (cleared to -1 before every pass), and a resolve item reads all
 // its collective's slots -- a value of -1 means "not yet launched".  The launch item
 // carries its slot in `dur`, the resolve item the collective's first slot in
-// `far_off`; aux bit 1 marks the mode and the expected-count field holds the member
+// `far_off`; aux bit 1 (without bit 0) marks the mode and the expected-count field holds the member
 // count.  Larger collectives count their arrivals and keep a per-scenario maximum.
 constexpr uint32_t kAuxSlots = 2u;
 constexpr int kSlotMembers = 8;
-__host__ __device__ inline int aux_channel(uint32_t x) { return int((x >> 1) & 7u); }
-__host__ __device__ inline int aux_parity(uint32_t x) { return int((x >> 4) & 1u); }
+__host__ __device__ inline uint32_t aux_local(int channel, int parity) {
+    return kAuxLocal | ((uint32_t)parity << 1) | ((uint32_t)channel << 2);
+}
+__host__ __device__ inline int aux_barrier(uint32_t x) { return int((x >> 1) & 15u); }   // channel * 2 + parity
 __host__ __device__ inline int aux_slot(uint32_t x) { return int((x >> 5) & 15u); }
 __host__ __device__ inline unsigned aux_expected(uint32_t x) { return x >> 9; }
 

@@ -330,6 +330,10 @@ __device__ int64_t wait_slots(const int64_t *p, unsigned n, int64_t ns, unsigned
 // segment is written once per pass and read again only by the same wavefront
 // (a far predecessor) or by the next kernel.
 __device__ __forceinline__ void put(int64_t *p, int64_t v) { __builtin_nontemporal_store(v, p); }
+typedef __attribute__((address_space(1))) int64_t GlobalI64;     // global, not flat, when made from an integer
+// The sweep's stores go through the cache: overlap detection and k_expand read the rows again,
+// and a later poll of the same wavefront waits for them.
+__device__ __forceinline__ void put(GlobalI64 *p, int64_t v) { *p = v; }
 
 // Duration d inflated by the slowdown factor of overlap mask m (Sec. 6): the largest entry
 // of the op's class row x over the collective types in m; an empty mask keeps factor 65536,
@@ -404,10 +408,11 @@ __device__ __forceinline__ Lane make_lane(const echo_scenario *scen, int32_t n_s
 template <int IN, bool FINAL, bool DIGEST>
 __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per_eu(4))) void k_walk(WalkArgs a) {
     constexpr bool REFINED = IN != kInNone;
-    __shared__ unsigned long long lbar[kChannels][2][kLanes];   // per channel and slot: latest launch per lane
-    __shared__ unsigned lcnt[kChannels][2];                      // per channel and slot: members arrived
-    __shared__ int64_t ccost[kClassSlots][kLanes];               // staged class costs of this tile
+    __shared__ unsigned long long lbar[kChannels * 2][kLanes];   // per channel and slot: latest launch per lane
+    __shared__ unsigned lcnt[kChannels * 2];                      // per channel and slot: members arrived
+    __shared__ int64_t ccost[kClassSlots][kLanes];                // staged class costs of this tile
     __shared__ int64_t slotmem[kBlockWalkers * kStreams * kLanes];   // slots 1..7 of every wave (slot 0 stays in a register)
+    __shared__ int64_t durmem[kBlockWalkers * kDurs * kLanes];       // durations of every wave's round
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform within a wavefront
@@ -421,8 +426,8 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
     const int64_t ns = a.n_scen;
 
     // block set-up: clear the barrier channels, stage the block's class costs
-    for (int i = threadIdx.x; i < kChannels * 2 * kLanes; i += blockDim.x) (&lbar[0][0][0])[i] = 0;
-    if (threadIdx.x < kChannels * 2) (&lcnt[0][0])[threadIdx.x] = 0;
+    for (int i = threadIdx.x; i < kChannels * 2 * kLanes; i += blockDim.x) (&lbar[0][0])[i] = 0;
+    if (threadIdx.x < kChannels * 2) lcnt[threadIdx.x] = 0;
     if (wave < kClassSlots) {
         const int32_t cls = a.block_class[(int64_t)blk * kClassSlots + wave];
         ccost[wave][lane] = cls >= 0 ? a.class_cost[(int64_t)cls * ns + sigma] : 0;
@@ -461,6 +466,18 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
     auto load_items = [&](int64_t r) -> int4 {
         return r < end ? items4[2 * kBlock * r] : make_int4(0, (int)kEmpty, 0, 0);
     };
+    // Rows are addressed by the lanes: lane j computes the addresses of item j's rows once per
+    // round, and a row is then two lane reads and a store with the lane's column as offset
+    // (five instructions when computed per store; an item costs its instructions here).
+    const uint32_t coff = (uint32_t)col * 8u;
+    const uint64_t sadr = reinterpret_cast<uint64_t>(sbase), fadr = reinterpret_cast<uint64_t>(fbase);
+    const uint64_t row_bytes = (uint64_t)a.n_scen * 8u;
+    auto row_at = [&](uint64_t base, int32_t row) -> uint64_t { return base + (uint64_t)(uint32_t)row * row_bytes; };
+    auto row_of = [&](uint64_t rows, int j) -> GlobalI64 * {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)rows, j);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(rows >> 32), j);
+        return reinterpret_cast<GlobalI64 *>((((uint64_t)hi << 32) | lo) + coff);
+    };
     // Segment durations (see WalkArgs): lane q < kDurs holds the rows of the round's segment q
     // (unused ones name op 0), fetched a round before the durations they name.
     const bool load_d = REFINED || ln.any_jitter;
@@ -468,18 +485,15 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
         return load_d && r < end ? reinterpret_cast<const int2 *>(a.rows)[r * kDurs + (lane & (kDurs - 1))]
                                  : make_int2(0, 0);
     };
-    typedef int64_t Durs __attribute__((ext_vector_type(kDurs)));
+    int64_t *const dmem = durmem + wave * kDurs * kLanes + lane;
     int64_t in_f[kDurs] = {}, in_s[kDurs] = {};
     auto load_durs = [&](int2 rows) {
         if (!load_d) return;
+        const uint64_t fr = row_at(fadr, rows.y), sr = row_at(sadr, rows.x);
 #pragma unroll
         for (int q = 0; q < kDurs; ++q) {
-            const int64_t l = __builtin_amdgcn_readlane(rows.y, q);
-            in_f[q] = (fbase + l * ns)[col];
-            if (REFINED) {
-                const int64_t f = __builtin_amdgcn_readlane(rows.x, q);
-                in_s[q] = (sbase + f * ns)[col];
-            }
+            in_f[q] = *row_of(fr, q);
+            if (REFINED) in_s[q] = *row_of(sr, q);
         }
     };
     int4 nxt = load_items(beg);
@@ -493,21 +507,22 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
         // and durations are fetched, and the rows of the one after.
         const int4 cur = nxt;
         __builtin_amdgcn_s_waitcnt(kWaitVm0);
-        Durs dur;
+        if (load_d) {
 #pragma unroll
-        for (int q = 0; q < kDurs; ++q) dur[q] = REFINED ? in_f[q] - in_s[q] : in_f[q];
+            for (int q = 0; q < kDurs; ++q) dmem[q * kLanes] = REFINED ? in_f[q] - in_s[q] : in_f[q];
+        }
         nxt = load_items(r + 1);
         load_durs(rows);
         rows = load_rows(r + 2);
         const int nb = __builtin_popcountll(__builtin_amdgcn_read_exec() &
                                             __ballot(lane < kBlock && !((uint32_t)cur.y & kEmpty)));
-        // the round's segments (the durations' index is a count of bits: kept in scalar registers)
+        // the round's segments (a duration's index is a count of bits)
         const uint32_t seg_bits = (uint32_t)(__builtin_amdgcn_read_exec() &
                                              __ballot(lane < kBlock && ((uint32_t)cur.y & (kEmpty | 1u)) == 0));
+        const uint64_t srow = row_at(sadr, cur.x);                                  // start: the (first) op
+        const uint64_t frow = row_at(fadr, ((uint32_t)cur.y & 1u) ? cur.x : cur.w);  // finish: the (last) op
         for (int j = 0; j < nb; ++j) {
-            const int32_t op = __builtin_amdgcn_readlane(cur.x, j);
             const uint32_t meta = (uint32_t)__builtin_amdgcn_readlane(cur.y, j);
-            const int32_t coll = __builtin_amdgcn_readlane(cur.w, j);       // a segment's last op
             const int kind = item_kind(meta);
             const int sq = (meta & kNoReg) ? kStreams : item_stream(meta);  // kStreams: no slot
             const bool storef = keep || (meta & kNeedF);
@@ -515,14 +530,32 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
                 // a comm op's barrier, due right before its first successor: its finish is the
                 // latest member launch plus the collective's cost
                 const uint32_t aux = (uint32_t)__builtin_amdgcn_readlane(cur.w, j + 32);
+                // The cost: from the workgroup's LDS slot, read first on every path; a class without
+                // a slot reads device memory and waits for that load inside its own branch, so
+                // the common path carries no wait on vector memory (which on this target would also
+                // wait for every timeline store still in flight).  Distinct load kinds keep the two
+                // reads from merging into one flat load.
+                const int sl = aux_slot(aux);
+                int64_t t = ccost[sl & (kClassSlots - 1)][lane];
+                int64_t own = 0;                             // linked: this member's published launch
                 uint64_t b = 0;
                 if (aux & kAuxLocal) {
-                    const int ch = aux_channel(aux), par = aux_parity(aux);
+                    const int ch = aux_barrier(aux);
+                    if (meta & kLaunch) {
+                        if (keep) put(row_of(srow, j), lf0);
+                        __hip_atomic_fetch_max(&lbar[ch][lane], (unsigned long long)lf0, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+                        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+                        if (lane == 0)
+                            __hip_atomic_fetch_add(&lcnt[ch], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
                     if (!dead && !__builtin_amdgcn_readfirstlane(
-                                     wait_local(&lcnt[ch][par], aux_expected(aux), a.status, a.spin_limit)))
+                                     wait_local(&lcnt[ch], aux_expected(aux), a.status, a.spin_limit)))
                         dead = true;
-                    b = lbar[ch][par][lane];
+                    b = lbar[ch][lane];
                 } else if (aux & kAuxSlots) {
+                    // the own launch is fetched with the members' (one round trip)
+                    if (keep && (meta & kLinked)) own = *row_of(srow, j);
                     bool ok = true;
                     if (!dead) {
                         const int64_t *p = a.slots + (int64_t)__builtin_amdgcn_readlane(cur.z, j) * ns + sigma;
@@ -533,6 +566,8 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
                     __builtin_amdgcn_s_waitcnt(kWaitVm0);    // settled on this path, not at the join
                     if (!__builtin_amdgcn_readfirstlane(ok)) dead = true;
                 } else {
+                    const int32_t coll = __builtin_amdgcn_readlane(cur.w, j);
+                    if (keep && (meta & kLinked)) own = *row_of(srow, j);
                     if (!dead && !__builtin_amdgcn_readfirstlane(wait_arrivals(tile_count + (int64_t)coll * a.n_tiles,
                                                                                (unsigned)a.c_N[coll], a.status,
                                                                                a.spin_limit)))
@@ -543,13 +578,6 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
                     __builtin_amdgcn_s_waitcnt(kWaitVm0);    // settled on this path, not at the join
                     b = mirror ? (uint64_t)__shfl((long long)b, col) : b;
                 }
-                const int sl = aux_slot(aux);
-                // The cost: from the workgroup's LDS slot, read first on every path; a class without
-                // a slot then reads device memory and waits for that load inside its own branch, so
-                // the common path carries no wait on vector memory (which on this target would also
-                // wait for every timeline store still in flight).  Distinct load kinds keep the two
-                // reads from merging into one flat load.
-                int64_t t = ccost[sl & (kClassSlots - 1)][lane];
                 if (sl >= kClassSlots) {
                     const int64_t cls = __builtin_amdgcn_readlane(cur.x, j + 32);
                     t = __hip_atomic_load(a.class_cost + cls * ns + sigma, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -558,28 +586,30 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
                 if (meta & kLinked) {
                     // the op it is linked to finished at p: the barrier, and this member's own
                     // launch, are no earlier
-                    int64_t own = keep ? (sbase + (int64_t)op * ns)[col] : 0, p;
-                    if (sq < kStreams) {
+                    int64_t p;
+                    if (sq == 0) {
+                        p = lf0;
+                    } else if (sq < kStreams) {
                         p = smem[sq * kLanes];
                     } else {
                         p = (fbase + (int64_t)__builtin_amdgcn_readlane(cur.z, j + 32) * ns)[col];
+                        __builtin_amdgcn_s_waitcnt(kWaitVm0);    // settled on this path, not at the join
                     }
-                    __builtin_amdgcn_s_waitcnt(kWaitVm0);    // settled on this path, not at the join
-                    if (sq == 0) p = lf0;
                     b = (uint64_t)p > b ? (uint64_t)p : b;
                     own = p > own ? p : own;
-                    if (keep) put(sbase + (int64_t)op * ns + col, own);
+                    if (keep) put(row_of(srow, j), own);
                 }
                 const int64_t f = (int64_t)b + t;
                 hi_or |= (uint32_t)((uint64_t)f >> 32);
-                if (storef) put(fbase + (int64_t)op * ns + col, f);
+                if (storef) put(row_of(frow, j), f);
                 if (DIGEST) {
-                    const int64_t s = (sbase + (int64_t)op * ns)[col];
+                    const int32_t op = __builtin_amdgcn_readlane(cur.x, j);
+                    const int64_t s = *row_of(srow, j);
                     dig += mix64(mix64((uint64_t)op ^ (uint64_t)s) ^ (uint64_t)f);
                 }
-                xmax = f > xmax ? f : xmax;
                 if (sq == 0) lf0 = f;
                 else if (sq < kStreams) smem[sq * kLanes] = f;
+                else xmax = f > xmax ? f : xmax;
                 if (meta & kFold) lf0 = f > lf0 ? f : lf0;
                 continue;
             }
@@ -600,17 +630,17 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
                 }
                 __builtin_amdgcn_s_waitcnt(kWaitVm0);        // settled on this path, not at the join
             }
-            if (keep) put(sbase + (int64_t)op * ns + col, ready);
+            if (keep) put(row_of(srow, j), ready);
             if (kind == ECHO_COMM) {
                 // launch: publish this member's launch time, then count the arrival
                 const uint32_t aux = (uint32_t)__builtin_amdgcn_readlane(cur.w, j + 32);
                 if (aux & kAuxLocal) {
-                    const int ch = aux_channel(aux), par = aux_parity(aux);
-                    __hip_atomic_fetch_max(&lbar[ch][par][lane], (unsigned long long)ready, __ATOMIC_RELAXED,
+                    const int ch = aux_barrier(aux);
+                    __hip_atomic_fetch_max(&lbar[ch][lane], (unsigned long long)ready, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_WORKGROUP);
                     __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
                     if (lane == 0)
-                        __hip_atomic_fetch_add(&lcnt[ch][par], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        __hip_atomic_fetch_add(&lcnt[ch], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 } else if (aux & kAuxSlots) {
                     // this member's slot (its index is in the item's duration field): one store,
                     // no wait -- the value is its own arrival flag
@@ -620,6 +650,7 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
                         __hip_atomic_store(a.slots + slot * ns + sigma, ready, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
                 } else {
+                    const int32_t coll = __builtin_amdgcn_readlane(cur.w, j);
                     if (active)
                         __hip_atomic_fetch_max(a.arrive + (int64_t)coll * ns + sigma, (unsigned long long)ready,
                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -631,17 +662,17 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
             } else {
                 int64_t d;
                 if (load_d) {
-                    d = dur[__builtin_amdgcn_readfirstlane(__builtin_popcount(seg_bits & ((1u << j) - 1)))];
+                    d = dmem[__builtin_popcount(seg_bits & ((1u << j) - 1)) * kLanes];
                 } else {
                     d = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(cur.y, j + 32) << 32) |
                                   (uint32_t)__builtin_amdgcn_readlane(cur.x, j + 32));
                 }
                 const int64_t f = ready + d;
                 hi_or |= (uint32_t)((uint64_t)f >> 32);
-                if (storef) put(fbase + (int64_t)coll * ns + col, f);
-                xmax = f > xmax ? f : xmax;
+                if (storef) put(row_of(frow, j), f);
                 if (sq == 0) lf0 = f;
                 else if (sq < kStreams) smem[sq * kLanes] = f;
+                else xmax = f > xmax ? f : xmax;
             }
         }
     }
