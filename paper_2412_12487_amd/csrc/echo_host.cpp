@@ -257,7 +257,7 @@ void overlap_ranges(const echo_graph_desc *d, const std::vector<int32_t> &poff, 
             }
             const int64_t lo = done[st][q];
             if (lo < hi) {
-                ranges->push_back(CommRange{(int32_t)lo, (int32_t)hi, cl[hi - 1], 0});
+                ranges->push_back(CommRange{(int32_t)lo, (int32_t)hi, cl[hi - 1], (int32_t)osegs->size()});
                 ++os.ncand;
             }
         }

@@ -166,10 +166,12 @@ static_assert(sizeof(OverlapSeg) == 32, "overlap segment must stay 32 bytes");
 struct CommRange {
     int32_t lo, hi;         // positions in the comm lists
     int32_t last_op;        // the comm op at hi - 1
-    int32_t pad;
+    int32_t seg;            // its overlap segment
 };
 static_assert(sizeof(CommRange) == 16, "comm range must stay 16 bytes");
-constexpr int kOverlapGroup = 8;    // segments a wavefront of overlap detection takes at a time
+// segments a wavefront of overlap detection takes at a time (their ranges, at most eight
+// each, fit the lanes)
+constexpr int kOverlapGroup = 8;
 
 // First and last op of a segment: the rows its start and finish live in.
 struct RowPair {

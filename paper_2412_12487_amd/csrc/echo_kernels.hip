@@ -326,14 +326,14 @@ __device__ int64_t wait_slots(const int64_t *p, unsigned n, int64_t ns, unsigned
     return 0;
 }
 
-// Timeline stores stream through the caches (non-temporal): each (op, tile) row
-// segment is written once per pass and read again only by the same wavefront
-// (a far predecessor) or by the next kernel.
-__device__ __forceinline__ void put(int64_t *p, int64_t v) { __builtin_nontemporal_store(v, p); }
 typedef __attribute__((address_space(1))) int64_t GlobalI64;     // global, not flat, when made from an integer
 // The sweep's stores go through the cache: overlap detection and k_expand read the rows again,
 // and a later poll of the same wavefront waits for them.
 __device__ __forceinline__ void put(GlobalI64 *p, int64_t v) { *p = v; }
+// The other timeline stores are read by nothing here.
+__device__ __forceinline__ void put_stream(GlobalI64 *p, int64_t v) {
+    __builtin_nontemporal_store(v, p);
+}
 
 // Duration d inflated by the slowdown factor of overlap mask m (Sec. 6): the largest entry
 // of the op's class row x over the collective types in m; an empty mask keeps factor 65536,
@@ -712,7 +712,11 @@ WalkKernel walk_kernel(int in, bool final_pass, bool digest) {
 // one tile.  Consecutive wavefronts take the tiles of one chunk, so that a row is written
 // whole by one workgroup at about one time, and each keeps its tile's scenario knobs.
 constexpr int kRecWaves = 4;             // wavefronts per workgroup
-constexpr int64_t kRecParts = 8192;      // wavefronts of a launch, unless there are more tiles
+// Wavefronts of a launch, unless there are more tiles: eight rounds of what the chip holds, so
+// that the last round is short against the rest (on the 1024-rank workload k_expand takes
+// 12.1 ms with one round, 11.8 with eight, 11.7 with a wavefront per chunk, which makes a
+// k_sum that has nothing to do eight times longer).
+constexpr int64_t kRecParts = 65536;
 
 __device__ __forceinline__ int4 load_chunk(const WalkArgs &a, int64_t chunk, int lane, int *n) {
     *n = 0;
@@ -769,7 +773,10 @@ __global__ __launch_bounds__(kRecWaves * 64) void k_sum(WalkArgs a, int64_t part
 // After the last pass: the start and finish of every op that the sweep has not written (all
 // but each segment's first start and last finish), and with DIGEST the segments' share of
 // the digest.  IN: what flagged segments carry per op -- nothing (no refinement), overlap
-// masks, or extra times.  Bound by the timeline stores.
+// masks, or extra times.  Bound by the timeline stores (57 GB in 11.8 ms on the
+// 1024-rank workload; a store-only probe of its pattern takes 10.2 at 5.6 TB/s).  An op's finish is the
+// next op's start, so a step of the loop is one draw and two stores, the last op of a segment
+// takes neither, and the lanes compute the chunk's row addresses once.
 template <int IN, bool DIGEST>
 __global__ __launch_bounds__(kRecWaves * 64) void k_expand(WalkArgs a, int64_t parts) {
     const int lane = threadIdx.x & 63;
@@ -779,8 +786,15 @@ __global__ __launch_bounds__(kRecWaves * 64) void k_expand(WalkArgs a, int64_t p
     if (part >= parts) return;
     const Lane ln = make_lane(a.scen, a.n_scen, tile, lane);
     const int64_t ns = a.n_scen;
-    int64_t *const sbase = a.start + (int64_t)tile * kLanes + ln.col;
-    int64_t *const fbase = a.finish + (int64_t)tile * kLanes + ln.col;
+    const uint64_t sadr = reinterpret_cast<uint64_t>(a.start + (int64_t)tile * kLanes);
+    const uint64_t fadr = reinterpret_cast<uint64_t>(a.finish + (int64_t)tile * kLanes);
+    const uint32_t coff = (uint32_t)ln.col * 8u;
+    const uint64_t row_bytes = (uint64_t)ns * 8u;
+    auto row_of = [&](uint64_t rows, int j) -> GlobalI64 * {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)rows, j);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(rows >> 32), j);
+        return reinterpret_cast<GlobalI64 *>((((uint64_t)hi << 32) | lo) + coff);
+    };
     const uint4 *const slow = reinterpret_cast<const uint4 *>(&a.scen[ln.sigma].slowdown_q16[0][0]);
     uint64_t dig = 0;
     typedef int64_t Starts __attribute__((ext_vector_type(8)));
@@ -790,6 +804,7 @@ __global__ __launch_bounds__(kRecWaves * 64) void k_expand(WalkArgs a, int64_t p
     for (int64_t chunk = part; chunk < a.n_chunks; chunk += parts) {
         const int4 cur = nxt;
         const int n = nn;
+        const uint64_t frow = fadr + (uint64_t)(uint32_t)cur.x * row_bytes, srow = sadr + (uint64_t)(uint32_t)cur.x * row_bytes;
         const uint64_t first_bits = __builtin_amdgcn_read_exec() & __ballot((uint32_t)cur.y & kRecFirst);
         const uint64_t last_bits = __builtin_amdgcn_read_exec() & __ballot((uint32_t)cur.y & kRecLast);
         const bool small = __builtin_amdgcn_readfirstlane((__builtin_amdgcn_read_exec() & __ballot(cur.w != 0)) == 0);
@@ -806,37 +821,11 @@ __global__ __launch_bounds__(kRecWaves * 64) void k_expand(WalkArgs a, int64_t p
         uint64_t todo = first_bits;
         Starts s8 = 0;
         int is = 8, ic = 0;
-        int64_t s = 0;
-        Ins x8 = 0;
-        bool flagged = false;
-        int j0 = 0;
-        auto body = [&](auto jit, auto is_small) {
-            for (int j = 0; j < n; ++j) {
-                const int32_t op = __builtin_amdgcn_readlane(cur.x, j);
+        auto steps = [&](auto jit, auto is_small, bool flagged, int64_t s, int j0, int end) {
+            Ins x8 = 0;
+            for (int j = j0; j < end; ++j) {
+                const int32_t op = decltype(jit)::value || DIGEST ? __builtin_amdgcn_readlane(cur.x, j) : 0;
                 const uint32_t dlo = (uint32_t)__builtin_amdgcn_readlane(cur.z, j);
-                const bool first = (first_bits >> j) & 1u, last = (last_bits >> j) & 1u;
-                if (first) {
-                    if (is == 8) {
-#pragma unroll
-                        for (int q = 0; q < 8; ++q)
-                            if (todo) {
-                                const int64_t v = __builtin_amdgcn_readlane(cur.x, __builtin_ctzll(todo));
-                                todo &= todo - 1;
-                                s8[q] = sbase[v * ns];
-                            }
-                        is = 0;
-                    }
-                    s = s8[is];
-                    ++is;
-                    if (IN != kInNone) {
-                        flagged = false;
-                        if ((cand_bits >> j) & 1u) {
-                            flagged = (flag_bits >> ic) & 1u;
-                            ++ic;
-                        }
-                        j0 = j;
-                    }
-                }
                 int64_t d;
                 if (decltype(is_small)::value) {
                     d = decltype(jit)::value ? jittered32(dlo, op, ln.jt) : (int64_t)dlo;
@@ -851,7 +840,7 @@ __global__ __launch_bounds__(kRecWaves * 64) void k_expand(WalkArgs a, int64_t p
                         // the segment's next eight masks (extra times), in one round trip
 #pragma unroll
                         for (int q = 0; q < 8; ++q) {
-                            if (j + q >= n) continue;
+                            if (j + q >= end) continue;
                             const int64_t at = (rec0 + j + q) * a.mstride + (int64_t)tile * kLanes + ln.col;
                             x8[q] = IN == kInExtFlags ? a.ext[at] : (uint32_t)a.tmask[at];
                         }
@@ -868,20 +857,44 @@ __global__ __launch_bounds__(kRecWaves * 64) void k_expand(WalkArgs a, int64_t p
                     }
                 }
                 const int64_t f = s + d;
-                if (a.timelines) {
-                    if (!first) put(sbase + (int64_t)op * ns, s);
-                    if (!last) put(fbase + (int64_t)op * ns, f);
-                }
                 if (DIGEST) dig += mix64(mix64((uint64_t)op ^ (uint64_t)s) ^ (uint64_t)f);
+                if (!DIGEST || a.timelines) {
+                    if (!DIGEST || j + 1 < end) {
+                        put_stream(row_of(frow, j), f);
+                        put_stream(row_of(srow, j + 1), f);
+                    }
+                }
                 s = f;
             }
         };
         nxt = load_chunk(a, chunk + parts, lane, &nn);
-        if (ln.any_jitter) {
-            if (small) body(std::true_type{}, std::true_type{});
-            else body(std::true_type{}, std::false_type{});
-        } else {
-            body(std::false_type{}, std::false_type{});
+        for (int j = 0; j < n;) {
+            // a segment: its ops but the last (with DIGEST the last too, without stores)
+            const int end = j + __builtin_ctzll(last_bits >> j);
+            if (is == 8) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    if (todo) {
+                        s8[q] = *row_of(srow, __builtin_ctzll(todo));
+                        todo &= todo - 1;
+                    }
+                is = 0;
+            }
+            const int64_t s = s8[is];
+            ++is;
+            bool flagged = false;
+            if (IN != kInNone && ((cand_bits >> j) & 1u)) {
+                flagged = (flag_bits >> ic) & 1u;
+                ++ic;
+            }
+            const int stop = DIGEST ? end + 1 : end;
+            if (ln.any_jitter) {
+                if (small) steps(std::true_type{}, std::true_type{}, flagged, s, j, stop);
+                else steps(std::true_type{}, std::false_type{}, flagged, s, j, stop);
+            } else {
+                steps(std::false_type{}, std::false_type{}, flagged, s, j, stop);
+            }
+            j = end + 1;
         }
     }
     if (DIGEST && ln.active)
@@ -1119,6 +1132,7 @@ __device__ uint32_t forest_factor_compact(const OverlapArgs &a, uint32_t m, cons
 // workgroup's wavefronts share one copy of the nodes).
 // NC: room for this many comm ranges per segment (the cursor and merge state scale with it).
 constexpr int kOverlapWaves = 4;         // wavefronts per workgroup
+constexpr int kXcds = 8;
 template <bool PRORATE, bool DETECT, int FOREST, int NC>
 __global__ __launch_bounds__(64 * kOverlapWaves) void k_overlap(OverlapArgs a, int64_t parts) {
     constexpr bool EXT = PRORATE || FOREST != 0;  // output: extra time per op instead of a mask
@@ -1131,9 +1145,12 @@ __global__ __launch_bounds__(64 * kOverlapWaves) void k_overlap(OverlapArgs a, i
         return;                                  // every scenario is at its fixed point
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t unit = (int64_t)blockIdx.x * W + wave;
+    // Workgroup b runs on XCD b % kXcds: each XCD takes a contiguous share of the groups, so
+    // that the comm rows that a rank's segments have in common stay in one L2 (1024-rank workload 3.7 -> 3.4 ms, 96 ranks 0.49 -> 0.41).
+    const int xcd = (int)(blockIdx.x % kXcds);
+    const int64_t unit = (int64_t)(blockIdx.x / kXcds) * W + wave;
     const int32_t tile = (int32_t)(unit % a.n_tiles);
-    const int64_t part = unit / a.n_tiles;
+    const int64_t part = unit / a.n_tiles;       // of this XCD's parts
     if (FOREST == 2) {
         // the nodes, then the roots of the trees
         for (int i = threadIdx.x; i < a.fx.n_words; i += 64 * W) fwords[i] = a.fx.words[i];
@@ -1176,69 +1193,153 @@ __global__ __launch_bounds__(64 * kOverlapWaves) void k_overlap(OverlapArgs a, i
     }
     typedef uint32_t Olds __attribute__((ext_vector_type(8)));
 
+    // Rows are addressed by the lanes (as in k_walk): lane j computes the address of item j's
+    // row, and a row is then two lane reads and a load.
+    const uint64_t sadr = reinterpret_cast<uint64_t>(a.start + (int64_t)tile * kLanes);
+    const uint64_t fadr = reinterpret_cast<uint64_t>(a.finish + (int64_t)tile * kLanes);
+    const uint32_t coff = (uint32_t)col * 8u;
+    const uint64_t row_bytes = (uint64_t)ns * 8u;
+    auto row_of = [&](uint64_t rows, int j) -> GlobalI64 * {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)rows, j);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(rows >> 32), j);
+        return reinterpret_cast<GlobalI64 *>((((uint64_t)hi << 32) | lo) + coff);
+    };
+    typedef int64_t Starts __attribute__((ext_vector_type(kOverlapGroup)));
     const int4 *const osegs4 = reinterpret_cast<const int4 *>(a.osegs);
     const int64_t groups = (a.n_osegs + kOverlapGroup - 1) / kOverlapGroup;
-    for (int64_t grp = part; grp < groups; grp += parts) {
+    const int64_t grp0 = groups * xcd / kXcds + part, grp1 = groups * (xcd + 1) / kXcds;
+    // lane 2q holds the first half of segment q of a group, lane 2q + 1 the second
+    auto load_group = [&](int64_t grp) -> int4 {
+        const int64_t at = 2 * grp * kOverlapGroup + lane;
+        return grp < grp1 && lane < 2 * kOverlapGroup && at < 2 * a.n_osegs ? osegs4[at] : make_int4(0, 0, 0, 0);
+    };
+    int4 nxt = load_group(grp0);
+    for (int64_t grp = grp0; grp < grp1; grp += parts) {
+        const int4 os = nxt;
         const int64_t o0 = grp * kOverlapGroup;
         const int no = a.n_osegs - o0 < kOverlapGroup ? (int)(a.n_osegs - o0) : kOverlapGroup;
-        // lane 2q holds the first half of segment q, lane 2q + 1 the second
-        const int4 os = lane < 2 * no ? osegs4[2 * o0 + lane] : make_int4(0, 0, 0, 0);
+        // the group's ranges: lane t holds range t, with its segment's place in the group
+        const int32_t r0 = __builtin_amdgcn_readlane(os.x, 1);
+        const int nr_all = __builtin_amdgcn_readlane(os.x, 2 * no - 1) + __builtin_amdgcn_readlane(os.y, 2 * no - 1) - r0;
+        const int4 rg = lane < nr_all ? reinterpret_cast<const int4 *>(a.ranges)[r0 + lane] : make_int4(0, 0, 0, 0);
+        nxt = load_group(grp + parts);
         uint8_t *const flag = a.xflag + (o0 + lane) * a.n_tiles + tile;      // of segment `lane`
         // segments inflated in the previous pass
         uint32_t was = 0;
         if (a.prev_refined) was = (uint32_t)__ballot(lane < no && *flag != 0);
         uint32_t now = 0;
+        // the segments' starts and, eight at a time, the finishes of the ranges' last comm ops,
+        // fetched together: bit t of `late` is set when range t's comes after its segment's start
+        const uint64_t srow = sadr + (uint64_t)(uint32_t)os.z * row_bytes;
+        const uint64_t lrow = fadr + (uint64_t)(uint32_t)rg.z * row_bytes;
+        Starts s8;
+#pragma unroll
+        for (int q = 0; q < kOverlapGroup; ++q) s8[q] = *row_of(srow, q < no ? 2 * q : 0);
+        uint64_t late = 0;
+        for (int t0 = 0; t0 < nr_all; t0 += 8) {
+            int64_t fin[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) fin[i] = *row_of(lrow, t0 + i < nr_all ? t0 + i : t0);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int t = t0 + i < nr_all ? t0 + i : t0;
+                const int64_t s = s8[__builtin_amdgcn_readlane(rg.w, t) & (kOverlapGroup - 1)];
+                late |= (uint64_t)(fin[i] > s ? 1u : 0u) << t;
+            }
+        }
         for (int q = 0; q < no; ++q) {
-            const int32_t first = __builtin_amdgcn_readlane(os.z, 2 * q), last = __builtin_amdgcn_readlane(os.w, 2 * q);
-            const int32_t cand0 = __builtin_amdgcn_readlane(os.x, 2 * q + 1);
+            const int t0 = __builtin_amdgcn_readlane(os.x, 2 * q + 1) - r0;   // its ranges t0 .. t0 + ncand
             const int ncand = __builtin_amdgcn_readlane(os.y, 2 * q + 1);
             const bool was_on = (was >> q) & 1u;
-            const int64_t s = sbase[(int64_t)first * ns];
-            bool late[NC];                       // the range's last comm op finishes after s
-            bool any = false;
-#pragma unroll
-            for (int k = 0; k < NC; ++k) {
-                late[k] = false;
-                if (k < ncand) {
-                    const int64_t c = __builtin_amdgcn_readfirstlane(a.ranges[cand0 + k].last_op);
-                    late[k] = fbase[c * ns] > s;
-                    any = any || late[k];
-                }
-            }
-            if (!was_on && !__builtin_amdgcn_readfirstlane(__ballot(any) != 0)) continue;
+            const uint32_t late_q = (uint32_t)(late >> t0) & ((1u << ncand) - 1u);
+            if (!was_on && !__builtin_amdgcn_readfirstlane(__ballot(late_q != 0) != 0)) continue;
 
             // some lane's segment may overlap: cursors at the first comm op ending after s
+            const int64_t s = s8[q];
+            const int32_t last = __builtin_amdgcn_readlane(os.w, 2 * q);
             const int32_t rec0 = __builtin_amdgcn_readlane(os.x, 2 * q);
             const int nr = __builtin_amdgcn_readlane(os.y, 2 * q);
             const int4 cur = lane < nr ? reinterpret_cast<const int4 *>(a.recs)[rec0 + lane] : make_int4(0, 0, 0, 0);
-            int32_t p[NC], hi[NC];
+            // Per range a cursor: the comm op at list position p, its interval and type, and the id
+            // of the one after it (read ahead, so that a move waits for one load, not two).
+            int32_t p[NC], hi[NC], cn[NC];
+            uint32_t ty[NC];
             int64_t cs[NC], cf[NC];
             int64_t cmin = kInf;                 // earliest start among the cursors: an op ending by then overlaps nothing
+            auto next_id = [&](int k) { cn[k] = a.cl[p[k] + 1 < hi[k] ? p[k] + 1 : hi[k] - 1]; };
+            {
+                // usually the range's last comm op is the only one that ends after s (a send still
+                // waiting for its receiver), or all of them do (the buckets behind the one an
+                // optimizer op waited for): the last, the one before it and the first are looked
+                // at together, and only then is the range searched
+                int32_t c2[NC], c1[NC];
+                int64_t f2[NC], f1[NC], s1[NC];
 #pragma unroll
-            for (int k = 0; k < NC; ++k) {
-                p[k] = hi[k] = 0;
-                cs[k] = cf[k] = kInf;
-                if (k < ncand) {
-                    int32_t lo = __builtin_amdgcn_readfirstlane(a.ranges[cand0 + k].lo);
-                    hi[k] = __builtin_amdgcn_readfirstlane(a.ranges[cand0 + k].hi);
-                    // finishes before lo are by s, those from x on after it
-                    int32_t x = late[k] ? hi[k] - 1 : lo, step = 1;
-                    while (lo < x) {
-                        const int32_t m = step ? (x - step > lo ? x - step : lo) : lo + (x - lo) / 2;
-                        if (fbase[(int64_t)a.cl[m] * ns] > s) {
-                            x = m;
-                            step *= 2;
-                        } else {
-                            lo = m + 1;
-                            step = 0;            // bracketed: bisect
-                        }
-                    }
-                    p[k] = late[k] ? x : hi[k];
-                    if (late[k]) {
-                        const int64_t c = a.cl[x];
+                for (int k = 0; k < NC; ++k) {
+                    p[k] = hi[k] = cn[k] = c2[k] = c1[k] = 0;
+                    ty[k] = 0;
+                    cs[k] = cf[k] = kInf;
+                    f2[k] = f1[k] = s1[k] = 0;
+                    if (k < ncand) {
+                        const int32_t lo = __builtin_amdgcn_readlane(rg.x, t0 + k);
+                        hi[k] = __builtin_amdgcn_readlane(rg.y, t0 + k);
+                        const int64_t c = __builtin_amdgcn_readlane(rg.z, t0 + k);
                         cs[k] = sbase[c * ns];
                         cf[k] = fbase[c * ns];
+                        ty[k] = a.cl_type[hi[k] - 1];
+                        cn[k] = (int32_t)c;
+                        c2[k] = hi[k] - 1 > lo ? __builtin_amdgcn_readfirstlane(a.cl[hi[k] - 2]) : -1;
+                        c1[k] = __builtin_amdgcn_readfirstlane(a.cl[lo]);
                     }
+                }
+#pragma unroll
+                for (int k = 0; k < NC; ++k)
+                    if (k < ncand && c2[k] >= 0) {
+                        f2[k] = fbase[(int64_t)c2[k] * ns];
+                        f1[k] = fbase[(int64_t)c1[k] * ns];
+                        s1[k] = sbase[(int64_t)c1[k] * ns];
+                    }
+#pragma unroll
+                for (int k = 0; k < NC; ++k) {
+                    if (k >= ncand) break;
+                    const bool on = (late_q >> k) & 1u;
+                    p[k] = on ? hi[k] - 1 : hi[k];
+                    const bool more = on && f2[k] > s;
+                    if (__ballot(more)) {
+                        const int32_t first_at = __builtin_amdgcn_readlane(rg.x, t0 + k);
+                        const bool all = more && f1[k] > s;
+                        if (all) {
+                            p[k] = first_at;
+                            cs[k] = s1[k];
+                            cf[k] = f1[k];
+                        }
+                        if (__ballot(more && !all)) {
+                            // backwards in doubling steps, then by halves: finishes before lo are by
+                            // s, those from x on after it
+                            int32_t lo = first_at, step = 2, x = more && !all ? hi[k] - 2 : lo;
+                            while (lo < x) {
+                                const int32_t m = step ? (x - step > lo ? x - step : lo) : lo + (x - lo) / 2;
+                                if (fbase[(int64_t)a.cl[m] * ns] > s) {
+                                    x = m;
+                                    step *= 2;
+                                } else {
+                                    lo = m + 1;
+                                    step = 0;            // bracketed: bisect
+                                }
+                            }
+                            if (more && !all) {
+                                p[k] = x;
+                                const int64_t c = a.cl[x];
+                                cs[k] = sbase[c * ns];
+                                cf[k] = fbase[c * ns];
+                            }
+                        }
+                        if (more) {
+                            ty[k] = a.cl_type[p[k]];
+                            next_id(k);
+                        }
+                    }
+                    if (!on) cs[k] = cf[k] = kInf;
                     cmin = cs[k] < cmin ? cs[k] : cmin;
                 }
             }
@@ -1310,17 +1411,18 @@ __global__ __launch_bounds__(64 * kOverlapWaves) void k_overlap(OverlapArgs a, i
                             if (!PRORATE) {
                                 const int64_t lo = sv > cs[k] ? sv : cs[k], up = fv < cf[k] ? fv : cf[k];
                                 if (lo < up) {
-                                    const uint32_t ty = a.cl_type[p[k]];
-                                    m |= 1u << ty;
-                                    NOTE_FOREST(p[k], ty)
+                                    m |= 1u << ty[k];
+                                    NOTE_FOREST(p[k], ty[k])
                                 }
                                 if (cf[k] >= fv) break;    // reaches v's end: later ops may overlap it
                             }
                             ++p[k];
                             if (p[k] < hi[k]) {
-                                const int64_t c = a.cl[p[k]];
+                                const int64_t c = cn[k];
                                 cs[k] = sbase[c * ns];
                                 cf[k] = fbase[c * ns];
+                                ty[k] = a.cl_type[p[k]];
+                                next_id(k);
                             } else {
                                 cs[k] = kInf;
                                 cf[k] = kInf;
@@ -1330,11 +1432,14 @@ __global__ __launch_bounds__(64 * kOverlapWaves) void k_overlap(OverlapArgs a, i
                     if (PRORATE) {
                         // merge the ranges' overlapping intervals in start order; every one of
                         // them ends after sv (each stream's intervals are disjoint and sorted)
-                        int32_t x[NC];
+                        int32_t x[NC], xn[NC];
+                        uint32_t xt[NC];
                         int64_t qs[NC], qf[NC];
 #pragma unroll
                         for (int k = 0; k < NC; ++k) {
                             x[k] = p[k];
+                            xn[k] = cn[k];
+                            xt[k] = ty[k];
                             qs[k] = cs[k];
                             qf[k] = cf[k];
                         }
@@ -1354,19 +1459,22 @@ __global__ __launch_bounds__(64 * kOverlapWaves) void k_overlap(OverlapArgs a, i
                                 if (k != bk) continue;
                                 const int64_t lo = sv > qs[k] ? sv : qs[k], up = fv < qf[k] ? fv : qf[k];
                                 if (lo < up) {
-                                    const uint32_t ty = a.cl_type[x[k]];
-                                    m |= 1u << ty;
-                                    NOTE_FOREST(x[k], ty)
+                                    m |= 1u << xt[k];
+                                    NOTE_FOREST(x[k], xt[k])
                                     const int64_t from = lo > t ? lo : t;
                                     if (up > from) {
                                         o += up - from;
                                         t = up;
                                     }
                                 }
-                                if (++x[k] < hi[k]) {
-                                    const int64_t c = a.cl[x[k]];
+                                if (qf[k] >= fv) {         // reaches v's end: the next starts no earlier
+                                    qs[k] = kInf;
+                                } else if (++x[k] < hi[k]) {
+                                    const int64_t c = xn[k];
                                     qs[k] = sbase[c * ns];
                                     qf[k] = fbase[c * ns];
+                                    xt[k] = a.cl_type[x[k]];
+                                    xn[k] = a.cl[x[k] + 1 < hi[k] ? x[k] + 1 : hi[k] - 1];
                                 } else {
                                     qs[k] = kInf;
                                 }
@@ -1519,8 +1627,10 @@ hipError_t launch_walk(const WalkArgs &a, int32_t n_blocks, hipStream_t stream) 
 template <bool PRORATE, bool DETECT, int FOREST, int NC>
 void launch_overlap_kernel(const OverlapArgs &a, size_t lds, hipStream_t stream) {
     const int64_t groups = (a.n_osegs + kOverlapGroup - 1) / kOverlapGroup;
-    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(groups, kRecParts / a.n_tiles));
-    const dim3 grid((unsigned)((parts * a.n_tiles + kOverlapWaves - 1) / kOverlapWaves)), block(kOverlapWaves * kLanes);
+    // the ensemble's LDS copy is filled by every workgroup: an eighth of the wavefronts there
+    const int64_t most = FOREST == 2 ? kRecParts / 8 : kRecParts;
+    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>((groups + kXcds - 1) / kXcds, most / kXcds / a.n_tiles));
+    const dim3 grid((unsigned)((parts * a.n_tiles + kOverlapWaves - 1) / kOverlapWaves * kXcds)), block(kOverlapWaves * kLanes);
     hipLaunchKernelGGL((k_overlap<PRORATE, DETECT, FOREST, NC>), grid, block, lds, stream, a, parts);
 }
 
@@ -1549,8 +1659,9 @@ hipError_t launch_overlap_nc(const OverlapArgs &a, hipStream_t stream) {
 
 hipError_t launch_overlap(const OverlapArgs &a, int32_t max_ranges, hipStream_t stream) {
     if (a.n_osegs == 0) return hipSuccess;
+    // GPT graphs have two (sends and data-parallel buckets)
     if (max_ranges > 4) return launch_overlap_nc<kStreams>(a, stream);
-    return launch_overlap_nc<4>(a, stream);
+    return max_ranges > 2 ? launch_overlap_nc<4>(a, stream) : launch_overlap_nc<2>(a, stream);
 }
 
 hipError_t launch_forest_bins(const DeviceGraph &g, int64_t n_recs, const CompactForest &fx, hipStream_t stream) {
