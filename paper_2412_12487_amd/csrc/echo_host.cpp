@@ -688,8 +688,8 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
     std::vector<WalkItem> items;                      // rounds of kBlock items, padded with empty ones
     items.reserve(2 * (order.size() + mem.size()));
     std::vector<int64_t> round_off(W + 1, 0);
-    std::vector<RowPair> rows;                        // kDurs per round: its segments' first and last ops
-    std::vector<int32_t> far;
+    std::vector<int32_t> rows;                        // kDurs per round: its segments' last ops
+    std::vector<RowPair> far;
     {
         const int npair = (int)(rpw * kStreams);       // (rank, stream) pairs of a walker
         std::vector<int32_t> latest(kStreams);
@@ -706,7 +706,7 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
         empty.coll = -1;
         auto close_round = [&]() {
             for (; in_round < kBlock; ++in_round) items.push_back(empty);
-            for (; segs_in_round < kDurs; ++segs_in_round) rows.push_back(RowPair{0, 0});
+            for (; segs_in_round < kDurs; ++segs_in_round) rows.push_back(0);
         };
         // the next item of the walk list; a round holds kBlock items, kDurs of them segments
         auto emit = [&](const WalkItem &it, bool seg) {
@@ -717,7 +717,7 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
             items.push_back(it);
             ++in_round;
             if (seg) {
-                rows.push_back(RowPair{it.op, it.coll});
+                rows.push_back(it.coll);
                 ++segs_in_round;
             }
         };
@@ -826,7 +826,7 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
                     if (fold && u != latest[0]) continue;          // folded into slot 0
                     const int su = slot[pair_of(u, r0)];
                     if (su >= 0 && latest[su] == u) mask |= 1u << su;
-                    else far.push_back(u);
+                    else far.push_back(RowPair{seg_of[u] < 0 ? -1 : recs[seg_off[seg_of[u]]].op, u});
                 }
                 if (sv == 0)
                     for (int32_t j = poff[v]; j < poff[v + 1]; ++j) covered[preds[j]] = 1;
@@ -885,7 +885,7 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
     {
         // what a pass that stores nothing else must still store
         std::vector<uint8_t> need(n, 0);
-        for (int32_t u : far) need[u] = 1;
+        for (const RowPair &u : far) need[u.last] = 1;
         for (int32_t u : link_prev)
             if (u >= 0) need[u] = 1;         // read back where the stream has no slot
         for (WalkItem &it : items) {

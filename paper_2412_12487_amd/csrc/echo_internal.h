@@ -241,8 +241,8 @@ struct DeviceGraph {
     int32_t n_ranks = 0, n_walkers = 0, n_blocks = 0;
     WalkItem *items = nullptr;       // walk lists, walker-major
     int64_t *round_off = nullptr;    // [n_walkers + 1] rounds of each walker: kBlock items, kDurs rows each
-    RowPair *walk_rows = nullptr;    // first and last op of the rounds' segments
-    int32_t *far = nullptr;          // far predecessor op ids
+    int32_t *walk_rows = nullptr;    // last op of the rounds' segments
+    RowPair *far = nullptr;          // far predecessors: a segment's first and last op, or a comm op (first -1)
     CollTable colls;                 // every collective
     int32_t *members = nullptr;      // [n_colls] member ops present: arrivals that complete a barrier
     CollTable classes;               // every cost class
@@ -280,16 +280,15 @@ constexpr int kClassMetrics = 4;
 // One pass over a range of scenario tiles: in the first pass the segments' jittered
 // durations are summed, then the sweep, and after the last one the ops' times.
 //
-// Where the sweep finds a segment's duration (other than the sum of its base durations,
-// in the first pass of a tile without jitter): the first pass of a tile with jitter in the
-// finish row of its last op; a refined pass as the difference of that row and the start
-// row of its first op, both left by the previous pass (overlap detection moves the finish
-// of a segment whose durations it changes).
+// Between the passes the finish row of a segment's last op holds the segment's duration:
+// k_sum puts it there (the first pass of a tile with jitter) or the first sweep (a tile
+// without, whose durations are the items'), and overlap detection changes it; the last
+// sweep replaces it by the finish.
 struct WalkArgs {
     const WalkItem *items;
     const int64_t *round_off;        // [walker + 1]
-    const RowPair *rows;             // [round][kDurs] first and last op of its segments
-    const int32_t *far;
+    const int32_t *rows;             // [round][kDurs] last op of its segments
+    const RowPair *far;
     const int32_t *c_N;              // [counted coll] member ops present (arrivals that complete the barrier)
     const int32_t *block_class;
     const echo_scenario *scen;
@@ -329,7 +328,8 @@ struct OverlapArgs {
     const int32_t *cl;
     const uint8_t *cl_type;
     const echo_scenario *scen;
-    int64_t *start, *finish;         // in: the previous pass's times; out: finish of a segment's last op
+    const int64_t *start;            // the previous pass's times
+    int64_t *finish;                 // of comm ops: their finishes; of segments (last op): in/out their durations
     // rows of the segment records, mstride columns
     uint8_t *tmask;                  // in: masks of the previous pass (if it was refined), out: new ones
     uint32_t *ext;                   // prorating: in/out like tmask, the extra time q16(o, F) - o

@@ -350,16 +350,26 @@ __device__ __forceinline__ int64_t inflate_row(int64_t d, uint32_t m, uint4 x) {
     const uint32_t F2 = a2 > a3 ? a2 : a3;
     return q16(d, F1 > F2 ? F1 : F2);
 }
-// s_waitcnt immediate for "lgkmcnt(0)" on gfx9-family targets (vmcnt and expcnt left at their maxima)
-constexpr int kWaitLgkm0 = 0xC07F;
-
-// Wait until `need` members have arrived at an LDS barrier slot of this block.
-__device__ __forceinline__ unsigned ld_local(const unsigned *p) {
-    return __builtin_amdgcn_readfirstlane(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+// Arrive at an LDS barrier with launch time v: raises the lanes' latest launch, then counts.
+// A wavefront's LDS operations are performed in order, so whoever sees the count sees the
+// launch; nothing is waited for.
+__device__ __forceinline__ void arrive_local(unsigned long long *bar, unsigned *cnt, int64_t v, int lane) {
+    __hip_atomic_fetch_max(&bar[lane], (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    asm volatile("" ::: "memory");                 // keep the compiler's order as well
+    if (lane == 0) __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-__device__ bool wait_local(const unsigned *cnt, unsigned need, unsigned *status, int64_t limit) {
-    if (ld_local(cnt) >= need) {
+// Wait until `need` members have arrived at an LDS barrier; *b gets the lane's latest launch,
+// read behind the count in each poll (in order, so it is whole when the count is).
+__device__ bool wait_local(const unsigned *cnt, unsigned need, const unsigned long long *bar, int lane, uint64_t *b,
+                           unsigned *status, int64_t limit) {
+    auto look = [&]() -> unsigned {
+        const unsigned c = __hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        asm volatile("" ::: "memory");             // keep the compiler's order as well
+        *b = __hip_atomic_load(&bar[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        return __builtin_amdgcn_readfirstlane(c);
+    };
+    if (look() >= need) {
         __builtin_amdgcn_s_setprio(3);             // last to arrive: see wait_arrivals
         return true;
     }
@@ -367,7 +377,7 @@ __device__ bool wait_local(const unsigned *cnt, unsigned need, unsigned *status,
     WaitClock clk;
     for (unsigned it = 1;; ++it) {
         __builtin_amdgcn_s_sleep(1);
-        if (ld_local(cnt) >= need) return true;
+        if (look() >= need) return true;
         if ((it & (kCheckPollsLocal - 1)) == 0 && !clk.check(status, limit)) return false;
     }
 }
@@ -478,26 +488,22 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
         const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(rows >> 32), j);
         return reinterpret_cast<GlobalI64 *>((((uint64_t)hi << 32) | lo) + coff);
     };
-    // Segment durations (see WalkArgs): lane q < kDurs holds the rows of the round's segment q
-    // (unused ones name op 0), fetched a round before the durations they name.
+    // Segment durations (see WalkArgs): lane q < kDurs holds the last op of the round's segment
+    // q (unused ones name op 0), fetched a round before the durations.
     const bool load_d = REFINED || ln.any_jitter;
-    auto load_rows = [&](int64_t r) -> int2 {
-        return load_d && r < end ? reinterpret_cast<const int2 *>(a.rows)[r * kDurs + (lane & (kDurs - 1))]
-                                 : make_int2(0, 0);
+    auto load_rows = [&](int64_t r) -> int32_t {
+        return load_d && r < end ? a.rows[r * kDurs + (lane & (kDurs - 1))] : 0;
     };
     int64_t *const dmem = durmem + wave * kDurs * kLanes + lane;
-    int64_t in_f[kDurs] = {}, in_s[kDurs] = {};
-    auto load_durs = [&](int2 rows) {
+    int64_t in_d[kDurs] = {};
+    auto load_durs = [&](int32_t rows) {
         if (!load_d) return;
-        const uint64_t fr = row_at(fadr, rows.y), sr = row_at(sadr, rows.x);
+        const uint64_t fr = row_at(fadr, rows);
 #pragma unroll
-        for (int q = 0; q < kDurs; ++q) {
-            in_f[q] = *row_of(fr, q);
-            if (REFINED) in_s[q] = *row_of(sr, q);
-        }
+        for (int q = 0; q < kDurs; ++q) in_d[q] = *row_of(fr, q);
     };
     int4 nxt = load_items(beg);
-    int2 rows = load_rows(beg);
+    int32_t rows = load_rows(beg);
     __builtin_amdgcn_s_waitcnt(kWaitVm0);
     load_durs(rows);
     rows = load_rows(beg + 1);
@@ -509,7 +515,7 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
         __builtin_amdgcn_s_waitcnt(kWaitVm0);
         if (load_d) {
 #pragma unroll
-            for (int q = 0; q < kDurs; ++q) dmem[q * kLanes] = REFINED ? in_f[q] - in_s[q] : in_f[q];
+            for (int q = 0; q < kDurs; ++q) dmem[q * kLanes] = in_d[q];
         }
         nxt = load_items(r + 1);
         load_durs(rows);
@@ -543,16 +549,11 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
                     const int ch = aux_barrier(aux);
                     if (meta & kLaunch) {
                         if (keep) put(row_of(srow, j), lf0);
-                        __hip_atomic_fetch_max(&lbar[ch][lane], (unsigned long long)lf0, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_WORKGROUP);
-                        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-                        if (lane == 0)
-                            __hip_atomic_fetch_add(&lcnt[ch], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        arrive_local(lbar[ch], &lcnt[ch], lf0, lane);
                     }
-                    if (!dead && !__builtin_amdgcn_readfirstlane(
-                                     wait_local(&lcnt[ch], aux_expected(aux), a.status, a.spin_limit)))
+                    if (!dead && !__builtin_amdgcn_readfirstlane(wait_local(&lcnt[ch], aux_expected(aux), lbar[ch], lane,
+                                                                            &b, a.status, a.spin_limit)))
                         dead = true;
-                    b = lbar[ch][lane];
                 } else if (aux & kAuxSlots) {
                     // the own launch is fetched with the members' (one round trip)
                     if (keep && (meta & kLinked)) own = *row_of(srow, j);
@@ -624,8 +625,10 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
                 const int32_t far_off = __builtin_amdgcn_readlane(cur.z, j);
                 const int32_t nfar = __builtin_amdgcn_readlane(cur.z, j + 32);
                 for (int32_t q = 0; q < nfar; ++q) {
-                    const int64_t u = a.far[far_off + q];
-                    const int64_t fu = (fbase + u * ns)[col];
+                    const RowPair u = a.far[far_off + q];
+                    int64_t fu = (fbase + (int64_t)u.last * ns)[col];
+                    // before the last pass a segment's row holds its duration
+                    if (!FINAL && u.first >= 0) fu += (sbase + (int64_t)u.first * ns)[col];
                     ready = fu > ready ? fu : ready;
                 }
                 __builtin_amdgcn_s_waitcnt(kWaitVm0);        // settled on this path, not at the join
@@ -636,11 +639,7 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
                 const uint32_t aux = (uint32_t)__builtin_amdgcn_readlane(cur.w, j + 32);
                 if (aux & kAuxLocal) {
                     const int ch = aux_barrier(aux);
-                    __hip_atomic_fetch_max(&lbar[ch][lane], (unsigned long long)ready, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
-                    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-                    if (lane == 0)
-                        __hip_atomic_fetch_add(&lcnt[ch], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    arrive_local(lbar[ch], &lcnt[ch], ready, lane);
                 } else if (aux & kAuxSlots) {
                     // this member's slot (its index is in the item's duration field): one store,
                     // no wait -- the value is its own arrival flag
@@ -669,7 +668,11 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
                 }
                 const int64_t f = ready + d;
                 hi_or |= (uint32_t)((uint64_t)f >> 32);
-                if (storef) put(row_of(frow, j), f);
+                if (FINAL) {
+                    if (storef) put(row_of(frow, j), f);
+                } else if (!load_d) {
+                    put(row_of(frow, j), d);
+                }
                 if (sq == 0) lf0 = f;
                 else if (sq < kStreams) smem[sq * kLanes] = f;
                 else xmax = f > xmax ? f : xmax;
@@ -912,8 +915,8 @@ __global__ __launch_bounds__(kRecWaves * 64) void k_expand(WalkArgs a, int64_t p
 // ops in turn.  The ops' intervals are rebuilt, not read: the first starts with the segment,
 // each later one where the one before finished, and a finish is start + base duration (the
 // same jitter draw as the composer pass, inflated by the factor that pass used).  With
-// the new factors the segment's new duration is known at once; its finish row is moved to
-// start + that duration, where the next pass takes it from.
+// the new factors the segment's new duration is known at once and goes where the next pass
+// takes it from.
 // Factor of a class-cls compute op overlapping the collective types in mask m:
 // the largest entry of the scenario's table row over them, 65536 for none.
 __device__ __forceinline__ uint32_t factor_of(uint32_t m, const uint32_t *slow, int cls) {
@@ -1520,7 +1523,7 @@ __global__ __launch_bounds__(64 * kOverlapWaves) void k_overlap(OverlapArgs a, i
                 if (DETECT) changed |= dn != d;
                 total += dn;
             }
-            fbase[(int64_t)last * ns] = s + total;
+            fbase[(int64_t)last * ns] = total;
             if (__builtin_amdgcn_readfirstlane(__ballot(hit) != 0)) now |= 1u << q;
         }
         if (lane < no) *flag = (now >> lane) & 1u;
