@@ -393,8 +393,11 @@ struct Lane {
                              // amplitude 0 gives f = 65536 and q16(d, 65536) = d)
     Jitter jt;
 };
-__device__ __forceinline__ Lane make_lane(const echo_scenario *scen, int32_t n_scen, int32_t tile, int lane) {
+// half: lanes 32..63 repeat lanes 0..31 (a tile of at most 32 scenarios)
+__device__ __forceinline__ Lane make_lane(const echo_scenario *scen, int32_t n_scen, int32_t tile, int lane,
+                                          bool half = false) {
     Lane x;
+    if (half) lane &= kLanes / 2 - 1;
     x.active = tile * kLanes + lane < n_scen;
     x.col = x.active ? lane : n_scen - 1 - tile * kLanes;
     x.sigma = tile * kLanes + x.col;
@@ -787,7 +790,11 @@ __global__ __launch_bounds__(kRecWaves * 64) void k_expand(WalkArgs a, int64_t p
     const int32_t tile = a.tile0 + (int32_t)(unit % a.tiles);
     const int64_t part = unit / a.tiles;
     if (part >= parts) return;
-    const Lane ln = make_lane(a.scen, a.n_scen, tile, lane);
+    // A tile of at most 32 scenarios fills half the lanes: the other half repeats it, and a
+    // finish and the next op's start, the same value, go out in one store (the store path takes
+    // a wavefront's store in about 32 cycles however many lanes it has).
+    const bool half = a.n_scen - tile * kLanes <= kLanes / 2;
+    const Lane ln = make_lane(a.scen, a.n_scen, tile, lane, half);
     const int64_t ns = a.n_scen;
     const uint64_t sadr = reinterpret_cast<uint64_t>(a.start + (int64_t)tile * kLanes);
     const uint64_t fadr = reinterpret_cast<uint64_t>(a.finish + (int64_t)tile * kLanes);
@@ -862,9 +869,14 @@ __global__ __launch_bounds__(kRecWaves * 64) void k_expand(WalkArgs a, int64_t p
                 const int64_t f = s + d;
                 if (DIGEST) dig += mix64(mix64((uint64_t)op ^ (uint64_t)s) ^ (uint64_t)f);
                 if (!DIGEST || a.timelines) {
-                    if (!DIGEST || j + 1 < end) {
-                        put_stream(row_of(frow, j), f);
-                        put_stream(row_of(srow, j + 1), f);
+                    if ((!DIGEST || j + 1 < end) && ln.active) {
+                        GlobalI64 *const pf = row_of(frow, j), *const ps = row_of(srow, j + 1);
+                        if (half) {
+                            put_stream(lane < kLanes / 2 ? pf : ps, f);
+                        } else {
+                            put_stream(pf, f);
+                            put_stream(ps, f);
+                        }
                     }
                 }
                 s = f;
@@ -900,7 +912,7 @@ __global__ __launch_bounds__(kRecWaves * 64) void k_expand(WalkArgs a, int64_t p
             j = end + 1;
         }
     }
-    if (DIGEST && ln.active)
+    if (DIGEST && ln.active && !(half && lane >= kLanes / 2))
         __hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(a.digest) + ln.sigma, (unsigned long long)dig,
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
