@@ -1661,6 +1661,7 @@ int echo_sync_status(echo_graph g, void *hip_stream) {
     if ((e = hipStreamSynchronize(static_cast<hipStream_t>(hip_stream)))) return hip_fail(e, "stream sync");
     unsigned st = 0;
     if ((e = hipMemcpy(&st, g->dg.status, sizeof st, hipMemcpyDeviceToHost))) return hip_fail(e, "status read");
+    if (st == 0) return ECHO_OK;                   // nothing to clear: one copy instead of two
     const unsigned zero = 0;
     if ((e = hipMemcpy(g->dg.status, &zero, sizeof zero, hipMemcpyHostToDevice))) return hip_fail(e, "status clear");
     if (st & kStatusTimeout)
