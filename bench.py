@@ -274,15 +274,15 @@ def cc_variant(sc, args):
     return sc
 
 
-# A final mask pass whose launches average at least this many 64-scenario tiles runs the walk
-# variant that fetches only flagged mask rows (the library's kFlagRowTiles).
+# A final mask pass whose launches average at least this many 64-scenario tiles runs under its
+# own kernel name (the library's kFlagRowTiles).
 FLAG_ROW_TILES = 2
 
 
 def walk_kernel_name(refined, final, digest, ext, n_tiles, launches=1):
     """The walk kernel a pass launches, as rocprofv3 names it: k_walk<input, final, digest>
-    with input 0 = none (first pass), 1 = whole mask rows, 2 = flagged mask rows (a final
-    pass of n_tiles >= FLAG_ROW_TILES x launches), 3 = flagged extra-time rows."""
+    with input 0 = none (first pass), 1 = refined by masks, 2 = the same in a final pass of
+    n_tiles >= FLAG_ROW_TILES x launches, 3 = refined by extra times."""
     b = lambda x: "true" if x else "false"
     flagged = final and n_tiles >= FLAG_ROW_TILES * launches
     inp = 0 if not refined else 3 if ext else 2 if flagged else 1
@@ -395,8 +395,8 @@ def walk_passes(kernel_times):
 # ---------------------------------------------------------------- latency floor of the walk
 def latency_model(E, jitter_amp, n_scen=64):
     """The walk's latencies measured on the device with small graphs whose longest
-    chain is known (workloads.microbench): ns per walk item (a chain of 40,000
-    compute ops on one rank), and per barrier met in LDS (eight ranks joining an
+    chain is known (workloads.microbench): ns per op (a chain of 40,000
+    compute ops on one rank, walked in segments), and per barrier met in LDS (eight ranks joining an
     all-reduce after every eight ops) or in device memory (send/recv between ranks
     of two workgroups), for the first pass (stores only what later kernels read)
     and the final, refined pass (stores every start and finish).  Each graph

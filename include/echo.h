@@ -337,7 +337,9 @@ int echo_sync_status(echo_graph g, void *hip_stream);
  * are recorded on the caller's stream around every kernel the call launches.
  * echo_kernel_times (after the stream has finished, e.g. after
  * echo_sync_status) reports the last compose call's kernels in launch order:
- * kinds[i] is ECHO_K_* and ms[i] the event-measured duration.  *n receives the
+ * kinds[i] is ECHO_K_* and ms[i] the event-measured duration (a walk entry covers
+ * the kernels that sum durations before a first sweep and write the ops' times
+ * after a last one).  *n receives the
  * number of kernels (at most max are written).
  */
 enum { ECHO_K_INIT = 0, ECHO_K_CC_COST = 1, ECHO_K_WALK = 2, ECHO_K_OVERLAP = 3, ECHO_K_CLEAR = 4 };
