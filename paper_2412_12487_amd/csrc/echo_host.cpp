@@ -811,6 +811,12 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
                     const int32_t u = preds[j];
                     fold = u == latest[0] || (d->op_kind[u] == ECHO_COMM && first_succ[u] == i - lo);
                 }
+                // slot 0's own comm ops first: their items set slot 0, and a linked one reads the
+                // finish of the op it is linked to there, so no other stream's finish may have
+                // raised it yet
+                if (fold)
+                    std::stable_partition(sched.begin() + next_due, sched.begin() + due_end,
+                                          [&](const auto &x) { return slot[pair_of(x.second, r0)] == 0; });
                 for (; next_due < due_end; ++next_due) {
                     const int32_t u = sched[next_due].second;
                     emit_resolve(u, slot[pair_of(u, r0)], fold);

@@ -90,7 +90,8 @@ constexpr uint32_t kLinked = 1u << 18;
 // The op's finish is read as a far predecessor: stored also by a pass that stores nothing
 // else (the last one, when neither timelines nor digests are asked for).
 constexpr uint32_t kNeedF = 1u << 19;
-// Resolve item: after writing the comm op's finish, raise slot 0 to it.
+// Resolve item: after writing the comm op's finish, raise slot 0 to it.  Among the items
+// folded before one segment, slot 0's own comm ops come first (they set slot 0).
 constexpr uint32_t kFold = 1u << 20;
 // Resolve item of a collective met in LDS that also is the comm op's launch, at slot 0's
 // value: the launch item right before it, waiting for nothing but the latest op of slot 0,

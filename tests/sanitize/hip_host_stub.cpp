@@ -5,9 +5,11 @@
 // instead of the HIP runtime and the device kernels, so that validation,
 // matching, levelling, walk-list construction, the upload and the walk-chain
 // analysis all run on the CPU under AddressSanitizer and UBSan.  "Device"
-// memory is host memory; kernel launches are refused.  Two controls for the
-// tests: fail the (k+1)-th allocation from now on (forced ECHO_ERR_NOMEM), and
-// count the allocations still live (nothing may leak on any error path).
+// memory is host memory; kernel launches are refused until the collectives' costs
+// are given, and then run as a model on the CPU (composer_model.h).  Controls for the
+// tests: fail the (k+1)-th allocation from now on (forced ECHO_ERR_NOMEM),
+// count the allocations still live (nothing may leak on any error path), and give
+// the costs [collective][scenario] that the composes from now on use (null: refuse).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -16,12 +18,14 @@
 #include <mutex>
 #include <set>
 
+#include "composer_model.h"
 #include "echo_internal.h"
 
 namespace {
 std::mutex g_mu;
 std::set<void *> g_live;
 int64_t g_fail_after = -1;   // allocations left before the next one fails (-1: never)
+const int64_t *g_costs = nullptr;   // [collective][scenario], or null: launches are refused
 }  // namespace
 
 extern "C" {
@@ -35,6 +39,8 @@ int64_t echo_stub_live_allocations(void) {
     std::lock_guard<std::mutex> lk(g_mu);
     return (int64_t)g_live.size();
 }
+
+void echo_stub_set_costs(const int64_t *costs) { g_costs = costs; }
 
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
@@ -83,22 +89,59 @@ hipError_t walk_capacity(int, int64_t workgroups[kWalkVariants]) {
     return hipSuccess;
 }
 
-hipError_t launch_init(const DeviceGraph &, const echo_scenario *, int32_t, unsigned long long *, int64_t, unsigned *,
-                       int64_t, int64_t *, int64_t, int64_t *, uint64_t *, hipStream_t) {
-    return hipErrorNotSupported;
+hipError_t launch_init(const DeviceGraph &, const echo_scenario *, int32_t n_scen, unsigned long long *arrive,
+                       int64_t n_arrive, unsigned *count, int64_t n_count, int64_t *slots, int64_t n_slot_values,
+                       int64_t *step, uint64_t *digest, hipStream_t stream) {
+    if (step) std::fill_n(step, n_scen, 0);
+    if (digest) std::fill_n(digest, n_scen, 0);
+    return launch_clear(arrive, n_arrive, count, n_count, slots, n_slot_values, stream);
 }
-hipError_t launch_clear(unsigned long long *, int64_t, unsigned *, int64_t, int64_t *, int64_t, hipStream_t) {
-    return hipErrorNotSupported;
+hipError_t launch_clear(unsigned long long *arrive, int64_t n_arrive, unsigned *count, int64_t n_count, int64_t *slots,
+                        int64_t n_slot_values, hipStream_t) {
+    if (!g_costs) return hipErrorNotSupported;
+    std::fill_n(arrive, n_arrive, 0);
+    std::fill_n(count, n_count, 0);
+    std::fill_n(slots, n_slot_values, -1);
+    return hipSuccess;
 }
-hipError_t launch_cc_cost(const CollTable &, const echo_cc_table *, const echo_scenario *, int32_t, int64_t *,
-                          unsigned *, hipStream_t) {
-    return hipErrorNotSupported;
+// the cost of a class is the given one of any of its collectives
+hipError_t launch_cc_cost(const CollTable &t, const echo_cc_table *, const echo_scenario *, int32_t n_scen,
+                          int64_t *cost, unsigned *, hipStream_t) {
+    if (!g_costs || t.row) return hipErrorNotSupported;
+    for (int64_t c = 0; c < t.n_out; ++c)
+        std::copy_n(g_costs + c * n_scen, n_scen, cost + (int64_t)t.class_of[c] * n_scen);
+    return hipSuccess;
 }
-hipError_t launch_walk(const WalkArgs &, int32_t, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_overlap(const OverlapArgs &, int32_t, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_settle(unsigned *, int32_t, int32_t *, unsigned *, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_fill_i32(int32_t *, int64_t, int32_t, hipStream_t) { return hipErrorNotSupported; }
-// the bins stay unset on the CPU: no compose runs there
+hipError_t launch_walk(const WalkArgs &a, int32_t, hipStream_t) {
+    if (!g_costs) return hipErrorNotSupported;
+    if (a.stable && *a.stable) return hipSuccess;
+    for (int32_t tile = a.tile0; tile < a.tile0 + a.tiles; ++tile) {
+        if (a.in == kInNone && echo_model::tile_jitter(a, tile)) echo_model::sums(a, tile);
+        if (!echo_model::sweep(a, tile)) return hipErrorUnknown;
+        if (a.final_pass && (a.timelines || a.digest)) echo_model::expand(a, tile);
+    }
+    return hipSuccess;
+}
+hipError_t launch_overlap(const OverlapArgs &a, int32_t, hipStream_t) {
+    if (!g_costs || a.forest_nodes) return hipErrorNotSupported;
+    if (!(a.stable && *a.stable)) echo_model::overlaps(a);
+    return hipSuccess;
+}
+hipError_t launch_settle(unsigned *chg, int32_t n_scen, int32_t *refinements, unsigned *stable, hipStream_t) {
+    bool any = false;
+    for (int32_t s = 0; s < n_scen; ++s) {
+        any = any || chg[s];
+        if (chg[s] && refinements) ++refinements[s];
+        chg[s] = 0;
+    }
+    if (!any) *stable = 1;
+    return hipSuccess;
+}
+hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t) {
+    std::fill_n(p, n, v);
+    return hipSuccess;
+}
+// the bins stay unset on the CPU: no compose with an ensemble runs there
 hipError_t launch_forest_bins(const DeviceGraph &, int64_t, const CompactForest &, hipStream_t) { return hipSuccess; }
 hipError_t scratch_buffer(int, void **ptr) {
     *ptr = nullptr;

@@ -6,7 +6,8 @@ streams is done (links).  These graphs sit at the edges: runs of 1, 31, 32, 33, 
 ops, runs broken by an op something else waits for, memcpy ops inside a run, a second
 compute stream, comm ops without dependencies launching in the middle of a run, chains of
 collectives of 3 members (member slots) and of 24 (counted arrivals), a stream that carries
-two communicators (no link), and several ranks per wavefront (streams without a slot).
+two communicators (no link), several ranks per wavefront (streams without a slot), and
+collectives on the compute streams.
 Integers, so every start, finish, step and digest must equal the oracle's.
 """
 from __future__ import annotations
@@ -16,7 +17,7 @@ import pytest
 
 import oracle
 from tests.test_gpu_parity import THREADS, assert_same, gpu_run
-from tests.tinygraph import AG, AR, MEMCPY, P2P, RS, Builder
+from tests.tinygraph import AG, AR, MEMCPY, P2P, RS, Builder, folded_link, shared_streams
 from workloads import scenarios
 
 pytestmark = pytest.mark.gpu
@@ -32,10 +33,11 @@ def E():
     return E
 
 
-def spmd_graph(seed, ranks=24, steps=10, buckets=6):
+def spmd_graph(seed, ranks=24, steps=10, buckets=6, shared=False):
     """Every rank runs the same program: per step a run of compute ops, then sometimes a
     pairwise exchange, a bucket reduction over ranks r, r + 8, r + 16 (stream 2) or over all
-    ranks (stream 1), or a send/recv to rank r +- 8; at the end one op per bucket waits for it."""
+    ranks (stream 1), or a send/recv to rank r +- 8; at the end one op per bucket waits for it.
+    shared: the reductions run on the compute streams 0 and 6 instead."""
     rng = np.random.default_rng(seed)
     b = Builder(ranks, gpus_per_node=4)
     plan = []
@@ -57,6 +59,7 @@ def spmd_graph(seed, ranks=24, steps=10, buckets=6):
             colls.append([b.collective(P2P, size) for _ in range(8)])
         else:
             colls.append([])
+    on = lambda stream: {1: 6, 2: 0, 7: 0}[stream] if shared else stream
     for r in range(ranks):
         tail, waits, buckets_of = -1, [], []
         for (run, kind, side, copy), ids in zip(plan, colls):
@@ -72,13 +75,13 @@ def spmd_graph(seed, ranks=24, steps=10, buckets=6):
                 if side == 2 and k == 5:
                     b.op(r, stream=5, kind=MEMCPY, dur=700)
             if kind == "bucket":
-                buckets_of.append(b.comm(r, ids[r % 8], stream=2, preds=[tail]))
+                buckets_of.append(b.comm(r, ids[r % 8], stream=on(2), preds=[tail]))
             elif kind == "free":              # no dependency but its stream: launches whenever that is free
-                b.comm(r, ids[r % 8], stream=2)
+                b.comm(r, ids[r % 8], stream=on(2))
             elif kind == "all":
-                buckets_of.append(b.comm(r, ids[0], stream=1 if side else 2, preds=[tail]))
+                buckets_of.append(b.comm(r, ids[0], stream=on(1 if side else 2), preds=[tail]))
             elif kind == "tp":
-                waits = [b.comm(r, ids[r // 4], stream=7, preds=[tail])]
+                waits = [b.comm(r, ids[r // 4], stream=on(7), preds=[tail])]
             elif kind == "p2p" and r < 16:
                 waits = [b.comm(r, ids[r % 8], stream=3 if r < 8 else 4, preds=[tail])] if r >= 8 else []
                 if r < 8:
@@ -111,6 +114,31 @@ def test_segments_and_links(E, seed, rpw):
             np.testing.assert_array_equal(out["refinements"].cpu().numpy(), ref["refinements"])
     finally:
         G.close()
+
+
+@pytest.mark.parametrize("rpw", [0, 3])
+@pytest.mark.parametrize("order", ["uxv", "xuv", "uvx"])
+def test_collectives_on_the_compute_stream_beside_a_folded_one(E, order, rpw):
+    """A comm op of the compute stream, linked or not, and one of another stream are resolved
+    before the same segment: neither's finish may stand in for the other's."""
+    g = folded_link(order)
+    sc = scenarios.draw(70, np.random.default_rng(1), bw_inter=(5_000, 400_000), slowdown=(65536, 150_000))
+    with E.Graph(g, 0, ranks_per_walker=rpw) as G:
+        for R in (0, 1):
+            assert_same(gpu_run(E, g, sc, R, graph=G), oracle.run(g, sc, R, threads=THREADS))
+
+
+@pytest.mark.parametrize("rpw", [0, 3])
+@pytest.mark.parametrize("seed", range(12))
+def test_collectives_on_compute_streams(E, seed, rpw):
+    rng = np.random.default_rng(seed)
+    g = spmd_graph(seed, shared=True) if seed < 4 else shared_streams(rng)
+    sc = scenarios.draw([1, 64, 70, 130][seed % 4], rng, bw_inter=(5_000, 400_000), bw_intra=(20_000, 400_000),
+                        alpha=(0, 20_000), ar_algo_random=True, slowdown=(65536, 150_000),
+                        jitter=(9000, seed) if seed % 2 else None)
+    with E.Graph(g, 0, ranks_per_walker=rpw) as G:
+        for R in (0, 2):
+            assert_same(gpu_run(E, g, sc, R, graph=G), oracle.run(g, sc, R, threads=THREADS))
 
 
 def test_digest_alone_and_one_output_alone(E):

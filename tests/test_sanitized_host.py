@@ -4,9 +4,9 @@ Builds echo_host.cpp (validation, matching, levelling, walk lists, upload,
 walk-chain analysis) with g++ -fsanitize=address,undefined, linked against a
 host-memory stand-in of the HIP runtime (tests/sanitize/hip_host_stub.cpp), and
 the oracle (oracle/echo_oracle.c) with gcc and the same sanitizers; then runs
-the ABI tests, the oracle pins and the stub-only loader tests (forced
-allocation failures, walk-chain hand cases) against those builds in a child
-pytest, with the AddressSanitizer runtime preloaded into it.  Any report
+the ABI tests, the oracle pins, the stub-only loader tests (forced
+allocation failures, walk-chain hand cases) and composes of the loaded lists by a
+CPU model of the kernels against those builds in a child pytest, with the AddressSanitizer runtime preloaded into it.  Any report
 (out-of-bounds access, use after free, undefined behaviour) fails the run.
 """
 from __future__ import annotations
@@ -59,7 +59,8 @@ def test_loader_and_oracle_under_sanitizers(sanitized):
                OMP_NUM_THREADS="1")
     r = subprocess.run([sys.executable, "-m", "pytest", "-q", "-x", "-p", "no:cacheprovider",
                         "-p", "tests.sanitize.plugin", "-m", "not gpu",
-                        "tests/test_abi.py", "tests/test_oracle_pins.py", "tests/sanitize/test_stubbed_loader.py"],
+                        "tests/test_abi.py", "tests/test_oracle_pins.py", "tests/sanitize/test_stubbed_loader.py",
+                        "tests/sanitize/test_composer_model.py"],
                        cwd=ROOT, env=env, capture_output=True, text=True, timeout=1500)
     tail = (r.stdout[-6000:] + "\n" + r.stderr[-6000:])
     assert r.returncode == 0, tail

@@ -119,3 +119,55 @@ def pipeline_1f1b(P, m, tf, tb, gpus_per_node=8):
                 comm(pid("b", p - 1, j), 3, False)
             j += 1
     return b.graph()
+
+
+def folded_link(order):
+    """16 ranks; on the compute stream of each the all-reduces u, then v, both over {r, r + 8}, and
+    on stream 1 a long one, x; the last compute op waits for v (its stream) and x.  order: the
+    program order of the three, as a string; where x comes before u, the latest it may be
+    resolved is still that op."""
+    b = Builder(16, gpus_per_node=4)
+    ids = {k: [b.collective(AR, size) for _ in range(8)] for k, size in (("u", 1 << 20), ("v", 1 << 20), ("x", 512 << 20))}
+    for r in range(16):
+        a = b.compute(r, 1000)
+        b.compute(r, 2000, cls=1)
+        op = {k: b.comm(r, ids[k][r % 8], stream=1 if k == "x" else 0, preds=[a]) for k in order}
+        b.compute(r, 500, cls=2, preds=[op["x"]])
+    return b.graph()
+
+
+def shared_streams(rng):
+    """Random ranks running one program of collectives in one order (so nothing deadlocks): pairs
+    over workgroups, all ranks, groups of four, random sets; comm ops, compute and memcpy ops
+    share streams 0, 1 and 6, with random dependencies."""
+    ranks = int(rng.integers(2, 28))
+    b = Builder(ranks, gpus_per_node=4)
+    plan, own = [], bool(rng.random() < 0.3)      # own: comm ops on streams of their own
+    for _ in range(int(rng.integers(2, 16))):
+        kind, stream = int(rng.integers(0, 4)), int(rng.integers(1, 4) if own else rng.integers(0, 3))
+        groups = [[r, r + 8] for r in range(max(0, min(8, ranks - 8)))] if kind == 0 else \
+            [list(range(ranks))] if kind == 1 else \
+            [list(range(i, min(i + 4, ranks))) for i in range(0, ranks, 4)] if kind == 2 else \
+            [sorted(rng.choice(ranks, size=int(rng.integers(1, ranks + 1)), replace=False).tolist())]
+        size = int(rng.integers(0, 64 << 20))
+        plan += [(b.collective(int(rng.choice([AR, AG, RS])), size), set(m), stream) for m in groups]
+    for r in range(ranks):
+        ids = []
+
+        def some(n, p):
+            return [u for u in ids[-n:] if rng.random() < p]
+
+        def work(streams, p):
+            copy = rng.random() < 0.15
+            ids.append(b.op(r, stream=int(rng.choice(streams)), kind=MEMCPY if copy else COMPUTE,
+                            cls=int(rng.integers(0, 8)), dur=int(rng.integers(0, 60_000)), preds=some(6, p)))
+
+        for c, members, stream in plan:
+            if r not in members:
+                continue
+            for _ in range(int(rng.integers(0, 4))):
+                work([0, 0, 0, 6, 1], 0.2)
+            ids.append(b.comm(r, c, stream=stream, preds=some(4, 0.3)))
+        for _ in range(3):
+            work([0, 6], 0.4)
+    return b.graph()
