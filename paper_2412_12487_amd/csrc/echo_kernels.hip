@@ -947,7 +947,8 @@ __device__ __forceinline__ uint32_t factor_of(uint32_t m, const uint32_t *slow, 
 // largest over the types.  Trees are walked from device memory (the walk stops at
 // a leaf; paths are at most ECHO_TREE_DEPTH splits long): when every lane that
 // needs a type shares one feature vector, once for the wavefront with one tree
-// per lane, else per lane.
+// per lane, else per lane.  Called with every lane active (m 0: 65536): a lane that
+// needs no type still walks its trees for the others.
 constexpr int kForestLanes = 16;
 // In the compact form the node reads are LDS reads and bound by its throughput (random banks):
 // a batch stops once its walks have reached their leaves, and a small one does so earlier
@@ -998,7 +999,7 @@ __device__ uint32_t forest_factor(const OverlapArgs &a, uint32_t m, const int64_
                 for (int o = kLanes / 2; o > 0; o >>= 1) leaf += __shfl_xor(leaf, o);
                 sum += leaf;
             }
-        } else {
+        } else if (has) {
             // kForestLanes trees walked side by side: their node loads are independent
             for (int32_t tr0 = 0; tr0 < a.n_trees; tr0 += kForestLanes) {
                 int32_t idx[kForestLanes];
@@ -1067,7 +1068,8 @@ __global__ void k_forest_bins(CollTable colls, const SegRec *recs, int64_t n_rec
 // rows 12-15: 0).  bS/bN: per type, the largest bins of S and N among the overlapping
 // type-t comm ops.  When every lane that has type t in its mask shares its feature
 // vector (knobs_uniform and equal S and N bins), the trees are walked once for the
-// wavefront, one tree per lane; otherwise each lane walks every tree on its own path.
+// wavefront, one tree per lane (every lane must be active); otherwise each lane that has
+// the type walks every tree on its own path.
 __device__ uint32_t forest_factor_compact(const OverlapArgs &a, uint32_t m, const int32_t *bS, const int32_t *bN,
                                           int cls, int32_t bd0, const uint32_t *fw, const int32_t *froots, uint16_t *fb,
                                           bool knobs_uniform, int lane) {
@@ -1109,7 +1111,7 @@ __device__ uint32_t forest_factor_compact(const OverlapArgs &a, uint32_t m, cons
                 for (int o = kLanes / 2; o > 0; o >>= 1) leaf += __shfl_xor(leaf, o);
                 sum += leaf;
             }
-        } else {
+        } else if (has) {
             for (int32_t tr0 = 0; tr0 < a.n_trees; tr0 += kFxLanes) {
                 int32_t idx[kFxLanes];
                 bool live[kFxLanes];
@@ -1133,7 +1135,7 @@ __device__ uint32_t forest_factor_compact(const OverlapArgs &a, uint32_t m, cons
                         moved |= off;
                     }
                     // every walk of the lanes that need type t rests on its leaf
-                    if (!__builtin_amdgcn_readfirstlane(__ballot(has && moved != 0) != 0)) break;
+                    if (!__builtin_amdgcn_readfirstlane(__ballot(moved != 0) != 0)) break;
                 }
 #pragma unroll
                 for (int q = 0; q < kFxLanes; ++q)
@@ -1512,9 +1514,10 @@ __global__ __launch_bounds__(64 * kOverlapWaves) void k_overlap(OverlapArgs a, i
 #undef NOTE_FOREST
                 int64_t dn;                                // v's duration in the next pass
                 if (EXT) {
-                    uint32_t e = 0;
-                    if (m != 0) {
-                        uint32_t F;
+                    uint32_t e = 0, F = 65536u;
+                    // the ensemble is walked by the whole wavefront, lanes that overlap nothing included:
+                    // a tree per lane where the others share one feature vector
+                    if (FOREST && __ballot(m != 0)) {
                         if (FOREST == 2) {
                             int32_t bS[kTypes];
 #pragma unroll
@@ -1523,11 +1526,12 @@ __global__ __launch_bounds__(64 * kOverlapWaves) void k_overlap(OverlapArgs a, i
                             F = forest_factor_compact(a, m, bS, nmax, cls, bd0, fwords,
                                                       reinterpret_cast<const int32_t *>(fwords) + a.fx.n_words, fb,
                                                       knobs_uniform, lane);
-                        } else if (FOREST == 1) {
-                            F = forest_factor(a, m, smax, nmax, cls, d0, sc, feat, knobs_uniform, lane);
                         } else {
-                            F = factor_of(m, slow, cls);
+                            F = forest_factor(a, m, smax, nmax, cls, d0, sc, feat, knobs_uniform, lane);
                         }
+                    }
+                    if (m != 0) {
+                        if (!FOREST) F = factor_of(m, slow, cls);
                         const int64_t oc = PRORATE ? (o < D ? o : D) : D;
                         const int64_t x = q16(oc, F) - oc;
                         ext_over |= x >= (int64_t)kExtLimit;
