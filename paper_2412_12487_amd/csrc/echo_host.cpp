@@ -1357,7 +1357,15 @@ int echo_cc_cost(echo_graph g, const echo_scenario *d_scen, int32_t n_scen, int6
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     if ((e = launch_init(g->dg, d_scen, n_scen, nullptr, 0, nullptr, 0, nullptr, 0, nullptr, nullptr, s)))
         return hip_fail(e, "init kernel");
-    if ((e = launch_cc_cost(g->dg.classes, g->dg.cc_tables, d_scen, n_scen, d_cost, g->dg.status, s)))
+    // The class rows and their copies take two kernels, every collective by itself one: the
+    // second launch (3 us) pays from about 800,000 evaluations replaced by copies.  Per call,
+    // one kernel / two, collectives x scenarios of three classes: 128 x 4096 13.7 / 17.1 us,
+    // 1024 x 256 13.1 / 16.4, 256 x 4096 20.8 / 17.6, 1024 x 1024 16.7 / 16.1, 1024 x 4096
+    // 44.9 / 21.7; with a class per collective the copies save nothing (1024 x 4096 44.4 / 46.0).
+    constexpr int64_t kCopiedEvals = 800000;
+    const bool copies = (g->dg.colls.n - g->dg.classes.n) * n_scen >= kCopiedEvals;
+    if ((e = launch_cc_cost(copies ? g->dg.classes : g->dg.colls, g->dg.cc_tables, d_scen, n_scen, d_cost,
+                            g->dg.status, s)))
         return hip_fail(e, "cc_cost kernel");
     return ECHO_OK;
 }

@@ -2,7 +2,7 @@
 //
 //   k_init     clear barrier state and outputs, check scenario ranges
 //   k_clear    clear barrier state between passes
-//   k_cc_cost  CC estimator (Sec. 5.3, Eq. 2-5): one lane per (collective, scenario)
+//   k_cc_cost  CC estimator (Sec. 5.3, Eq. 2-5): one lane per (collective or cost class, scenario)
 //   k_sum      what-if durations: per segment and scenario, the sum of its ops' jittered
 //              base durations (first pass)
 //   k_walk     timeline composer (Sec. 4.2) with the collective synchronisation
@@ -145,7 +145,7 @@ __global__ void k_clear(unsigned long long *arrive, int64_t n_arrive, unsigned *
 }
 
 // ------------------------------------------------------------------ CC estimator
-// One block per cost class; lanes stride over scenarios.  Row of class c: t.row[c], or c.
+// One block per collective or cost class; lanes stride over scenarios.  Row of c: t.row[c], or c.
 __global__ __launch_bounds__(64) void k_cc_cost(CollTable t, const echo_cc_table *tables, const echo_scenario *scen,
                                                 int32_t n_scen, int64_t *cost, unsigned *status) {
     const int64_t c = blockIdx.x;
@@ -1610,7 +1610,7 @@ hipError_t launch_clear(unsigned long long *arrive, int64_t n_arrive, unsigned *
 hipError_t launch_cc_cost(const CollTable &t, const echo_cc_table *tables, const echo_scenario *scen,
                           int32_t n_scen, int64_t *cost, unsigned *status, hipStream_t stream) {
     if (t.n == 0 || n_scen == 0) return hipSuccess;
-    // one lane per (collective, scenario): collectives along x, 64-scenario tiles along y
+    // one lane per (row of the table, scenario): rows along x, 64-scenario tiles along y
     const unsigned tiles = (unsigned)std::min<int64_t>((n_scen + 63) / 64, 65535);
     hipLaunchKernelGGL(k_cc_cost, dim3((unsigned)t.n, tiles), dim3(64), 0, stream, t, tables, scen, n_scen, cost,
                        status);

@@ -8,8 +8,9 @@
 // memory is host memory; kernel launches are refused until the collectives' costs
 // are given, and then run as a model on the CPU (composer_model.h).  Controls for the
 // tests: fail the (k+1)-th allocation from now on (forced ECHO_ERR_NOMEM),
-// count the allocations still live (nothing may leak on any error path), and give
-// the costs [collective][scenario] that the composes from now on use (null: refuse).
+// count the allocations still live (nothing may leak on any error path), give the
+// costs [collective][scenario] that the composes from now on use (null: refuse), and
+// ask how many collectives or cost classes the last cost launch evaluated.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -26,6 +27,7 @@ std::mutex g_mu;
 std::set<void *> g_live;
 int64_t g_fail_after = -1;   // allocations left before the next one fails (-1: never)
 const int64_t *g_costs = nullptr;   // [collective][scenario], or null: launches are refused
+int64_t g_cost_rows = -1;    // collectives or cost classes that the last cost launch evaluates
 }  // namespace
 
 extern "C" {
@@ -41,6 +43,7 @@ int64_t echo_stub_live_allocations(void) {
 }
 
 void echo_stub_set_costs(const int64_t *costs) { g_costs = costs; }
+int64_t echo_stub_cost_rows(void) { return g_cost_rows; }
 
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
@@ -98,7 +101,7 @@ hipError_t launch_init(const DeviceGraph &, const echo_scenario *, int32_t n_sce
 }
 hipError_t launch_clear(unsigned long long *arrive, int64_t n_arrive, unsigned *count, int64_t n_count, int64_t *slots,
                         int64_t n_slot_values, hipStream_t) {
-    if (!g_costs) return hipErrorNotSupported;
+    if (!g_costs && (n_arrive || n_count || n_slot_values)) return hipErrorNotSupported;
     std::fill_n(arrive, n_arrive, 0);
     std::fill_n(count, n_count, 0);
     std::fill_n(slots, n_slot_values, -1);
@@ -107,7 +110,8 @@ hipError_t launch_clear(unsigned long long *arrive, int64_t n_arrive, unsigned *
 // the cost of a class is the given one of any of its collectives
 hipError_t launch_cc_cost(const CollTable &t, const echo_cc_table *, const echo_scenario *, int32_t n_scen,
                           int64_t *cost, unsigned *, hipStream_t) {
-    if (!g_costs || t.row) return hipErrorNotSupported;
+    g_cost_rows = t.n;
+    if (!g_costs || t.row || !t.class_of) return hipErrorNotSupported;
     for (int64_t c = 0; c < t.n_out; ++c)
         std::copy_n(g_costs + c * n_scen, n_scen, cost + (int64_t)t.class_of[c] * n_scen);
     return hipSuccess;

@@ -149,3 +149,25 @@ def test_walk_chain_covers_the_longest_walk_list(E):
         ch2 = _chain(G, (1, 10**6, 10**6))
         assert ch2["ps"] == ch2["items"] + 10**6 * (ch2["lds_barriers"] + ch2["global_barriers"])
         assert ch2["ps"] >= ch["ps"] and ch2["lds_barriers"] + ch2["global_barriers"] > 0
+
+
+def test_cost_classes_are_used_where_copies_replace_enough_evaluations(E):
+    """echo_cc_cost evaluates every collective by itself (one kernel) until the class rows and
+    their copies (two) save 800,000 evaluations; where every collective is a class of its own,
+    always."""
+    E.lib().echo_stub_cost_rows.restype = ctypes.c_int64
+
+    def rows(k, classes, n):
+        b = Builder(2)
+        ids = [b.collective(AR, 1000 + c % classes) for c in range(k)]
+        for r in range(2):
+            for c in ids:
+                b.comm(r, c)
+        with E.Graph(b.graph()) as G:
+            scen = out = ctypes.c_void_p(64)        # never read: the launch is refused
+            E.lib().echo_cc_cost(G.handle, scen, n, out, None)
+        return int(E.lib().echo_stub_cost_rows())
+
+    assert rows(6, 3, 1) == 6 and rows(6, 3, 4096) == 6
+    assert rows(203, 3, 3999) == 203 and rows(203, 3, 4000) == 3
+    assert rows(300, 300, 1 << 20) == 300
