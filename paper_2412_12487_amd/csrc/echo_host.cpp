@@ -688,7 +688,7 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
     std::vector<WalkItem> items;                      // rounds of kBlock items, padded with empty ones
     items.reserve(2 * (order.size() + mem.size()));
     std::vector<int64_t> round_off(W + 1, 0);
-    std::vector<int32_t> rows;                        // kDurs per round: its segments' last ops
+    std::vector<int32_t> rows, rec_rows;              // kDurs per round: its segments' last ops and first records
     std::vector<RowPair> far;
     {
         const int npair = (int)(rpw * kStreams);       // (rank, stream) pairs of a walker
@@ -706,7 +706,10 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
         empty.coll = -1;
         auto close_round = [&]() {
             for (; in_round < kBlock; ++in_round) items.push_back(empty);
-            for (; segs_in_round < kDurs; ++segs_in_round) rows.push_back(0);
+            for (; segs_in_round < kDurs; ++segs_in_round) {
+                rows.push_back(0);
+                rec_rows.push_back(0);
+            }
         };
         // the next item of the walk list; a round holds kBlock items, kDurs of them segments
         auto emit = [&](const WalkItem &it, bool seg) {
@@ -718,6 +721,7 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
             ++in_round;
             if (seg) {
                 rows.push_back(it.coll);
+                rec_rows.push_back(seg_off[seg_of[it.op]]);
                 ++segs_in_round;
             }
         };
@@ -988,6 +992,7 @@ int load(const echo_graph_desc *d, int device, int32_t min_rpw, echo_graph *out)
     UP(dg.items, items);
     UP(dg.round_off, round_off);
     UP(dg.walk_rows, rows);
+    UP(dg.walk_recs, rec_rows);
     UP(dg.far, far);
     for (int t = 0; t < 2; ++t) {
         HostCollTable &h = t == 0 ? colls : cls;
@@ -1097,6 +1102,32 @@ int ensure_workspace(echo_graph g, const ComposeShape &sh, int32_t n_refine, int
     return ECHO_OK;
 }
 
+// A compose without refinement (one pass) has two routes to its timelines: the sweep of
+// segments between k_sum and k_expand, which has the shorter chain, or one sweep of the ops
+// themselves (kInOps), which draws and stores while other wavefronts wait.  The second takes
+// about 0.1 us longer per level of the graph (a walker of several ranks, per rank) and saves
+// what the first spends per op and scenario: it pays from about 48,000 evaluations (ops x
+// scenarios) per level, rank of a walker and launch.  Measured, segments / ops in ms, by
+// thousands of evaluations per level: 26 (8 ranks x 4096 scenarios) 0.117 / 0.141, 35 (2048 x
+// 32) 2.9 / 3.2, 46 (a replica of 128 x 1000) 4.1 / 4.3, 67 (640 x 192) 2.0 / 1.6, 69 (32 x
+// 3000) 0.65 / 0.55, 93 (16 x 8000) 1.26 / 1.03, 178 (1024 x 256) 15.1 / 11.5; 8192 ranks, two
+// per walker: 46 (x 32) 4.6 / 5.3, 93 (x 64, jitter) 8.4 / 7.8.  With digests the second has
+// more to do per op on its chain, and segments stay (1024 x 256 17.0 / 16.7, a replica of 128 x
+// 2000 6.7 / 8.1, 96 x 2048 11.3 / 12.8).  The tiles are shared out evenly among the launches:
+// one tile left over would cost a chain of its own.
+constexpr int64_t kOpsEvals = 48000;
+bool sweep_ops(echo_graph g, int32_t n_scen, int32_t n_tiles, int64_t *per_launch) {
+    if (g->dg.n_recs == 0) return false;
+    const int64_t most = std::min(*per_launch, g->capacity[walk_variant(kInOps, true, false)] / g->dg.n_blocks);
+    const int64_t launches = (n_tiles + most - 1) / most, even = (n_tiles + launches - 1) / launches;
+    const int64_t rpw = (g->n_ranks + g->n_walkers - 1) / g->n_walkers;
+    if ((double)g->n_ops * (double)std::min<int64_t>(n_scen, even * kLanes) <
+        (double)kOpsEvals * (double)g->n_levels * (double)rpw)
+        return false;
+    *per_launch = even;
+    return true;
+}
+
 // Enqueue one compose: init, class costs, pass 1, then per refinement overlap
 // detection (+ settle) and the refined pass.  `timed`: record kernel events.
 int enqueue_compose(echo_graph g, const echo_scenario *d_scen, int32_t n_scen, const echo_validator &val,
@@ -1135,6 +1166,7 @@ int enqueue_compose(echo_graph g, const echo_scenario *d_scen, int32_t n_scen, c
         const int64_t cap = g->capacity[walk_variant(walk_input(p > 0, ext, false), fin, d_digest != nullptr)];
         int64_t per_launch = std::max<int64_t>(1, std::min<int64_t>(n_tiles, cap / g->dg.n_blocks));
         if (g->max_launch_tiles > 0) per_launch = std::min<int64_t>(per_launch, g->max_launch_tiles);
+        const bool ops = n_refine == 0 && timelines && !d_digest && sweep_ops(g, n_scen, n_tiles, &per_launch);
         if (p > 0) {
             OverlapArgs o{};
             o.osegs = g->dg.osegs;
@@ -1180,6 +1212,8 @@ int enqueue_compose(echo_graph g, const echo_scenario *d_scen, int32_t n_scen, c
             a.items = g->dg.items;
             a.round_off = g->dg.round_off;
             a.rows = g->dg.walk_rows;
+            a.rec_rows = g->dg.walk_recs;
+            a.n_recs = g->dg.n_recs;
             a.recs = g->dg.recs;
             a.chunks = g->dg.chunks;
             a.n_chunks = g->dg.n_chunks;
@@ -1207,7 +1241,7 @@ int enqueue_compose(echo_graph g, const echo_scenario *d_scen, int32_t n_scen, c
             a.tile0 = (int32_t)t0;
             a.tiles = (int32_t)std::min<int64_t>(per_launch, n_tiles - t0);
             a.n_walkers = g->n_walkers;
-            a.in = walk_input(p > 0, ext, fin && n_tiles >= kFlagRowTiles * ((n_tiles + per_launch - 1) / per_launch));
+            a.in = ops ? kInOps : walk_input(p > 0, ext, fin && n_tiles >= kFlagRowTiles * ((n_tiles + per_launch - 1) / per_launch));
             a.final_pass = fin;
             a.timelines = fin && timelines;
             if (g->n_ranks == 0 || g->n_ops == 0) continue;

@@ -243,6 +243,7 @@ struct DeviceGraph {
     WalkItem *items = nullptr;       // walk lists, walker-major
     int64_t *round_off = nullptr;    // [n_walkers + 1] rounds of each walker: kBlock items, kDurs rows each
     int32_t *walk_rows = nullptr;    // last op of the rounds' segments
+    int32_t *walk_recs = nullptr;    // their first records
     RowPair *far = nullptr;          // far predecessors: a segment's first and last op, or a comm op (first -1)
     CollTable colls;                 // every collective
     int32_t *members = nullptr;      // [n_colls] member ops present: arrivals that complete a barrier
@@ -289,6 +290,7 @@ struct WalkArgs {
     const WalkItem *items;
     const int64_t *round_off;        // [walker + 1]
     const int32_t *rows;             // [round][kDurs] last op of its segments
+    const int32_t *rec_rows;         // [round][kDurs] their first records
     const RowPair *far;
     const int32_t *c_N;              // [counted coll] member ops present (arrivals that complete the barrier)
     const int32_t *block_class;
@@ -296,7 +298,7 @@ struct WalkArgs {
     const int64_t *class_cost;       // [class][scen]
     const SegRec *recs;
     const RecChunk *chunks;
-    int64_t n_chunks;
+    int64_t n_chunks, n_recs;
     // Per-op outputs of overlap detection, one row per segment record of a flagged segment,
     // mstride columns (the tiles' scenarios, padded to whole tiles):
     const uint8_t *tmask;            // overlap type masks, or null
@@ -379,21 +381,23 @@ hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t stream)
 // What a pass is refined by, the walk kernel's first template argument.  The sweep itself
 // only tells the first pass from the others; the rest is a label that keeps the passes
 // apart in kernel traces: refined by masks (a final pass over many tiles, whose timelines
-// fill the memory system, under a name of its own) or by extra times.
+// fill the memory system, under a name of its own) or by extra times.  With kInOps the
+// sweep draws every op and writes its times itself, without k_sum and k_expand.
 constexpr int kInNone = 0;        // first pass: base durations
 constexpr int kInMasks = 1;       // overlap masks
 constexpr int kInMaskFlags = 2;   // overlap masks, final pass of kFlagRowTiles tiles per launch or more
 constexpr int kInExtFlags = 3;    // prorated or ensemble extra times
+constexpr int kInOps = 4;         // only pass (no refinement, no digest): the sweep walks the segments' ops
 inline int walk_input(bool refined, bool ext, bool many_tiles) {
     return !refined ? kInNone : ext ? kInExtFlags : many_tiles ? kInMaskFlags : kInMasks;
 }
 // Co-resident walk workgroups (kBlockWalkers wavefronts each) the device can hold,
-// for each kernel variant (bits 0-1 input, bit 2 final, bit 3 digest); at most
+// for each kernel variant (bits 0-2 input, bit 3 final, bit 4 digest); at most
 // kWalkersPerCu / kBlockWalkers per compute unit.
-constexpr int kWalkVariants = 16;
+constexpr int kWalkVariants = 32;
 hipError_t walk_capacity(int device, int64_t workgroups[kWalkVariants]);
 inline int walk_variant(int in, bool final_pass, bool digest) {
-    return in | (final_pass ? 4 : 0) | (digest ? 8 : 0);
+    return in | (final_pass ? 8 : 0) | (digest ? 16 : 0);
 }
 // Device address of this GPU's fixed workspace array (ECHO_SCRATCH_BYTES) for
 // echo_compose_batch_static; `device` must be current.  Looked up once per device.

@@ -330,7 +330,7 @@ typedef __attribute__((address_space(1))) int64_t GlobalI64;     // global, not 
 // The sweep's stores go through the cache: overlap detection and k_expand read the rows again,
 // and a later poll of the same wavefront waits for them.
 __device__ __forceinline__ void put(GlobalI64 *p, int64_t v) { *p = v; }
-// The other timeline stores are read by nothing here.
+// The other timeline stores are read by nothing here, or only by far predecessors.
 __device__ __forceinline__ void put_stream(GlobalI64 *p, int64_t v) {
     __builtin_nontemporal_store(v, p);
 }
@@ -410,22 +410,30 @@ __device__ __forceinline__ Lane make_lane(const echo_scenario *scen, int32_t n_s
 
 // A workgroup of kBlockWalkers wavefronts walks the walkers of one block for
 // one 64-scenario tile; wavefront w walks walker block * kBlockWalkers + w.  IN (kIn*):
-// what the pass is refined by.  FINAL: the pass produces the step time (and DIGEST: the comm ops'
-// share of the digest).
+// what the pass is refined by, or kInOps.  FINAL: the pass produces the step time (and DIGEST:
+// the comm ops' share of the digest).
 //
 // What bounds it: latency.  The sweep is one chain of segments and barriers per
 // scenario tile (on the 1024-rank workload 1.5 thousand segments and 2.7 thousand
 // barriers long), and a wavefront runs its items one after the other.  So an item costs its
 // instructions, and everything an item could wait for is fetched well before: items a round
 // (32) ahead, segment durations a group (kDurs) ahead, both settled by one wait each.
+//
+// kInOps is bound by its stores once enough wavefronts share the chip: with draws, barriers and
+// stores of different wavefronts side by side 1024 ranks x 256 scenarios take 11.5 ms (65 GB at 5.7 TB/s)
+// where k_sum, this sweep and k_expand one after another take 15.1; 640 x 768 4.7 and 6.2.  All its stores
+// are non-temporal (with the last finish of a segment and the comm ops' times through the cache
+// 32 ranks x 5000 take 0.90 instead of 0.83 ms, 1024 x 256 11.9 instead of 11.5).
 template <int IN, bool FINAL, bool DIGEST>
 __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per_eu(4))) void k_walk(WalkArgs a) {
-    constexpr bool REFINED = IN != kInNone;
+    constexpr bool OPS = IN == kInOps, REFINED = IN != kInNone && !OPS;
+    static_assert(!OPS || (FINAL && !DIGEST), "the sweep of the ops is the only pass, without digests");
     __shared__ unsigned long long lbar[kChannels * 2][kLanes];   // per channel and slot: latest launch per lane
     __shared__ unsigned lcnt[kChannels * 2];                      // per channel and slot: members arrived
     __shared__ int64_t ccost[kClassSlots][kLanes];                // staged class costs of this tile
     __shared__ int64_t slotmem[kBlockWalkers * kStreams * kLanes];   // slots 1..7 of every wave (slot 0 stays in a register)
-    __shared__ int64_t durmem[kBlockWalkers * kDurs * kLanes];       // durations of every wave's round
+    // durations of every wave's round; OPS: the records of its segments, kSegOps each
+    __shared__ __align__(16) int64_t durmem[kBlockWalkers * kDurs * kLanes];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform within a wavefront
@@ -491,15 +499,35 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
         const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(rows >> 32), j);
         return reinterpret_cast<GlobalI64 *>((((uint64_t)hi << 32) | lo) + coff);
     };
+    // OPS: nothing but a far predecessor reads the times again
+    auto put_time = [&](GlobalI64 *p, int64_t v) {
+        if (OPS) put_stream(p, v);
+        else put(p, v);
+    };
     // Segment durations (see WalkArgs): lane q < kDurs holds the last op of the round's segment
     // q (unused ones name op 0), fetched a round before the durations.
-    const bool load_d = REFINED || ln.any_jitter;
+    const bool load_d = REFINED || (!OPS && ln.any_jitter);
     auto load_rows = [&](int64_t r) -> int32_t {
-        return load_d && r < end ? a.rows[r * kDurs + (lane & (kDurs - 1))] : 0;
+        return (OPS || load_d) && r < end ? (OPS ? a.rec_rows : a.rows)[r * kDurs + (lane & (kDurs - 1))] : 0;
     };
     int64_t *const dmem = durmem + wave * kDurs * kLanes + lane;
     int64_t in_d[kDurs] = {};
+    // OPS: the records instead, lanes 32 * (q & 1) onwards of in_rec[q / 2] holding segment q's
+    // (records behind a shorter segment's are fetched too, and not looked at)
+    constexpr int kRecLoads = kDurs * kSegOps / kLanes;
+    static_assert(kSegOps == kLanes / 2 && kRecLoads * sizeof(SegRec) == kDurs * sizeof(int64_t), "records fill the durations' place");
+    typedef int Rec __attribute__((ext_vector_type(4)));
+    Rec *const rmem = reinterpret_cast<Rec *>(durmem + wave * kDurs * kLanes);
+    Rec in_rec[kRecLoads] = {};
     auto load_durs = [&](int32_t rows) {
+        if (OPS) {
+#pragma unroll
+            for (int p = 0; p < kRecLoads; ++p) {
+                const int64_t at = (int64_t)__shfl(rows, 2 * p + (lane >> 5)) + (lane & (kSegOps - 1));
+                in_rec[p] = reinterpret_cast<const Rec *>(a.recs)[at < a.n_recs ? at : 0];
+            }
+            return;
+        }
         if (!load_d) return;
         const uint64_t fr = row_at(fadr, rows);
 #pragma unroll
@@ -519,6 +547,10 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
         if (load_d) {
 #pragma unroll
             for (int q = 0; q < kDurs; ++q) dmem[q * kLanes] = in_d[q];
+        }
+        if (OPS) {
+#pragma unroll
+            for (int p = 0; p < kRecLoads; ++p) rmem[p * kLanes + lane] = in_rec[p];
         }
         nxt = load_items(r + 1);
         load_durs(rows);
@@ -605,7 +637,7 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
                 }
                 const int64_t f = (int64_t)b + t;
                 hi_or |= (uint32_t)((uint64_t)f >> 32);
-                if (storef) put(row_of(frow, j), f);
+                if (storef) put_time(row_of(frow, j), f);
                 if (DIGEST) {
                     const int32_t op = __builtin_amdgcn_readlane(cur.x, j);
                     const int64_t s = *row_of(srow, j);
@@ -636,7 +668,7 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
                 }
                 __builtin_amdgcn_s_waitcnt(kWaitVm0);        // settled on this path, not at the join
             }
-            if (keep) put(row_of(srow, j), ready);
+            if (keep) put_time(row_of(srow, j), ready);
             if (kind == ECHO_COMM) {
                 // launch: publish this member's launch time, then count the arrival
                 const uint32_t aux = (uint32_t)__builtin_amdgcn_readlane(cur.w, j + 32);
@@ -662,6 +694,39 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
                                                __HIP_MEMORY_SCOPE_AGENT);
                 }
             } else {
+                int64_t f;
+                if (OPS) {
+                    // the segment's ops one after the other: each finish but the last is the next op's start
+                    const Rec rec = rmem[__builtin_popcount(seg_bits & ((1u << j) - 1)) * kSegOps + (lane & (kSegOps - 1))];
+                    const int n = __builtin_amdgcn_readlane(cur.w, j + 32);
+                    const uint64_t prow = row_at(fadr, rec.x), qrow = row_at(sadr, rec.x);
+                    f = ready;
+                    auto steps = [&](auto jit, auto is_small) {
+                        for (int i = 0; i < n; ++i) {
+                            const int32_t op = decltype(jit)::value ? __builtin_amdgcn_readlane(rec.x, i) : 0;
+                            const uint32_t dlo = (uint32_t)__builtin_amdgcn_readlane(rec.z, i);
+                            if (decltype(is_small)::value) {
+                                f += decltype(jit)::value ? jittered32(dlo, op, ln.jt) : (int64_t)dlo;
+                            } else {
+                                const uint32_t dhi = (uint32_t)__builtin_amdgcn_readlane(rec.w, i);
+                                const int64_t d0 = (int64_t)(((uint64_t)dhi << 32) | dlo);
+                                f += decltype(jit)::value ? jittered(d0, op, ln.jt) : d0;
+                            }
+                            put_time(row_of(prow, i), f);
+                            if (i + 1 < n) put_time(row_of(qrow, i + 1), f);
+                        }
+                    };
+                    // (of the records behind the segment too: the general form is right for all)
+                    const bool small = __builtin_amdgcn_readfirstlane(__ballot(rec.w != 0) == 0);
+                    if (!ln.any_jitter) steps(std::false_type{}, std::false_type{});
+                    else if (small) steps(std::true_type{}, std::true_type{});
+                    else steps(std::true_type{}, std::false_type{});
+                    hi_or |= (uint32_t)((uint64_t)f >> 32);
+                    if (sq == 0) lf0 = f;
+                    else if (sq < kStreams) smem[sq * kLanes] = f;
+                    else xmax = f > xmax ? f : xmax;
+                    continue;
+                }
                 int64_t d;
                 if (load_d) {
                     d = dmem[__builtin_popcount(seg_bits & ((1u << j) - 1)) * kLanes];
@@ -669,7 +734,7 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
                     d = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(cur.y, j + 32) << 32) |
                                   (uint32_t)__builtin_amdgcn_readlane(cur.x, j + 32));
                 }
-                const int64_t f = ready + d;
+                f = ready + d;
                 hi_or |= (uint32_t)((uint64_t)f >> 32);
                 if (FINAL) {
                     if (storef) put(row_of(frow, j), f);
@@ -700,12 +765,13 @@ __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per
 
 using WalkKernel = void (*)(WalkArgs);
 WalkKernel walk_kernel(int in, bool final_pass, bool digest) {
-    // a digest only in a final pass, kInMaskFlags too
+    // a digest only in a final pass, kInMaskFlags too; kInOps is a final pass without one
     if (!final_pass) {
         if (in == kInNone) return k_walk<kInNone, false, false>;
         return in == kInExtFlags ? k_walk<kInExtFlags, false, false> : k_walk<kInMasks, false, false>;
     }
     switch (in) {
+    case kInOps: return k_walk<kInOps, true, false>;
     case kInNone: return digest ? k_walk<kInNone, true, true> : k_walk<kInNone, true, false>;
     case kInMasks: return digest ? k_walk<kInMasks, true, true> : k_walk<kInMasks, true, false>;
     case kInMaskFlags: return digest ? k_walk<kInMaskFlags, true, true> : k_walk<kInMaskFlags, true, false>;
@@ -1651,7 +1717,7 @@ hipError_t launch_walk(const WalkArgs &a, int32_t n_blocks, hipStream_t stream) 
     // one (8 ranks x 4096 scenarios: 196 -> 152 us per call)
     e = n_blocks == 1 ? hipLaunchKernel(reinterpret_cast<const void *>(k), grid, block, params, 0, stream)
                       : hipLaunchCooperativeKernel(reinterpret_cast<const void *>(k), grid, block, params, 0, stream);
-    if (e != hipSuccess || a.n_chunks == 0 || !a.final_pass || !(a.timelines || a.digest)) return e;
+    if (e != hipSuccess || a.in == kInOps || a.n_chunks == 0 || !a.final_pass || !(a.timelines || a.digest)) return e;
     if (a.ext) return launch_expand<kInExtFlags>(a, parts, stream);
     return a.tmask ? launch_expand<kInMasks>(a, parts, stream) : launch_expand<kInNone>(a, parts, stream);
 }
@@ -1743,8 +1809,14 @@ hipError_t walk_capacity(int device, int64_t workgroups[kWalkVariants]) {
     hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
     if (e != hipSuccess) return e;
     for (int v = 0; v < kWalkVariants; ++v) {
+        const WalkKernel k = walk_kernel(v & 7, v & 8, v & 16);
+        int u = 0;                                   // a kernel of several variants is asked about once
+        while (walk_kernel(u & 7, u & 8, u & 16) != k) ++u;
+        if (u < v) {
+            workgroups[v] = workgroups[u];
+            continue;
+        }
         int per_cu = 0;
-        const WalkKernel k = walk_kernel(v & 3, v & 4, v & 8);
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(k),
                                                          kBlockWalkers * kLanes, 0);
         if (e != hipSuccess) return e;

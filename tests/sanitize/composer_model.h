@@ -72,7 +72,8 @@ inline bool sweep(const WalkArgs &a, int32_t tile) {
     };
     const int64_t ns = a.n_scen, s0 = (int64_t)tile * kLanes;
     const int lanes = (int)std::min<int64_t>(kLanes, ns - s0);
-    const bool refined = a.in != kInNone, load_d = refined || tile_jitter(a, tile);
+    const bool ops = a.in == kInOps, refined = a.in != kInNone && !ops;
+    const bool load_d = refined || (!ops && tile_jitter(a, tile));
     const bool keep = !a.final_pass || a.digest || a.timelines;
     auto at = [&](int64_t *base, int64_t row) { return base + row * ns + s0; };
     std::vector<Walker> ws(a.n_walkers);
@@ -178,8 +179,22 @@ inline bool sweep(const WalkArgs &a, int32_t tile) {
                 int64_t q = 0;
                 for (int64_t x = k.item - in_round; x < k.item; ++x) q += (a.items[x].meta & 1u) == 0;
                 if (q >= kDurs || a.rows[k.item / kBlock * kDurs + q] != it.coll) return false;
+                const int64_t r0 = a.rec_rows[k.item / kBlock * kDurs + q], r1 = r0 + it.aux;
+                if (r0 < 0 || r1 > a.n_recs || a.recs[r0].op != it.op || a.recs[r1 - 1].op != it.coll) return false;
                 for (int l = 0; l < lanes; ++l) {
                     int64_t &row = at(a.finish, it.coll)[l];
+                    if (ops) {
+                        int64_t t = ready[l];
+                        for (int64_t i = r0; i < r1; ++i) {
+                            const SegRec &r = a.recs[i];
+                            at(a.start, r.op)[l] = t;
+                            t += jittered(r.dur, r.op, a.scen[s0 + l]);
+                            at(a.finish, r.op)[l] = t;
+                        }
+                        if (sq >= 0) k.slot[sq][l] = t;
+                        else k.none[l] = std::max(k.none[l], t);
+                        continue;
+                    }
                     const int64_t d = load_d ? row : it.dur, f = ready[l] + d;
                     if (!a.final_pass) row = d;
                     else if (keep || (it.meta & kNeedF)) row = f;

@@ -10,7 +10,8 @@
 // tests: fail the (k+1)-th allocation from now on (forced ECHO_ERR_NOMEM),
 // count the allocations still live (nothing may leak on any error path), give the
 // costs [collective][scenario] that the composes from now on use (null: refuse), and
-// ask how many collectives or cost classes the last cost launch evaluated.
+// ask how many collectives or cost classes the last cost launch evaluated and which input
+// the last sweep had.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -28,6 +29,7 @@ std::set<void *> g_live;
 int64_t g_fail_after = -1;   // allocations left before the next one fails (-1: never)
 const int64_t *g_costs = nullptr;   // [collective][scenario], or null: launches are refused
 int64_t g_cost_rows = -1;    // collectives or cost classes that the last cost launch evaluates
+int64_t g_sweep_in = -1;     // input (kIn*) of the last sweep
 }  // namespace
 
 extern "C" {
@@ -44,6 +46,7 @@ int64_t echo_stub_live_allocations(void) {
 
 void echo_stub_set_costs(const int64_t *costs) { g_costs = costs; }
 int64_t echo_stub_cost_rows(void) { return g_cost_rows; }
+int64_t echo_stub_sweep_in(void) { return g_sweep_in; }
 
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
@@ -117,12 +120,13 @@ hipError_t launch_cc_cost(const CollTable &t, const echo_cc_table *, const echo_
     return hipSuccess;
 }
 hipError_t launch_walk(const WalkArgs &a, int32_t, hipStream_t) {
+    g_sweep_in = a.in;
     if (!g_costs) return hipErrorNotSupported;
     if (a.stable && *a.stable) return hipSuccess;
     for (int32_t tile = a.tile0; tile < a.tile0 + a.tiles; ++tile) {
         if (a.in == kInNone && echo_model::tile_jitter(a, tile)) echo_model::sums(a, tile);
         if (!echo_model::sweep(a, tile)) return hipErrorUnknown;
-        if (a.final_pass && (a.timelines || a.digest)) echo_model::expand(a, tile);
+        if (a.in != kInOps && a.final_pass && (a.timelines || a.digest)) echo_model::expand(a, tile);
     }
     return hipSuccess;
 }

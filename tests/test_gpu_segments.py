@@ -141,6 +141,39 @@ def test_collectives_on_compute_streams(E, seed, rpw):
             assert_same(gpu_run(E, g, sc, R, graph=G), oracle.run(g, sc, R, threads=THREADS))
 
 
+@pytest.mark.parametrize("seed,rpw,cap", [(0, 0, 0), (1, 0, 0), (3, 0, 7), (4, 3, 0), (5, 0, 0)])
+def test_unrefined_timelines_from_the_sweep_of_the_ops(E, seed, rpw, cap):
+    """From 48,000 evaluations per level and rank of a walker on (of one launch) the sweep walks the
+    ops themselves: just below that line, at it and above, ragged tiles, base durations above
+    2^32 ns, launches of a few tiles (cap), the allocation-free entry point and no timelines."""
+    import torch
+    rng = np.random.default_rng(seed)
+    g = shared_streams(np.random.default_rng(0)) if seed == 5 else spmd_graph(seed, steps=2, buckets=1, shared=seed == 4)
+    if seed == 1:
+        wide = (np.arange(len(g["op_dur"])) % 11 == 0) & (g["op_kind"] == 0)
+        g["op_dur"][wide] += 1 << 33
+    with E.Graph(g, 0, ranks_per_walker=rpw) as G:
+        line = -(-48_000 * G.n_levels * max(rpw, 1) // G.n_ops)
+        for n in (line - 1, line, line + 70):
+            n = n * 3 if cap else n
+            sc = scenarios.draw(n, rng, bw_inter=(5_000, 400_000), alpha=(0, 20_000), ar_algo_random=True,
+                                jitter=(9000, seed) if seed != 3 else None)
+            ref = oracle.run(g, sc, 0, threads=THREADS)
+            G.set_launch_tiles(-(-n // 64) // 3 if cap else 0)
+            d, n = E.scenarios_to_device(sc)
+            out = {k: torch.full((G.n_ops, n) if k != "step" else (n,), -1, dtype=torch.int64, device="cuda:0")
+                   for k in ("start", "finish", "step")}
+            G.compose(d, n, 0, out=out)
+            outs = [out]
+            if seed == 0:
+                outs.append(G.compose_static(d, n, 0, {k: torch.full_like(v, -1) for k, v in out.items()}))
+            for o in outs:
+                np.testing.assert_array_equal(o["step"].cpu().numpy(), ref["step"])
+                np.testing.assert_array_equal(o["start"].cpu().numpy().T, ref["start"])
+                np.testing.assert_array_equal(o["finish"].cpu().numpy().T, ref["finish"])
+            np.testing.assert_array_equal(G.compose(d, n, 0, timelines=False)["step"].cpu().numpy(), ref["step"])
+
+
 def test_digest_alone_and_one_output_alone(E):
     """Digest without timelines, and start or finish alone through the C ABI."""
     import ctypes
