@@ -235,9 +235,10 @@ class Graph:
             self.handle = None
         _open_graphs.discard(self)
 
-    def __del__(self):
-        # no HIP calls while the interpreter shuts down: the runtime may be gone
-        if sys.is_finalizing():
+    def __del__(self, _finalizing=sys.is_finalizing):
+        # no HIP calls while the interpreter shuts down: the runtime may be gone, and so may
+        # this module's globals (the check is bound here)
+        if _finalizing():
             return
         try:
             self.close()

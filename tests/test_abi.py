@@ -221,3 +221,15 @@ def test_binding_rejects_unfit_buffers(E):
             B._device_buffer(t, "start", cpu, 4 * 8 * 8, torch.int64)
     with pytest.raises(B.EchoError, match="the graph on"):
         B._device_buffer(ok, "start", torch.device("meta"), 8)
+
+
+def test_a_graph_collected_after_the_module_is_torn_down(E, monkeypatch):
+    """At interpreter exit a module's globals become None before the last objects go: the finalizer
+    neither raises nor reaches the library then."""
+    import paper_2412_12487_amd.echo as echo
+    g = object.__new__(E.Graph)
+    g.handle = 1                                  # no graph: freeing it would crash
+    for name in ("sys", "lib", "_open_graphs"):
+        monkeypatch.setattr(echo, name, None)
+    g.__del__()
+    g.handle = None
