@@ -6,8 +6,8 @@ refinement) with step time, on inputs already resident in HBM.  The graph is
 loaded once before timing (the simulator's initialisation, excluded as in
 Table 8 of the paper).
 
-Prints one JSON line with the metric, a roofline entry for the composer
-(walk) kernel, and the CPU oracle timed on a bounded sample of the same work.
+Prints one JSON line with the metric, a roofline entry for the composer's
+passes, and the CPU oracle timed on a bounded sample of the same work.
 
 --replica times the data-parallel symmetry reduction instead (Sec. 8.5, DDP
 mode): one DP replica of a graph whose replicas share their durations,
@@ -64,6 +64,11 @@ def walk_bytes(g, n_scen, n_refine):
     n_compute = int((g["op_kind"] == 0).sum())
     passes = [per_pass] + [per_pass + 1 * n_compute * n_scen] * n_refine
     return passes
+
+
+def timeline_bytes(n_ops, n_scen):
+    """What a pass that writes timelines cannot do without: start and finish of every op, once."""
+    return 16 * int(n_ops) * int(n_scen)
 
 
 def source_hash():
@@ -274,19 +279,41 @@ def cc_variant(sc, args):
     return sc
 
 
+# Without refinement (and digests) the sweep walks the ops themselves from this many evaluations
+# (ops x scenarios of a launch) per level and rank of a walker on (the library's kOpsEvals).
+OPS_EVALS = 48_000
+# Ranks that get a wavefront of their own: more share them (8 wavefronts per workgroup, two
+# workgroups on each of 256 compute units).
+WALKERS = 4096
+
 # A final mask pass whose launches average at least this many 64-scenario tiles runs under its
 # own kernel name (the library's kFlagRowTiles).
 FLAG_ROW_TILES = 2
 
 
-def walk_kernel_name(refined, final, digest, ext, n_tiles, launches=1):
+def walk_kernel_name(refined, final, digest, ext, n_tiles, launches=1, ops=False):
     """The walk kernel a pass launches, as rocprofv3 names it: k_walk<input, final, digest>
     with input 0 = none (first pass), 1 = refined by masks, 2 = the same in a final pass of
-    n_tiles >= FLAG_ROW_TILES x launches, 3 = refined by extra times."""
+    n_tiles >= FLAG_ROW_TILES x launches, 3 = refined by extra times, 4 = an only pass that
+    walks the ops (ops)."""
     b = lambda x: "true" if x else "false"
     flagged = final and n_tiles >= FLAG_ROW_TILES * launches
-    inp = 0 if not refined else 3 if ext else 2 if flagged else 1
+    inp = (4 if ops and final and not digest else 0) if not refined else 3 if ext else 2 if flagged else 1
     return f"k_walk<{inp}, {b(final)}, {b(digest)}>"
+
+
+def sweep_of_ops(n_ops, levels, ranks, n_scen, launches):
+    """Whether an only pass over n_scen scenarios in so many launches walks the ops."""
+    tiles = -(-n_scen // 64)
+    per_launch = min(n_scen, -(-tiles // max(launches, 1)) * 64)
+    return n_ops * per_launch >= OPS_EVALS * levels * -(-ranks // WALKERS)
+
+
+def pass_kernels(walk, first, final):
+    """Kernels that a pass's sweep entry covers (it writes timelines when it is the last one)."""
+    if walk.startswith("k_walk<4"):
+        return [walk]
+    return (["k_sum"] if first else []) + [walk] + (["k_expand"] if final else [])
 
 
 def time_compose(E, g, sc, args, extras, latency=None):
@@ -296,12 +323,12 @@ def time_compose(E, g, sc, args, extras, latency=None):
     t = time.perf_counter()
     G = E.Graph(g, 0)
     try:
-        return _time_compose(E, G, sc, args, extras, latency, time.perf_counter() - t)
+        return _time_compose(E, G, sc, args, extras, latency, time.perf_counter() - t, int(g["n_ranks"]))
     finally:
         G.close()
 
 
-def _time_compose(E, G, sc, args, extras, latency, load_s):
+def _time_compose(E, G, sc, args, extras, latency, load_s, ranks):
     import torch
     if extras.get("cc_tables") is not None:
         G.set_cc_tables(extras["cc_tables"])
@@ -345,7 +372,9 @@ def _time_compose(E, G, sc, args, extras, latency, load_s):
            "kernels_ms": {k: round(float(np.mean(v)), 4) for k, v in kernels.items()},
            # the last step's walk launches, pass by pass (a split pass lists each launch)
            "walk_pass_ms": [[round(ms, 4) for ms in p] for p in pass_runs[-1] if p] if pass_runs else []}
-    res.update(pass_summary(pass_runs, args.prorate or args.forest, (n_scen + 63) // 64))
+    launches = len(pass_runs[-1][0]) if pass_runs else 1
+    res.update(pass_summary(pass_runs, args.prorate or args.forest, (n_scen + 63) // 64,
+                            sweep_of_ops(G.n_ops, G.n_levels, ranks, n_scen, launches)))
     if latency is not None:
         n_pass = max(res["pass_index"]) + 1 if res["pass_index"] else 1
         res["floors"] = [walk_floor(G, latency, k, n_pass) for k in res["pass_index"]]
@@ -366,7 +395,7 @@ def _time_compose(E, G, sc, args, extras, latency, load_s):
     return res
 
 
-def pass_summary(pass_runs, ext, n_tiles):
+def pass_summary(pass_runs, ext, n_tiles, ops=False):
     """Walk passes of the timed steps: mean time per pass (a pass split over several
     launches counts all of them), launches per pass and the kernel variant; passes that
     returned at once (every scenario already at its fixed point) are left out."""
@@ -375,7 +404,8 @@ def pass_summary(pass_runs, ext, n_tiles):
     launches = [max(len(p[k]) for p in pass_runs if k < len(p)) for k in range(n_pass)]
     top = max(pass_ms, default=0.0)
     ran = [k for k in range(n_pass) if pass_ms[k] > 0.02 * top]
-    names = [walk_kernel_name(k > 0, k == n_pass - 1, False, ext, n_tiles, launches[k]) for k in range(n_pass)]
+    names = [walk_kernel_name(k > 0, k == n_pass - 1, False, ext, n_tiles, launches[k], ops and n_pass == 1)
+             for k in range(n_pass)]
     return {"pass_ms": [pass_ms[k] for k in ran], "pass_launches": [launches[k] for k in ran],
             "pass_kernels": [names[k] for k in ran], "pass_index": ran}
 
@@ -463,12 +493,16 @@ def walk_floor(G, latency, k, n_pass):
 
 
 def roofline(g, r, args, traffic_config):
-    """Per walk pass: algorithmic bytes (edge-relaxation model) and their fraction of
-    the HBM peak at the pass's measured time, the byte counters' bytes when recorded
-    for these very kernels, and the latency floor; the headline is the final,
-    timeline-producing pass."""
+    """Per pass: its time (an entry of the sweep covers the sums before a first sweep and the
+    expansion after the last one), what the byte counters recorded for these very kernels, and
+    the latency floor of the sweep's longest chain.  The headline is the last pass, the one
+    that writes the caller's timelines: 16 bytes per op and scenario, the least it can move,
+    against its time.  Passes before it are bound by latency and have no such fraction.
+    edge_model_bytes is what relaxing every edge through memory would move (the work of
+    a pass, for comparison between graphs; segments keep most of it in registers)."""
     n_pass = max(r["pass_index"]) + 1 if r["pass_index"] else 1
-    alg = walk_bytes(g, r["n_scen"], n_pass - 1)
+    edges = walk_bytes(g, r["n_scen"], n_pass - 1)
+    timelines = timeline_bytes(len(g["op_rank"]), r["n_scen"])
     traffic = {}
     if traffic_config is not None and os.path.exists(TRAFFIC_FILE):
         tr = json.load(open(TRAFFIC_FILE))
@@ -476,27 +510,29 @@ def roofline(g, r, args, traffic_config):
             traffic = tr.get("pass_bytes", {})
     passes = []
     for j, k in enumerate(r["pass_index"]):
-        ms = r["pass_ms"][j]
-        e = {"pass": k + 1, "kernel": r["pass_kernels"][j], "launches": r["pass_launches"][j], "ms": round(ms, 4),
-             "alg_bytes": int(alg[k]), "alg_frac": round(alg[k] / (ms / 1000.0) / 1e9 / HBM_PEAK_GBS, 4)}
+        ms, final = r["pass_ms"][j], k == n_pass - 1
+        e = {"pass": k + 1, "kernel": r["pass_kernels"][j], "covers": pass_kernels(r["pass_kernels"][j], k == 0, final),
+             "launches": r["pass_launches"][j], "ms": round(ms, 4),
+             "alg_bytes": timelines if final else None,
+             "alg_frac": round(timelines / (ms / 1000.0) / 1e9 / HBM_PEAK_GBS, 4) if final else None,
+             "edge_model_bytes": int(edges[k])}
         cb = traffic.get(r["pass_kernels"][j])
         e["counter_bytes"] = int(cb) if cb is not None else None
         e["counter_frac"] = round(cb / (ms / 1000.0) / 1e9 / HBM_PEAK_GBS, 4) if cb is not None else None
         if r.get("floors"):
-            f = r["floors"][j]
-            e.update(f)
-            e["over_floor"] = round(ms / f["floor_ms"], 3) if f["floor_ms"] > 0 else None
+            e.update(r["floors"][j])
         passes.append(e)
-    head = passes[-1] if passes else {"kernel": "k_walk", "launches": 1, "ms": 0.0, "alg_bytes": 0,
-                                      "counter_bytes": None, "counter_frac": None}
-    per_launch = head["alg_bytes"] / max(head["launches"], 1)
+    head = passes[-1] if passes else {"kernel": "k_walk", "covers": ["k_walk"], "launches": 1, "ms": 0.0,
+                                      "alg_bytes": 0, "counter_bytes": None, "counter_frac": None}
+    per_launch = (head["alg_bytes"] or 0) / max(head["launches"], 1)
     launch_ms = head["ms"] / max(head["launches"], 1)
     achieved = per_launch / (launch_ms / 1000.0) / 1e9 if launch_ms > 0 else 0.0
     out = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": round(achieved / HBM_PEAK_GBS, 4),
            "traffic": int(head["counter_bytes"] / max(head["launches"], 1))
            if head["counter_bytes"] is not None else None,
-           "kernel": head["kernel"], "role": "final walk pass, the one that writes the caller's timelines",
+           "kernel": head["kernel"], "covers": head["covers"],
+           "role": "last pass: the sweep and the expansion that writes the caller's timelines",
            "avg_launch_ms": round(launch_ms, 4), "algorithmic_bytes_per_launch": int(per_launch)}
     if out["traffic"] is not None:
         out["traffic_frac"] = head["counter_frac"]
@@ -522,7 +558,7 @@ def batch_mode(args, E, configs):
         G.set_timing(True)
         d, n = E.scenarios_to_device(sc, "cuda:0")
         graphs.append({"G": G, "d": d, "n": n, "ops": G.n_ops, "ranks": int(g["n_ranks"]), "levels": G.n_levels})
-        alg.append(walk_bytes(g, n, args.refine))
+        alg.append(timeline_bytes(G.n_ops, n))
         log(f"graph {i + 1}/{n_graphs}: {G.n_ops} ops, {g['n_ranks']} ranks, loaded "
             f"({time.perf_counter() - t:.1f} s so far)")
         del g
@@ -568,13 +604,12 @@ def batch_mode(args, E, configs):
         runs = [walk_passes(kt) for kt in per_graph[j]]
         ps = pass_summary(runs, False, (x["n"] + 63) // 64)
         compose_ms = float(np.mean([sum(ms for _, ms in kt) for kt in per_graph[j]]))
-        final = ps["pass_index"][-1] if ps["pass_index"] else 0
         fms = ps["pass_ms"][-1] if ps["pass_ms"] else 0.0
         model, tp, pp, dp, m, distopt = configs.EXTRAP_GRAPHS[j]
         rows.append({"graph": j + 1, "model": model, "tp": tp, "pp": pp, "dp": dp, "microbatches": m,
                      "distributed_optimizer": distopt, "ops": x["ops"], "ranks": x["ranks"], "levels": x["levels"],
                      "kernels_ms": round(compose_ms, 4), "walk_pass_ms": [round(v, 4) for v in ps["pass_ms"]],
-                     "final_pass_alg_frac": round(alg[j][final] / (fms / 1000.0) / 1e9 / HBM_PEAK_GBS, 4)
+                     "final_pass_alg_frac": round(alg[j] / (fms / 1000.0) / 1e9 / HBM_PEAK_GBS, 4)
                      if fms > 0 else None})
     line = {
         "metric": "op-evaluations/sec (ops x scenarios composed), 1 GPU",
@@ -595,8 +630,8 @@ def batch_mode(args, E, configs):
                                f"{args.refine} refinement(s)",
                    "n_ops": sum(x["ops"] for x in graphs), "n_scenarios_each": graphs[0]["n"],
                    "n_refine": args.refine, "load_s": round(time.perf_counter() - t - wall, 1)},
-        "note": "32 scenarios fill half of each 64-lane wavefront: every walk item costs a whole "
-                "wavefront for half its lanes",
+        "note": "32 scenarios fill half of each 64-lane wavefront: every item of a sweep costs a "
+                "whole wavefront for half its lanes",
         "graphs": rows,
     }
     print(json.dumps(line), flush=True)

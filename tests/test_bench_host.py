@@ -64,15 +64,19 @@ def _timed(pass_ms, launches):
 
 def test_roofline_headline_is_the_final_pass():
     """Two passes of two launches each: the headline is the final (timeline-writing)
-    pass, per launch; every pass is listed with its own algorithmic fraction."""
+    pass, per launch, at the bytes it has to write; a pass before it has no fraction."""
     g = _graph()
     rf = bench.roofline(g, _timed([4.0, 6.0], [2, 2]), None, None)
-    alg = bench.walk_bytes(g, 128, 1)
-    assert rf["algorithmic_bytes_per_launch"] == int(alg[1] / 2)
-    assert np.isclose(rf["achieved"], round(alg[1] / 2 / 3e-3 / 1e9, 1))
+    edges, written = bench.walk_bytes(g, 128, 1), 16 * len(g["op_rank"]) * 128
+    assert rf["algorithmic_bytes_per_launch"] == written // 2
+    assert np.isclose(rf["achieved"], round(written / 2 / 3e-3 / 1e9, 1))
     assert rf["kernel"] == "k_walk<1, true, false>" and rf["traffic"] is None
     assert [p["kernel"] for p in rf["passes"]] == ["k_walk<0, false, false>", "k_walk<1, true, false>"]
-    assert rf["passes"][0]["alg_frac"] == round(alg[0] / 4e-3 / 1e9 / bench.HBM_PEAK_GBS, 4)
+    assert rf["passes"][1]["alg_frac"] == round(written / 6e-3 / 1e9 / bench.HBM_PEAK_GBS, 4)
+    assert rf["passes"][0]["alg_frac"] is None
+    assert [p["edge_model_bytes"] for p in rf["passes"]] == edges
+    assert rf["passes"][0]["covers"] == ["k_sum", "k_walk<0, false, false>"]
+    assert rf["covers"] == ["k_walk<1, true, false>", "k_expand"]
 
 
 def test_pass_summary_groups_and_drops_skipped_passes():
@@ -100,6 +104,13 @@ def test_walk_kernel_names_follow_the_library_variants():
     assert bench.walk_kernel_name(True, True, False, False, tiles, tiles) == "k_walk<1, true, false>"
     assert bench.walk_kernel_name(True, False, False, True, 1) == "k_walk<3, false, false>"
     assert bench.walk_kernel_name(True, True, False, True, 1) == "k_walk<3, true, false>"
+    assert bench.walk_kernel_name(False, True, False, False, 8, 1, ops=True) == "k_walk<4, true, false>"
+    assert bench.walk_kernel_name(False, True, True, False, 8, 1, ops=True) == "k_walk<0, true, true>"
+    assert bench.walk_kernel_name(True, True, False, False, 8, 1, ops=True) == "k_walk<2, true, false>"
+    host = (ROOT / "paper_2412_12487_amd" / "csrc" / "echo_host.cpp").read_text()
+    assert int(re.search(r"constexpr int64_t kOpsEvals = (\d+);", host).group(1)) == bench.OPS_EVALS
+    assert bench.sweep_of_ops(4800, 10, 8, 100, 1) and not bench.sweep_of_ops(4799, 10, 8, 100, 1)
+    assert not bench.sweep_of_ops(4800, 10, 8, 100, 2) and not bench.sweep_of_ops(4800, 10, 4097, 100, 1)
     hdr = (ROOT / "paper_2412_12487_amd" / "csrc" / "echo_internal.h").read_text()
     assert int(re.search(r"constexpr int kFlagRowTiles = (\d+);", hdr).group(1)) == tiles
 
