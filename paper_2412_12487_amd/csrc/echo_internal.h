@@ -290,7 +290,6 @@ struct WalkArgs {
     const WalkItem *items;
     const int64_t *round_off;        // [walker + 1]
     const int32_t *rows;             // [round][kDurs] last op of its segments
-    const int32_t *rec_rows;         // [round][kDurs] their first records
     const RowPair *far;
     const int32_t *c_N;              // [counted coll] member ops present (arrivals that complete the barrier)
     const int32_t *block_class;
@@ -298,7 +297,7 @@ struct WalkArgs {
     const int64_t *class_cost;       // [class][scen]
     const SegRec *recs;
     const RecChunk *chunks;
-    int64_t n_chunks, n_recs;
+    int64_t n_chunks;
     // Per-op outputs of overlap detection, one row per segment record of a flagged segment,
     // mstride columns (the tiles' scenarios, padded to whole tiles):
     const uint8_t *tmask;            // overlap type masks, or null
@@ -320,6 +319,10 @@ struct WalkArgs {
     int32_t in;                      // what the pass is refined by (kIn*)
     int32_t final_pass;              // accumulate step time (and digest)
     int32_t timelines;               // final pass: write every op's start and finish
+    // kInOps only, and last: among the fields above they moved the argument loads of every
+    // variant (a fixed point's sweeps took 2 % longer)
+    const int32_t *rec_rows;         // [round][kDurs] first records of the round's segments
+    int64_t n_recs;
 };
 
 
