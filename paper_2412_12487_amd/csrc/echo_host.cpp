@@ -1161,7 +1161,8 @@ int enqueue_compose(echo_graph g, const echo_scenario *d_scen, int32_t n_scen, c
     if (d_refinements && (e = launch_fill_i32(d_refinements, ns, until_stable ? 0 : n_refine, stream)))
         return hip_fail(e, "fill kernel");
     for (int32_t p = 0; p <= n_refine; ++p) {
-        // tiles per walk launch: every rank block of a tile must be co-resident
+        // tiles per walk launch: every rank block of a tile must be co-resident (one block per tile
+        // need not be; its launches are cut at the same count, which keeps them below 2^32 threads)
         const bool fin = p == n_refine;
         const int64_t cap = g->capacity[walk_variant(walk_input(p > 0, ext, false), fin, d_digest != nullptr)];
         int64_t per_launch = std::max<int64_t>(1, std::min<int64_t>(n_tiles, cap / g->dg.n_blocks));

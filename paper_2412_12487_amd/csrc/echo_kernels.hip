@@ -233,8 +233,8 @@ __global__ __launch_bounds__(64) void k_cc_cost(CollTable t, const echo_cc_table
 // Cost of every collective: its class's, from the row of the class's first collective.  The
 // 64-bit divisions and 128-bit products of the model (about a thousand instructions per
 // class and scenario) then run once per class; what is left is bound by the stores (23,808
-// collectives of 19 classes x 4000 scenarios, 762 MB: 1.88 ms when every collective was
-// costed by itself, 0.14 now).  T: two scenarios per store where rows are 16-byte aligned.
+// collectives of 19 classes x 4000 scenarios, 762 MB: 1.88 ms per call when every collective
+// was costed by itself, 0.16 now).  T: two scenarios per store where rows are 16-byte aligned.
 template <class T>
 __global__ __launch_bounds__(256) void k_cc_spread(const int32_t *class_of, const int32_t *row, int64_t n,
                                                    int32_t per_row, T *cost) {
@@ -414,16 +414,17 @@ __device__ __forceinline__ Lane make_lane(const echo_scenario *scen, int32_t n_s
 // the comm ops' share of the digest).
 //
 // What bounds it: latency.  The sweep is one chain of segments and barriers per
-// scenario tile (on the 1024-rank workload 1.5 thousand segments and 2.7 thousand
-// barriers long), and a wavefront runs its items one after the other.  So an item costs its
-// instructions, and everything an item could wait for is fetched well before: items a round
-// (32) ahead, segment durations a group (kDurs) ahead, both settled by one wait each.
+// scenario tile (on the 1024-rank workload the longest passes 1135 barriers in LDS and 265 in
+// device memory), and a wavefront runs its items one after the other.  So an item costs its
+// instructions, and everything an item could wait for is fetched a round (32 items, kDurs
+// segments) ahead and settled by one wait.
 //
 // kInOps is bound by its stores once enough wavefronts share the chip: with draws, barriers and
-// stores of different wavefronts side by side 1024 ranks x 256 scenarios take 11.5 ms (65 GB at 5.7 TB/s)
-// where k_sum, this sweep and k_expand one after another take 15.1; 640 x 768 4.7 and 6.2.  All its stores
-// are non-temporal (with the last finish of a segment and the comm ops' times through the cache
-// 32 ranks x 5000 take 0.90 instead of 0.83 ms, 1024 x 256 11.9 instead of 11.5).
+// stores of different wavefronts side by side 1024 ranks x 256 scenarios take 11.5 to 14.0 ms, by how
+// the two arrays lie in memory (65 GB at 4.7 to 5.7 TB/s), where k_sum, this sweep and k_expand one
+// after another take 15.0 to 17.0; 640 x 768 4.7 and 6.2.  All its stores are non-temporal (with
+// the last finish of a segment and the comm ops' times through the cache 32 ranks x 5000 take
+// 0.90 instead of 0.83 ms, 1024 x 256 11.9 instead of 11.5).
 template <int IN, bool FINAL, bool DIGEST>
 __global__ __launch_bounds__(kBlockWalkers * 64) __attribute__((amdgpu_waves_per_eu(4))) void k_walk(WalkArgs a) {
     constexpr bool OPS = IN == kInOps, REFINED = IN != kInNone && !OPS;
@@ -799,8 +800,8 @@ __device__ __forceinline__ int4 load_chunk(const WalkArgs &a, int64_t chunk, int
 }
 
 // First pass, tiles with jitter: the sum of each segment's jittered durations, into the
-// finish row of its last op.  Bound by the draws (21 vector instructions per op and
-// scenario); the records of the next chunk are fetched while the current one is summed.
+// finish row of its last op.  Bound by the draws (25 vector instructions per op and
+// wavefront); the records of the next chunk are fetched while the current one is summed.
 __global__ __launch_bounds__(kRecWaves * 64) void k_sum(WalkArgs a, int64_t parts) {
     const int lane = threadIdx.x & 63;
     const int64_t unit = (int64_t)blockIdx.x * kRecWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -845,8 +846,9 @@ __global__ __launch_bounds__(kRecWaves * 64) void k_sum(WalkArgs a, int64_t part
 // After the last pass: the start and finish of every op that the sweep has not written (all
 // but each segment's first start and last finish), and with DIGEST the segments' share of
 // the digest.  IN: what flagged segments carry per op -- nothing (no refinement), overlap
-// masks, or extra times.  Bound by the timeline stores (57 GB in 11.8 ms on the
-// 1024-rank workload; a store-only probe of its pattern takes 10.2 at 5.6 TB/s).  An op's finish is the
+// masks, or extra times.  Bound by the timeline stores (57 GB in 11.9 ms on the
+// 1024-rank workload, its wavefronts 68 % of their cycles waiting to issue; a store-only probe
+// of the pattern takes 10.2 at 5.6 TB/s).  An op's finish is the
 // next op's start, so a step of the loop is one draw and two stores, the last op of a segment
 // takes neither, and the lanes compute the chunk's row addresses once.
 template <int IN, bool DIGEST>
