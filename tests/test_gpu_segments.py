@@ -174,6 +174,50 @@ def test_unrefined_timelines_from_the_sweep_of_the_ops(E, seed, rpw, cap):
             np.testing.assert_array_equal(G.compose(d, n, 0, timelines=False)["step"].cpu().numpy(), ref["step"])
 
 
+def test_sweep_of_the_ops_and_direct_costs_in_a_hip_graph(E):
+    """An unrefined compose on the sweep of the ops (three workgroups: a cooperative launch) and a
+    small echo_cc_cost, captured and replayed with eager work between the replays."""
+    import ctypes
+    import torch
+    ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+    g = spmd_graph(0, steps=2, buckets=1)
+    with E.Graph(g, 0) as G:
+        n = -(-48_000 * G.n_levels // G.n_ops)
+        sc = scenarios.draw(n, np.random.default_rng(5), bw_inter=(5_000, 400_000), jitter=(9000, 5))
+        d, n = E.scenarios_to_device(sc)
+        out = {k: torch.full((G.n_ops, n) if k != "step" else (n,), -1, dtype=torch.int64, device="cuda:0")
+               for k in ("start", "finish", "step")}
+        cost = torch.full((G.n_colls, n), -1, dtype=torch.int64, device="cuda:0")
+
+        def calls():
+            G.compose(d, n, 0, out=out, check=False)
+            rc = E.lib().echo_cc_cost(G.handle, ptr(d), n, ptr(cost),
+                                      ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+            assert rc == E.ECHO_OK
+
+        torch.cuda.synchronize()
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            calls()                                # sizes the workspace
+        torch.cuda.synchronize()
+        ref = oracle.run(g, sc, 0, threads=THREADS, costs=True)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            calls()
+        for _ in range(3):
+            for v in (*out.values(), cost):
+                v.fill_(-1)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(out["step"].cpu().numpy(), ref["step"])
+            np.testing.assert_array_equal(out["start"].cpu().numpy().T, ref["start"])
+            np.testing.assert_array_equal(out["finish"].cpu().numpy().T, ref["finish"])
+            np.testing.assert_array_equal(cost.cpu().numpy().T, ref["cost"])
+        G.sync_status()
+        del graph
+
+
 def test_digest_alone_and_one_output_alone(E):
     """Digest without timelines, and start or finish alone through the C ABI."""
     import ctypes
