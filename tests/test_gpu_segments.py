@@ -145,7 +145,9 @@ def test_collectives_on_compute_streams(E, seed, rpw):
 def test_unrefined_timelines_from_the_sweep_of_the_ops(E, seed, rpw, cap):
     """From 48,000 evaluations per level and rank of a walker on (of one launch) the sweep walks the
     ops themselves: just below that line, at it and above, ragged tiles, base durations above
-    2^32 ns, launches of a few tiles (cap), the allocation-free entry point and no timelines."""
+    2^32 ns, launches of a few tiles (cap), the allocation-free entry point, one output alone and
+    no timelines."""
+    import ctypes
     import torch
     rng = np.random.default_rng(seed)
     g = shared_streams(np.random.default_rng(0)) if seed == 5 else spmd_graph(seed, steps=2, buckets=1, shared=seed == 4)
@@ -167,6 +169,14 @@ def test_unrefined_timelines_from_the_sweep_of_the_ops(E, seed, rpw, cap):
             outs = [out]
             if seed == 0:
                 outs.append(G.compose_static(d, n, 0, {k: torch.full_like(v, -1) for k, v in out.items()}))
+                alone = {k: torch.full_like(out[k], -1) for k in ("start", "finish")}     # one output each
+                ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+                for k in alone:
+                    rc = E.lib().echo_compose_batch(G.handle, ptr(d), n, 0, ptr(alone[k]) if k == "start" else None,
+                                                    ptr(alone[k]) if k == "finish" else None, ptr(out["step"]), None,
+                                                    ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+                    assert rc == E.ECHO_OK
+                outs.append({"step": out["step"], **alone})
             for o in outs:
                 np.testing.assert_array_equal(o["step"].cpu().numpy(), ref["step"])
                 np.testing.assert_array_equal(o["start"].cpu().numpy().T, ref["start"])
